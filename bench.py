@@ -66,11 +66,15 @@ def gemm_flops(case, t: int):
     return base, (base if pen else 0.0)
 
 
+def pass_peaks(prec: str):
+    """Peaks of the two passes: fp32 graphs run both in fp32, the others A.S (0/1 operands, exact)
+    in fp4 and the penalty pass in bf16."""
+    return (PEAK["fp32"], PEAK["fp32"]) if prec == "fp32" else (PEAK["fp4"], PEAK["bf16"])
+
+
 def mixed_peak(prec: str, f_as: float, f_pen: float) -> float:
-    """Peak of a launch whose A.S pass runs at the operand dtype and whose penalty pass runs
-    in bf16 (fp8 and fp4 precision) or the operand dtype: total flops over the ideal time."""
-    p_as = PEAK[prec]
-    p_pen = PEAK["bf16"] if prec in ("fp8", "fp4") else PEAK[prec]
+    """Peak of a launch of both passes: total flops over the ideal time."""
+    p_as, p_pen = pass_peaks(prec)
     ideal = f_as / p_as + f_pen / p_pen
     return (f_as + f_pen) / ideal
 
@@ -238,8 +242,8 @@ def run_batch(args, torch, pk):
                      "kernel": f"k_gemm over the {G} graphs (A.S pass + fitness gather + G store, and the bf16 "
                                f"penalty pass of the {dense_graphs:g} graphs on the dense route)",
                      "flops_per_launch": f_as + f_pen, "ms_per_launch": ph["gemm"]},
-        "roofline_as_only": {"bound": "mfma", "achieved": f_as / as_s / 1e12, "peak": PEAK[prec] / 1e12,
-                             "unit": "TFLOP/s", "frac": f_as / as_s / PEAK[prec], "ms_per_launch": ph["gemm_as_only"],
+        "roofline_as_only": {"bound": "mfma", "achieved": f_as / as_s / 1e12, "peak": pass_peaks(prec)[0] / 1e12,
+                             "unit": "TFLOP/s", "frac": f_as / as_s / pass_peaks(prec)[0], "ms_per_launch": ph["gemm_as_only"],
                              "kernel": f"k_gemm A.S pass alone over the {G} graphs (no gather, no store), "
                                        f"back to back"},
         "phases_ms": ph,
@@ -353,8 +357,8 @@ def main():
     s.close()
     # the same fractions against this device's measured MFMA throughput (register-operand
     # chains on every CU, no memory traffic), beside the published peaks above
-    pm_as = max(pk.mfma_peak(PREC[prec]) for _ in range(3)) * 1e12
-    pm_pen = max(pk.mfma_peak(tcolgen.BF16) for _ in range(3)) * 1e12 if prec in ("fp8", "fp4") else pm_as
+    pm_as = max(pk.mfma_peak(tcolgen.FP32 if prec == "fp32" else tcolgen.FP4) for _ in range(3)) * 1e12
+    pm_pen = max(pk.mfma_peak(tcolgen.BF16) for _ in range(3)) * 1e12 if prec != "fp32" else pm_as
     n_it = args.steps
     n_d = routes["dense"]
     mixed_m = (n_it * f_as + n_d * f_pen) / (n_it * f_as / pm_as + n_d * f_pen / pm_pen)
@@ -431,8 +435,7 @@ def contraction_roofline(case, prec, opts, ph, routes):
     t_d, t_o = ph["gemm"] / 1e3, ph["gemm_as_store"] / 1e3
     flops = (n_d + n_o) * f_as + n_d * f_pen
     secs = n_d * t_d + n_o * t_o
-    p_as = PEAK[prec]
-    p_pen = PEAK["bf16"] if prec in ("fp8", "fp4") else PEAK[prec]
+    p_as, p_pen = pass_peaks(prec)
     peak = flops / ((n_d + n_o) * f_as / p_as + n_d * f_pen / p_pen)
     achieved = flops / secs
     launches = {

@@ -88,9 +88,8 @@ enum { TCOL_KCOL = 0, TCOL_ECP = 1, TCOL_KPART = 2, TCOL_BKPART = 3, TCOL_MSCP =
 /* Operand precision of the contractions A.S and (penalty).S.  The 0/1
  * operands A and S are exact in every format and accumulate in FP32, so the
  * conflict counts are exact in all four; the penalty operand is rounded to
- * bf16 in TCOL_BF16, TCOL_FP8 and TCOL_FP4 (TCOL_FP8 runs A.S in fp8 e4m3,
- * TCOL_FP4 in fp4 e2m1, both with the penalty product in bf16).  Softmax,
- * gradient and update are FP32. */
+ * bf16 in TCOL_BF16, TCOL_FP8 and TCOL_FP4, which all run A.S in fp4 e2m1 and
+ * the penalty product in bf16.  Softmax, gradient and update are FP32. */
 enum { TCOL_FP32 = 0, TCOL_BF16 = 1, TCOL_FP8 = 2, TCOL_FP4 = 3 };
 
 /* Parameters of one graph (parameter table of the paper: eta 1e-3, nb_iter 5,

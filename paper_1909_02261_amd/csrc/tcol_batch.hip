@@ -164,8 +164,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
 // ------------------------------------------------------------------ dispatch --
 
 #define TCOL_BATCH_KERNELS(X) \
-    X(kPrecFP32, 8) X(kPrecBF16, 8) X(kPrecFP8, 8) X(kPrecFP4, 8) \
-    X(kPrecFP32, 36) X(kPrecBF16, 36) X(kPrecFP8, 36) X(kPrecFP4, 36)
+    X(kPrecFP32, 8) X(kPrecFP4, 8) X(kPrecFP32, 36) X(kPrecFP4, 36)
 
 int batch_kpl(int kmax) {
     const int need = (kmax + 15) / 16;

@@ -3,7 +3,7 @@
 // with S_cat = [S_1 ... S_D] (n x D*k, stored transposed as S^T [D*k][n_pad])
 // and P the penalty operand built by the group-concentration kernel.
 //
-// A and S are 0/1, so A.S is exact in fp32, bf16, fp8 and fp4 operands with FP32
+// A and S are 0/1, so A.S is exact in fp32 and fp4 operands with FP32
 // accumulation; between the two passes each block gathers (A.S_d)[i, c_d(i)]
 // into 2 f_color(S_d) (the gradient's first term is the TabuCol gamma matrix,
 // whose entry at the vertex's own colour counts its conflicts).
@@ -37,12 +37,9 @@ typedef int i32x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 
 // one MFMA step on a 16x16 output subtile for each operand format
-__device__ inline f32x4 mfma_fp8(const i32x8& a, const i32x8& b, const f32x4& c) {
-    // operand formats 0/0 = fp8 e4m3; zero scale arguments select the unscaled instruction
-    return __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(a, b, c, 0, 0, 0, 0, 0, 0);
-}
 __device__ inline f32x4 mfma_fp4(const i32x8& a, const i32x8& b, const f32x4& c) {
-    // operand formats 4/4 = fp4 e2m1 (the low four registers of each operand)
+    // operand formats 4/4 = fp4 e2m1 (the low four registers of each operand); zero scale
+    // arguments select the unscaled instruction
     return __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(a, b, c, 4, 4, 0, 0, 0, 0);
 }
 __device__ inline f32x4 mfma_bf16(const bf16x8& a, const bf16x8& b, const f32x4& c) {
@@ -83,40 +80,27 @@ struct Tile {
 };
 
 // Fragments of one LDS stage for one wave (chunk c of row r sits at slot c ^ ((r >> 1) & 7)).
-// A stage is one K-step of the 16x16x128 fp8 MFMA (32 bytes per lane: chunks 2q and
-// 2q+1) or two K-steps of 16 bytes per lane (chunk 4 ks + q) for fp4 (16x16x128),
-// bf16 (16x16x32) and fp32 (four 16x16x4); A and B use the same chunks, so every
-// format sums the plain product.
+// A stage is two K-steps of 16 bytes per lane (chunk 4 ks + q): one 16x16x128 MFMA each in fp4,
+// four 16x16x4 in fp32; A and B use the same chunks, so both formats sum the plain product.
 template <int PREC, int BM, int NTW>
 struct StageFrags {
     static constexpr int MT = Tile<BM, NTW>::MT;
-    static constexpr int SUB = PREC == kPrecFP8 ? 1 : 2;   // K-steps per stage
-    static constexpr int W = PREC == kPrecFP8 ? 2 : 1;     // 16-byte chunks per fragment
-    uint4 a[SUB][MT][W], b[SUB][NTW][W];
+    uint4 a[2][MT], b[2][NTW];
 };
 
 template <int PREC, int BM, int NTW>
 __device__ __forceinline__ void stage_read(StageFrags<PREC, BM, NTW>& F, const uint8_t* L, int lane, int wm, int wn) {
-    using Fr = StageFrags<PREC, BM, NTW>;
     const int ra = wm * Tile<BM, NTW>::RW + (lane & 15);
     const int rb = BM + wn * (NTW * 16) + (lane & 15);
     const int q = lane >> 4;
     const int swz = (lane & 15) >> 1;  // = (row >> 1) & 7 for every row this lane reads
 #pragma unroll
-    for (int ks = 0; ks < Fr::SUB; ++ks) {
+    for (int ks = 0; ks < 2; ++ks) {
+        const int o = ((ks * 4 + q) ^ swz) * 16;
 #pragma unroll
-        for (int w = 0; w < Fr::W; ++w) {
-            const int o = ((Fr::W == 2 ? 2 * q + w : ks * 4 + q) ^ swz) * 16;
+        for (int mt = 0; mt < Tile<BM, NTW>::MT; ++mt) F.a[ks][mt] = *(const uint4*)(L + (ra + mt * 16) * kStageRowBytes + o);
 #pragma unroll
-            for (int mt = 0; mt < Fr::MT; ++mt) F.a[ks][mt][w] = *(const uint4*)(L + (ra + mt * 16) * kStageRowBytes + o);
-        }
-#pragma unroll
-        for (int nt = 0; nt < NTW; ++nt)
-#pragma unroll
-            for (int w = 0; w < Fr::W; ++w) {
-                const int o = ((Fr::W == 2 ? 2 * q + w : ks * 4 + q) ^ swz) * 16;
-                F.b[ks][nt][w] = *(const uint4*)(L + (rb + nt * 16) * kStageRowBytes + o);
-            }
+        for (int nt = 0; nt < NTW; ++nt) F.b[ks][nt] = *(const uint4*)(L + (rb + nt * 16) * kStageRowBytes + o);
     }
 }
 
@@ -139,53 +123,39 @@ __device__ __forceinline__ void kstep_read(KStepFrags<PREC, BM, NTW>& F, const u
     for (int nt = 0; nt < NTW; ++nt) F.b[nt] = *(const uint4*)(L + (rb + nt * 16) * kStageRowBytes + o);
 }
 
+// acc += a . b over one K-step of 16 bytes per lane
+template <int PREC>
+__device__ __forceinline__ f32x4 frag_mma(const uint4& a0, const uint4& b0, f32x4 c) {
+    if constexpr (PREC == kPrecFP4) {
+        const i32x8 a{(int)a0.x, (int)a0.y, (int)a0.z, (int)a0.w, 0, 0, 0, 0};
+        const i32x8 b{(int)b0.x, (int)b0.y, (int)b0.z, (int)b0.w, 0, 0, 0, 0};
+        return mfma_fp4(a, b, c);
+    } else {
+        const float4 a = __builtin_bit_cast(float4, a0), b = __builtin_bit_cast(float4, b0);
+        c = mfma_f32(a.x, b.x, c);
+        c = mfma_f32(a.y, b.y, c);
+        c = mfma_f32(a.z, b.z, c);
+        return mfma_f32(a.w, b.w, c);
+    }
+}
+
 template <int PREC, int BM, int NTW>
 __device__ __forceinline__ void kstep_mma(f32x4 (&acc)[tile_mt(BM)][NTW], const KStepFrags<PREC, BM, NTW>& F) {
-    static_assert(PREC == kPrecFP4 || PREC == kPrecBF16, "fp4 and bf16 stages hold two K-steps");
 #pragma unroll
     for (int nt = 0; nt < NTW; ++nt)
 #pragma unroll
-        for (int mt = 0; mt < Tile<BM, NTW>::MT; ++mt) {
-            const uint4 a0 = F.a[mt], b0 = F.b[nt];
-            if constexpr (PREC == kPrecFP4) {
-                const i32x8 a{(int)a0.x, (int)a0.y, (int)a0.z, (int)a0.w, 0, 0, 0, 0};
-                const i32x8 b{(int)b0.x, (int)b0.y, (int)b0.z, (int)b0.w, 0, 0, 0, 0};
-                acc[mt][nt] = mfma_fp4(a, b, acc[mt][nt]);
-            } else {
-                acc[mt][nt] = mfma_bf16(__builtin_bit_cast(bf16x8, a0), __builtin_bit_cast(bf16x8, b0), acc[mt][nt]);
-            }
-        }
+        for (int mt = 0; mt < Tile<BM, NTW>::MT; ++mt) acc[mt][nt] = frag_mma<PREC>(F.a[mt], F.b[nt], acc[mt][nt]);
 }
 
 template <int PREC, int BM, int NTW>
 __device__ __forceinline__ void stage_mma(f32x4 (&acc)[tile_mt(BM)][NTW], const StageFrags<PREC, BM, NTW>& F) {
-    using Fr = StageFrags<PREC, BM, NTW>;
 #pragma unroll
-    for (int ks = 0; ks < Fr::SUB; ++ks)
+    for (int ks = 0; ks < 2; ++ks)
 #pragma unroll
         for (int nt = 0; nt < NTW; ++nt)
 #pragma unroll
-            for (int mt = 0; mt < Fr::MT; ++mt) {
-                const uint4 a0 = F.a[ks][mt][0], b0 = F.b[ks][nt][0];
-                if constexpr (PREC == kPrecFP8) {
-                    const uint4 a1 = F.a[ks][mt][Fr::W - 1], b1 = F.b[ks][nt][Fr::W - 1];
-                    const i32x8 a{(int)a0.x, (int)a0.y, (int)a0.z, (int)a0.w, (int)a1.x, (int)a1.y, (int)a1.z, (int)a1.w};
-                    const i32x8 b{(int)b0.x, (int)b0.y, (int)b0.z, (int)b0.w, (int)b1.x, (int)b1.y, (int)b1.z, (int)b1.w};
-                    acc[mt][nt] = mfma_fp8(a, b, acc[mt][nt]);
-                } else if constexpr (PREC == kPrecFP4) {
-                    const i32x8 a{(int)a0.x, (int)a0.y, (int)a0.z, (int)a0.w, 0, 0, 0, 0};
-                    const i32x8 b{(int)b0.x, (int)b0.y, (int)b0.z, (int)b0.w, 0, 0, 0, 0};
-                    acc[mt][nt] = mfma_fp4(a, b, acc[mt][nt]);
-                } else if constexpr (PREC == kPrecBF16) {
-                    acc[mt][nt] = mfma_bf16(__builtin_bit_cast(bf16x8, a0), __builtin_bit_cast(bf16x8, b0), acc[mt][nt]);
-                } else {
-                    const float4 a = __builtin_bit_cast(float4, a0), b = __builtin_bit_cast(float4, b0);
-                    acc[mt][nt] = mfma_f32(a.x, b.x, acc[mt][nt]);
-                    acc[mt][nt] = mfma_f32(a.y, b.y, acc[mt][nt]);
-                    acc[mt][nt] = mfma_f32(a.z, b.z, acc[mt][nt]);
-                    acc[mt][nt] = mfma_f32(a.w, b.w, acc[mt][nt]);
-                }
-            }
+            for (int mt = 0; mt < Tile<BM, NTW>::MT; ++mt)
+                acc[mt][nt] = frag_mma<PREC>(F.a[ks][mt], F.b[ks][nt], acc[mt][nt]);
 }
 
 typedef const __attribute__((address_space(1))) void* gbl_ptr;
@@ -240,7 +210,7 @@ __device__ __forceinline__ void stage_barrier() {
 // reads of stage s+1 proceed while the MFMAs of stage s run.  At the top of
 // iteration s every wave has finished reading stage s, so its buffer takes the
 // loads of stage s+NB.  Large tiles, whose two fragment sets would spill, keep one:
-// in fp4 and bf16 (two K-steps per stage) they put the barrier between the K-steps.
+// in fp4 they put the barrier between a stage's two K-steps.
 template <int PREC, int BM, int NTW>
 __device__ __forceinline__ void gemm_sweep(f32x4 (&acc)[tile_mt(BM)][NTW], const uint8_t* __restrict__ Arow,
                                            const uint8_t* __restrict__ Brow, size_t ld, int nstages,
@@ -250,9 +220,9 @@ __device__ __forceinline__ void gemm_sweep(f32x4 (&acc)[tile_mt(BM)][NTW], const
     const int tid = threadIdx.x;
     const int lane = tid & 63, wave = tid >> 6;
     const int wm = wave >> 1, wn = wave & 1;
-    if constexpr (Fr::SUB * (Fr::MT + NTW) * Fr::W * 4 > 64 && Fr::SUB == 2 && PREC != kPrecFP32) {
-        // fp4 and bf16 tiles whose stage fragments would not fit twice in registers (two
-        // K-steps per stage): the barrier falls between the K-steps.  The second K-step's fragments
+    if constexpr (2 * (Fr::MT + NTW) * 4 > 64 && PREC != kPrecFP32) {
+        // fp4 tiles whose stage fragments would not fit twice in registers: the barrier falls
+        // between the two K-steps.  The second K-step's fragments
         // are read before it and its MFMAs run after it, while the next stage's first
         // K-step is read; the buffer freed at the barrier takes the loads of stage s+NB
         // at once, so a load has a whole stage of MFMAs to land.  Two K-step sets hold
@@ -281,8 +251,8 @@ __device__ __forceinline__ void gemm_sweep(f32x4 (&acc)[tile_mt(BM)][NTW], const
             kstep_mma<PREC, BM, NTW>(acc, Fb);
         }
         return;
-    } else if constexpr (Fr::SUB * (Fr::MT + NTW) * Fr::W * 4 > 64) {
-        // fp8 and fp32 tiles whose fragments would not fit twice in registers: one
+    } else if constexpr (2 * (Fr::MT + NTW) * 4 > 64) {
+        // fp32 tiles whose fragments would not fit twice in registers: one
         // fragment set, the global -> LDS loads NB - 1 stages ahead (fp32, whose K-step is
         // four MFMAs, ran 8 % slower at C5 in the staggered form)
         constexpr int NB = T::NB;
@@ -335,7 +305,7 @@ __device__ __forceinline__ void gemm_sweep(f32x4 (&acc)[tile_mt(BM)][NTW], const
     }
 }
 
-// ---- penalty pass of the fp4 mode: P (bf16) against S^T straight from the fp4 operand ----
+// ---- penalty pass of the fp4 form: P (bf16) against S^T straight from the fp4 operand ----
 //
 // A K-stage covers 64 K-values: 128 bytes of each P row (as in the sweep above) and 32
 // bytes of each S^T row in fp4, whose 0/1 nibbles (1.0 = 0x2) become bf16 in registers
@@ -593,7 +563,8 @@ __device__ __forceinline__ void gemm_tile(const GraphDev* __restrict__ gd, int g
         for (int nt = 0; nt < NTW; ++nt) acc[mt][nt] = f32x4{0.f, 0.f, 0.f, 0.f};
 
     const size_t ld = op_row_bytes(PREC, d.n_pad);
-    const int nst = (int)(ld / kStageRowBytes);
+    // stages up to the last vertex (the operands are zero from n to n_pad)
+    const int nst = ceil_div(n, (int)(d.n_pad * (size_t)kStageRowBytes / ld));
 
     // per-lane columns: member and colour of each 16-column subtile
     int cm[NTW], cl[NTW];
@@ -660,12 +631,7 @@ __device__ __forceinline__ void gemm_tile(const GraphDev* __restrict__ gd, int g
             // bf16 P against the fp4 S^T operand itself
             const size_t ld2 = (size_t)d.n_pad * 2;
             pen_sweep<BM, NTW>(acc, (const uint8_t*)d.Pop + (size_t)m0 * ld2,
-                               (const uint8_t*)d.Sop[pS] + (size_t)n0 * ld, ld2, ld, d.n_pad / 64, lds);
-        } else if constexpr (PREC == kPrecFP8) {
-            const size_t ld2 = (size_t)d.n_pad * 2;
-            gemm_sweep<kPrecBF16, BM, NTW>(acc, (const uint8_t*)d.Pop + (size_t)m0 * ld2,
-                                           (const uint8_t*)d.Sp2[pS] + (size_t)n0 * ld2, ld2,
-                                           d.n_pad * 2 / kStageRowBytes, lds);
+                               (const uint8_t*)d.Sop[pS] + (size_t)n0 * ld, ld2, ld, ceil_div(n, 64), lds);
         } else {
             gemm_sweep<PREC, BM, NTW>(acc, (const uint8_t*)d.Pop + (size_t)m0 * ld,
                                       (const uint8_t*)d.Sop[pS] + (size_t)n0 * ld, ld, nst, lds);
@@ -907,12 +873,8 @@ static hipError_t launch_one(const GraphDev* gd, int G, int total_tiles, int hon
 static hipError_t gemm_dispatch(int op, const GemmShape& s, const GraphDev* gd, int G, int total_tiles,
                                 int honor_stop, int passes, int cstage, hipStream_t st, size_t* lds_out) {
     TCOL_GEMM_SHAPES(TCOL_GEMM_CASE, kPrecFP32, 0)
-    TCOL_GEMM_SHAPES(TCOL_GEMM_CASE, kPrecBF16, 0)
-    TCOL_GEMM_SHAPES(TCOL_GEMM_CASE, kPrecFP8, 0)
     TCOL_GEMM_SHAPES(TCOL_GEMM_CASE, kPrecFP4, 0)
     TCOL_GEMM_SHAPES(TCOL_GEMM_CASE, kPrecFP32, 1)
-    TCOL_GEMM_SHAPES(TCOL_GEMM_CASE, kPrecBF16, 1)
-    TCOL_GEMM_SHAPES(TCOL_GEMM_CASE, kPrecFP8, 1)
     TCOL_GEMM_SHAPES(TCOL_GEMM_CASE, kPrecFP4, 1)
     return hipErrorInvalidValue;
 }

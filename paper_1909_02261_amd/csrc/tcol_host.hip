@@ -41,7 +41,7 @@ constexpr int kMaxLdsBytes = 160 * 1024;
 inline size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 
 enum Buf {
-    B_LUT_PEN, B_LUT_BON, B_LUT_KA, B_LUT_VB, B_DEM, B_SEL, B_W2, B_A8, B_AOP, B_POP, B_S0, B_S1, B_SP0, B_SP1, B_C0, B_C1,
+    B_LUT_PEN, B_LUT_BON, B_LUT_KA, B_LUT_VB, B_DEM, B_SEL, B_W2, B_A8, B_AOP, B_POP, B_S0, B_S1, B_C0, B_C1,
     B_V0, B_V1, B_G, B_F2, B_F2P, B_FCOL, B_FEQ, B_F, B_PART, B_SNAP, B_CT, B_CLSV, B_CLSOFF, B_CINFO, B_SQ, B_VEL, B_COUNT
 };
 
@@ -61,7 +61,7 @@ Layout make_layout(const tcol_graph_params& p) {
     L.rows_S = round_up(p.D * p.k, 16) + kSRowSlack;
     // group-concentration tiles: 32 x 32 for small graphs (more blocks), else 64 x 64
     L.mt_ts = L.n_pad <= 2048 ? 32 : 64;
-    L.mt_T = L.n_pad / L.mt_ts;
+    L.mt_T = ceil_div(p.n, L.mt_ts);   // the operand stays zero past them
     L.mt_tiles = L.mt_T * (L.mt_T + 1) / 2;
     const size_t n2 = (size_t)L.n_pad * L.n_pad;
     const size_t dnk = (size_t)p.D * p.n * p.k;
@@ -77,10 +77,9 @@ Layout make_layout(const tcol_graph_params& p) {
     sz[B_SEL] = cm > 1 ? sizeof(int16_t) * ((size_t)p.D * cm * round_up(p.n, 64) + 64) : 0;
     sz[B_W2] = sizeof(float) * dnk;
     sz[B_A8] = n2;
-    sz[B_AOP] = (size_t)L.n_pad * op_row_bytes(p.precision, L.n_pad);
+    sz[B_AOP] = (size_t)L.n_pad * op_row_bytes(op_prec(p.precision), L.n_pad);
     sz[B_POP] = n2 * (p.precision == TCOL_FP32 ? 4 : 2);
-    sz[B_S0] = sz[B_S1] = (size_t)L.rows_S * op_row_bytes(p.precision, L.n_pad);
-    sz[B_SP0] = sz[B_SP1] = prec_split(p.precision) ? (size_t)L.rows_S * L.n_pad * 2 : 0;
+    sz[B_S0] = sz[B_S1] = (size_t)L.rows_S * op_row_bytes(op_prec(p.precision), L.n_pad);
     sz[B_C0] = sz[B_C1] = sizeof(int16_t) * ((size_t)p.D * round_up(p.n, 64) + 64);
     sz[B_V0] = sz[B_V1] = sizeof(int32_t) * (size_t)p.D * p.k;
     sz[B_G] = sizeof(float) * dnk;
@@ -219,10 +218,11 @@ static void drop_graphs(tcol_ctx* c) {
     c->graph_fused = -1;
 }
 
-static int common_precision(const tcol_ctx* c) {
-    int prec = c->params[0].precision;
+// operand format shared by every graph of the context, or -1
+static int common_op(const tcol_ctx* c) {
+    const int prec = op_prec(c->params[0].precision);
     for (auto& p : c->params)
-        if (p.precision != prec) return -1;
+        if (op_prec(p.precision) != prec) return -1;
     return prec;
 }
 
@@ -238,7 +238,7 @@ static long long tiles_for(const tcol_ctx* c, int bm, int ntw, int mode) {
     const int BN = gemm_bn(ntw);
     for (int g = 0; g < c->G; ++g) {
         const auto& p = c->params[g];
-        const int tm = c->layouts[g].n_pad / bm;
+        const int tm = ceil_div(p.n, bm);
         int tn;
         if (mode == 1) {
             if (BN < p.k) return -1;
@@ -270,7 +270,7 @@ static double shape_cost(const tcol_ctx* c, int bm, int ntw) {
 
 // tile shapes: options first, else the listed shape of least estimated time
 static void pick_shapes(tcol_ctx* c) {
-    const int prec = std::max(0, common_precision(c));
+    const int prec = std::max(0, common_op(c));
     GemmShape s{prec, 128, 8, 0};
     double best = -1.0;
     for (auto& sh : kShapes) {
@@ -309,7 +309,7 @@ static void pick_shapes(tcol_ctx* c) {
         }
     }
     c->fshape = f;
-    c->fused_ok = f.ntw > 0 && common_precision(c) >= 0;
+    c->fused_ok = f.ntw > 0 && common_op(c) >= 0;
 }
 
 // Automatic penalty mode.  A balanced colouring gives each row about D n / k class-mates,
@@ -355,7 +355,7 @@ static int path_of(const tcol_ctx* c);
 static tcol_status build_batch(tcol_ctx* c, const std::vector<int>& order) {
     c->batch_ok = false;
     if (c->opt.fused != 3) return TCOL_OK;
-    const int prec = common_precision(c);
+    const int prec = common_op(c);
     const int kpl = batch_kpl(c->kmax);
     if (c->total_ps > 0 || c->any_momentum || c->any_mcol || prec < 0 || kpl == 0 || !update_rows_kpl(c->kmax))
         return TCOL_OK;
@@ -475,11 +475,11 @@ static tcol_status rebuild_schedule(tcol_ctx* c) {
         d.ex_begin = ex;
         d.ex_cblocks = expand_blocks(p.D, p.k, L.n_pad);
         ex += d.ex_cblocks;
-        d.gm_tm[0] = L.n_pad / c->shape.bm;
+        d.gm_tm[0] = ceil_div(p.n, c->shape.bm);
         d.gm_tn[0] = ceil_div(p.D * p.k, BN0);
         if (c->fused_ok) {
             d.gm_mpb = BN1 / p.k;
-            d.gm_tm[1] = L.n_pad / c->fshape.bm;
+            d.gm_tm[1] = ceil_div(p.n, c->fshape.bm);
             d.gm_tn[1] = ceil_div(p.D, d.gm_mpb);
         }
     }
@@ -575,26 +575,14 @@ static hipError_t enqueue_sparse_add(tcol_ctx* c, bool fitness, hipStream_t s) {
     return hipSuccess;
 }
 
-// whether some graph computes A.S in fp8: its expansion writes the bf16 copy of S only in
-// the iterations that take the dense pass, so it has to follow the penalty choice
-static bool any_split(const tcol_ctx* c) {
-    for (int g = 0; g < c->G; ++g)
-        if (prec_split(c->params[g].precision)) return true;
-    return false;
-}
-
 // one iteration on the fast path; c[pS] holds the colours of the current weights.  The
-// expansion reads only the colours, so unless it depends on the penalty choice its
-// blocks ride on the class-size launch
-// blocks ride on the class-size launch.  In a run of iterations the class-size launch
+// expansion reads only the colours, so its blocks ride on the class-size launch.  In a run of iterations the class-size launch
 // also ends the previous one (advance_prev), and only the last iteration launches its own
 // end (advance_own)
 static hipError_t enqueue_step_fast(tcol_ctx* c, bool advance_prev, bool advance_own, hipStream_t s) {
-    const bool merged = !any_split(c);
     HIPRET(launch_prep(c->ddesc, c->G, c->total_mem, c->prep_lds, 1, 0, c->total_ps > 0 ? 1 : 0,
-                       merged ? c->total_ex : 0, advance_prev ? 1 : 0, s));
+                       c->total_ex, advance_prev ? 1 : 0, s));
     HIPRET(enqueue_penalty(c, s));
-    if (!merged) HIPRET(launch_expand(c->ddesc, c->G, c->total_ex, 1, 0, 1, s));
     HIPRET(launch_gemm(c->shape, c->ddesc, c->G, c->total_gm[0], 1, 7 | 32 | 64, 0, s));
     HIPRET(enqueue_sparse_add(c, true, s));
     // the row update of the graphs whose update did not ride on the sparse rows
@@ -861,7 +849,7 @@ tcol_status tcol_init(tcol_ctx** out, int32_t G, const tcol_graph_params* p, con
         d.ncols = q.D * q.k;
         d.rows_S = L.rows_S;
         d.problem = q.problem;
-        d.precision = q.precision;
+        d.op = op_prec(q.precision);
         d.bonus_diag = q.bonus_diag ? 1 : 0;
         d.stop_on_legal = q.stop_on_legal ? 1 : 0;
         d.nb_iter = q.nb_iter;
@@ -885,8 +873,6 @@ tcol_status tcol_init(tcol_ctx** out, int32_t G, const tcol_graph_params* p, con
         d.Pop = b + L.off[B_POP];
         d.Sop[0] = b + L.off[B_S0];
         d.Sop[1] = b + L.off[B_S1];
-        d.Sp2[0] = prec_split(q.precision) ? (void*)(b + L.off[B_SP0]) : nullptr;
-        d.Sp2[1] = prec_split(q.precision) ? (void*)(b + L.off[B_SP1]) : nullptr;
         d.c[0] = (int16_t*)(b + L.off[B_C0]);
         d.c[1] = (int16_t*)(b + L.off[B_C1]);
         d.V[0] = (int32_t*)(b + L.off[B_V0]);
@@ -933,7 +919,7 @@ tcol_status tcol_init(tcol_ctx** out, int32_t G, const tcol_graph_params* p, con
                 rc = init_fail("demand upload");
         }
         if (rc == TCOL_OK &&
-            launch_pack_graph(A_dev[g], q.n, L.n_pad, q.precision, (uint8_t*)d.A8, d.Aop, dbad,
+            launch_pack_graph(A_dev[g], q.n, L.n_pad, op_prec(q.precision), (uint8_t*)d.A8, d.Aop, dbad,
                               (unsigned long long*)(dbad + 2) + g, c->stream) != hipSuccess)
             rc = init_fail("graph packing launch");
     }
@@ -1491,7 +1477,7 @@ extern "C" tcol_status tcol_conflicts_noalloc(const tcol_graph_params* p, const 
     d.ncols = p->D * p->k;
     d.rows_S = L.rows_S;
     d.problem = p->problem;
-    d.precision = kPrecFP4;
+    d.op = kPrecFP4;
     d.cmax = 1;   // one colour per vertex (multicolouring is rejected above)
     d.c1 = p->n / p->k;
     d.c2 = (p->n % p->k == 0) ? p->n / p->k : p->n / p->k + 1;
@@ -1511,7 +1497,7 @@ extern "C" tcol_status tcol_conflicts_noalloc(const tcol_graph_params* p, const 
     const int total_rows = p->D * p->n;
     d.ex_cblocks = expand_blocks(p->D, p->k, L.n_pad);
     const GemmShape sh{kPrecFP4, L.n_pad >= 2048 ? 128 : 64, L.n_pad >= 2048 ? 6 : 4, 0};
-    d.gm_tm[0] = L.n_pad / sh.bm;
+    d.gm_tm[0] = ceil_div(p->n, sh.bm);
     d.gm_tn[0] = ceil_div(d.ncols, gemm_bn(sh.ntw));
     GraphDev* gd = (GraphDev*)(base + L.desc);
 

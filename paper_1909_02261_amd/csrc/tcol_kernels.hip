@@ -24,11 +24,6 @@ __device__ inline uint16_t f32_to_bf16_rne(float x) {
 
 __device__ inline bool finite_f(float x) { return (__float_as_uint(x) & 0x7F800000u) != 0x7F800000u; }
 
-// 1.0 in each operand format
-__device__ inline uint32_t one_bits(int prec) {
-    return prec == kPrecFP32 ? 0x3F800000u : (prec == kPrecBF16 ? 0x3F80u : 0x38u);
-}
-
 __device__ inline int graph_of_row(const GraphDev* gd, int G, int w) {
     return find_graph(gd, G, w, [](const GraphDev& x) { return x.row_begin; });
 }
@@ -94,10 +89,6 @@ __global__ __launch_bounds__(256) void k_pack_graph(const uint8_t* __restrict__ 
         if (A8) A8[e] = a;
         if (prec == kPrecFP32)
             ((float*)Aop)[e] = a ? 1.0f : 0.0f;
-        else if (prec == kPrecBF16)
-            ((uint16_t*)Aop)[e] = a ? 0x3F80 : 0;
-        else if (prec == kPrecFP8)
-            ((uint8_t*)Aop)[e] = a ? 0x38 : 0;
         else if ((j & 1) == 0) {
             // the even column writes the byte of the pair (n_pad is even)
             const uint8_t a1 = (i < n && j + 1 < n) ? (A[(size_t)i * n + j + 1] ? 1 : 0) : 0;
@@ -978,17 +969,14 @@ k_pen_sparse(const GraphDev* __restrict__ gd, int G, int total_blocks, int honor
 
 
 // One-hot S^T [rows (d,l)][cols j] in the operand format; 16 columns per thread
-// (fp4: two columns per byte, the lower in the low nibble, 1.0 = 0x2).  For FP8
-// graphs the bf16 copy used by the penalty pass is written as well (the fp4 penalty
-// pass reads the fp4 operand itself).
+// (fp4: two columns per byte, the lower in the low nibble, 1.0 = 0x2; both contraction
+// passes read it).
 __device__ __forceinline__ void expand_block(const GraphDev* __restrict__ gd, int G, int b, int honor_stop, int next, int gate,
                              int adv) {
     const GraphDev& d = gd[find_graph(gd, G, b, [](const GraphDev& x) { return x.ex_begin; })];
     GraphState* st = d.st;
     if (honor_stop && (st->stopped || (adv && st->next_bad))) return;
     const int p = next ? st->pS ^ 1 : st->pS;
-    // the bf16 copy of S feeds only the dense penalty pass of FP8 graphs
-    const bool want_sp2 = prec_split(d.precision) && (!gate || !d.psparse || st->pdense);
     // a thread takes 16 columns of kExpandRows consecutive colour rows of one member: their
     // colours are loaded once for all of its rows
     const int cgs = d.n_pad / 16;
@@ -1038,7 +1026,7 @@ __device__ __forceinline__ void expand_block(const GraphDev* __restrict__ gd, in
         }
     }
     const size_t off = (size_t)row * d.n_pad + j0;
-    if (d.precision == kPrecFP32) {
+    if (d.op == kPrecFP32) {
         float4* o = (float4*)((float*)d.Sop[p] + off);
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
@@ -1050,39 +1038,11 @@ __device__ __forceinline__ void expand_block(const GraphDev* __restrict__ gd, in
             o[v] = x;
         }
     } else {
-        // bf16: the BF16 operand itself, or the FP8 graphs' copy for the penalty pass
-        const bool bf16_out = d.precision == kPrecBF16 || want_sp2;
-        uint16_t* sb = d.precision == kPrecBF16 ? (uint16_t*)d.Sop[p] : (uint16_t*)d.Sp2[p];
-        uint4* o = (uint4*)(sb + off);
+        uint32_t w[2] = {0u, 0u};
 #pragma unroll
-        for (int v = 0; v < 2; ++v) {
-            if (!bf16_out) break;
-            uint32_t w[4];
-#pragma unroll
-            for (int h = 0; h < 4; ++h) {
-                int q = 8 * v + 2 * h;
-                w[h] = (((mask >> q) & 1) ? 0x3F80u : 0u) | (((mask >> (q + 1)) & 1) ? 0x3F800000u : 0u);
-            }
-            o[v] = make_uint4(w[0], w[1], w[2], w[3]);
-        }
-        if (d.precision == kPrecFP8) {
-            uint32_t w[4];
-#pragma unroll
-            for (int h = 0; h < 4; ++h) {
-                uint32_t x = 0;
-#pragma unroll
-                for (int e = 0; e < 4; ++e)
-                    if ((mask >> (4 * h + e)) & 1) x |= 0x38u << (8 * e);
-                w[h] = x;
-            }
-            *(uint4*)((uint8_t*)d.Sop[p] + off) = make_uint4(w[0], w[1], w[2], w[3]);
-        } else if (d.precision == kPrecFP4) {
-            uint32_t w[2] = {0u, 0u};
-#pragma unroll
-            for (int q = 0; q < 16; ++q)
-                if ((mask >> q) & 1) w[q >> 3] |= 0x2u << (4 * (q & 7));
-            *(uint2*)((uint8_t*)d.Sop[p] + (off >> 1)) = make_uint2(w[0], w[1]);
-        }
+        for (int q = 0; q < 16; ++q)
+            if ((mask >> q) & 1) w[q >> 3] |= 0x2u << (4 * (q & 7));
+        *(uint2*)((uint8_t*)d.Sop[p] + (off >> 1)) = make_uint2(w[0], w[1]);
     }
     }
 }
@@ -1175,7 +1135,7 @@ __device__ __forceinline__ void mtilde_tile(const GraphDev& d, GraphState* st, i
     }
     const bool mirror = ti != tj;
     double ka = 0.0, vb = 0.0;
-    const bool fp32 = d.precision == kPrecFP32;
+    const bool fp32 = d.op == kPrecFP32;
     // fields used between the stores below stay in registers (no reload through gd)
     const int n = d.n;
     const size_t n_pad = d.n_pad;
@@ -1239,14 +1199,12 @@ __device__ __forceinline__ void mtilde_tile(const GraphDev& d, GraphState* st, i
                 }
             }
         } else {
-            // fp4 graphs: the penalty pass multiplies by 2 S (cheaper to widen from fp4), so
-            // their operand is stored halved, exactly
-            if (d.precision == kPrecFP4) {
+            // the penalty pass multiplies by 2 S (cheaper to widen from fp4), so the operand is
+            // stored halved, exactly
 #pragma unroll
-                for (int a = 0; a < PT; ++a)
+            for (int a = 0; a < PT; ++a)
 #pragma unroll
-                    for (int q = 0; q < PT; ++q) val[a][q] *= 0.5f;
-            }
+                for (int q = 0; q < PT; ++q) val[a][q] *= 0.5f;
 #pragma unroll
             for (int a = 0; a < PT; ++a) {
                 uint16_t* o = (uint16_t*)Pop + (size_t)(ib + a) * n_pad + jb;
