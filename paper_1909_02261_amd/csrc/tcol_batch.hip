@@ -55,13 +55,10 @@ __device__ __forceinline__ void batch_item(const GraphDev* __restrict__ gd, int 
             break;
         }
         case 1: {
-            int16_t(*ci)[64] = (int16_t(*)[64])batch_lds;
-            int16_t(*cj)[64] = (int16_t(*)[64])(batch_lds + sizeof(int16_t) * kMtChunk * 64);
-            double(*red)[256] = (double(*)[256])(batch_lds + 2 * sizeof(int16_t) * kMtChunk * 64);
             const int t0 = idx * kBatchMtilde, t1 = min(t0 + kBatchMtilde, d.mt_T * (d.mt_T + 1) / 2);
             for (int t = t0; t < t1; ++t) {
                 __syncthreads();
-                mtilde_block(gd, G, d.mt_begin + t, 1, kFlagGate, -1, nullptr, ci, cj, red);
+                mtilde_block(gd, G, d.mt_begin + t, 1, kFlagGate, -1, nullptr, batch_lds);
             }
             break;
         }
@@ -78,7 +75,7 @@ __device__ __forceinline__ void batch_item(const GraphDev* __restrict__ gd, int 
             const int end = d.row_begin + d.D * d.n;
             for (int u = 0; u < kBatchRowGroups; ++u) {
                 const int row = d.row_begin + (idx * kBatchRowGroups + u) * 16 + (threadIdx.x >> 4);
-                if (row < end) update_row<KPL, 1>(gd, G, row, 1, 0, -1, nullptr, nullptr);
+                if (row < end) update_row<KPL, 1>(gd, G, row, 1, 0, -1, nullptr, nullptr, 0);
             }
             break;
         }
@@ -176,8 +173,7 @@ int batch_kpl(int kmax) {
 size_t batch_lds_bytes(int prec, size_t prep_bytes) {
     GemmShape s{prec, kBatchBM, kBatchNTW, 0};
     size_t b = gemm_lds_bytes(s, 0);
-    const size_t mt = 2 * sizeof(int16_t) * kMtChunk * 64 + 2 * 256 * sizeof(double);
-    if (mt > b) b = mt;
+    if ((size_t)kMtLds > b) b = kMtLds;
     if (prep_bytes > b) b = prep_bytes;
     return b;
 }

@@ -41,7 +41,7 @@ constexpr int kMaxLdsBytes = 160 * 1024;
 inline size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 
 enum Buf {
-    B_LUT_PEN, B_LUT_BON, B_LUT_KA, B_LUT_VB, B_DEM, B_SEL, B_W2, B_A8, B_AOP, B_POP, B_S0, B_S1, B_C0, B_C1,
+    B_LUT_PEN, B_LUT_BON, B_LUT_KA, B_LUT_VB, B_DEM, B_SEL, B_W2, B_A8, B_AB, B_AOP, B_POP, B_S0, B_S1, B_C0, B_C1,
     B_V0, B_V1, B_G, B_F2, B_F2P, B_FCOL, B_FEQ, B_F, B_PART, B_SNAP, B_CT, B_CLSV, B_CLSOFF, B_CINFO, B_SQ, B_VEL, B_COUNT
 };
 
@@ -77,6 +77,7 @@ Layout make_layout(const tcol_graph_params& p) {
     sz[B_SEL] = cm > 1 ? sizeof(int16_t) * ((size_t)p.D * cm * round_up(p.n, 64) + 64) : 0;
     sz[B_W2] = sizeof(float) * dnk;
     sz[B_A8] = n2;
+    sz[B_AB] = n2 / 8;
     sz[B_AOP] = (size_t)L.n_pad * op_row_bytes(op_prec(p.precision), L.n_pad);
     sz[B_POP] = n2 * (p.precision == TCOL_FP32 ? 4 : 2);
     sz[B_S0] = sz[B_S1] = (size_t)L.rows_S * op_row_bytes(op_prec(p.precision), L.n_pad);
@@ -182,6 +183,9 @@ struct tcol_ctx {
     int cus = 0;
     size_t ps_lds = 0;              // dynamic LDS of the sparse penalty kernel
     size_t prep_lds = 0;            // dynamic LDS of the class-size kernel
+    bool rows = false;              // fp32 graphs take the class-row sums (fast path, loss, conflicts)
+    size_t p1_lds = 0, cr_lds = 0;  // dynamic LDS of the merged first launch and of the class-row sums
+    int total_cr = 0;               // blocks of the class-row sums
     int total_ps = 0;               // blocks of the sparse penalty kernel (0: no graph uses it)
     int total_rows = 0, total_mem = 0, total_mt = 0, total_ex = 0;
     int total_gm[2] = {0, 0};
@@ -457,7 +461,17 @@ static tcol_status rebuild_schedule(tcol_ctx* c) {
     for (int g = 0; g < c->G; ++g)
         if (!c->hdesc[g].pfuse) c->all_pfuse = false;
     c->prep_lds = prep_lds(c->kmax, c->nmax, ps_k > 0);
-    int rows = 0, mem = 0, pg = 0, mt = 0, ex = 0;
+    // class-row sums: fp32 operands, one colour per vertex, a row in registers, and a block's 64
+    // gradient rows with a member's list in LDS; beyond that the fp32 contraction
+    c->rows = common_op(c) == kPrecFP32 && !c->any_mcol && update_rows_kpl(c->kmax) > 0 &&
+              class_rows_lds(c->kmax, c->nmax) <= (size_t)kMaxBlockLds;
+    c->cr_lds = c->rows ? class_rows_lds(c->kmax, c->nmax) : 0;
+    if (c->rows) HIPCHK(class_rows_prepare(c->kmax, c->update_var));
+    bool stops = false;
+    for (auto& p : c->params) stops = stops || p.stop_on_legal;
+    c->p1_lds = phase1_lds(c->kmax, c->nmax, c->rows || (stops && update_rows_kpl(c->kmax) > 0));
+    HIPCHK(phase1_prepare());
+    int rows = 0, mem = 0, pg = 0, mt = 0, ex = 0, cr = 0;
     for (int g = 0; g < c->G; ++g) {
         const tcol_graph_params& p = c->params[g];
         const Layout& L = c->layouts[g];
@@ -466,6 +480,9 @@ static tcol_status rebuild_schedule(tcol_ctx* c) {
         rows += p.D * p.n;
         d.mem_begin = mem;
         mem += p.D;
+        d.rows = c->rows ? 1 : 0;
+        d.cr_begin = cr;
+        cr += p.D * ceil_div(p.n, 64);
         d.ps_begin = pg;
         if (d.psparse) pg += p.n;
         d.mt_begin = mt;
@@ -504,6 +521,7 @@ static tcol_status rebuild_schedule(tcol_ctx* c) {
     c->total_ps = pg;
     c->total_mt = mt;
     c->total_ex = ex;
+    c->total_cr = cr;
     c->total_gm[0] = gm0;
     c->total_gm[1] = gm1;
     tcol_status bs = build_batch(c, order);
@@ -525,23 +543,44 @@ static bool use_fused(const tcol_ctx* c) { return path_of(c) == 2; }
 
 static hipError_t launch_update_any(tcol_ctx* c, int honor, int mode, int gsel, float* gs, float* gw, hipStream_t s) {
     if (update_rows_kpl(c->kmax))
-        return launch_update_rows(c->ddesc, c->G, c->total_rows, c->kmax, c->update_var, honor, mode, gsel, gs, gw, s);
+        return launch_update_rows(c->ddesc, c->G, c->total_rows, c->kmax, c->update_var, honor, mode, gsel, gs, gw, 0, s);
     return launch_update(c->ddesc, c->G, c->total_rows, honor, mode, gsel, gs, gw, s);
 }
 
 // ---------------------------------------------------------------- sequences --
 
+// merged schedule of the fast path: no graph of the context takes the sparse rows, so an
+// iteration's penalty route does not depend on its class sizes
+static bool merged(const tcol_ctx* c) { return path_of(c) == 1 && c->total_ps == 0; }
+
+// everything that depends only on the colours, in one launch (S^T where a contraction follows)
+static hipError_t enqueue_phase1(tcol_ctx* c, int honor, int adv, int legal, int tiles, int flags, int gsel,
+                                 bool expand, hipStream_t s) {
+    return launch_phase1(c->ddesc, c->G, c->total_mem, tiles, expand ? c->total_ex : 0, c->p1_lds, honor, adv, legal,
+                         flags, gsel, s);
+}
+
 // one Algorithm-1 iteration for every running graph (plain path)
 static hipError_t enqueue_step_plain(tcol_ctx* c, hipStream_t s) {
     HIPRET(launch_colors(c->ddesc, c->G, c->total_rows, 1, s));
-    HIPRET(launch_prep(c->ddesc, c->G, c->total_mem, c->prep_lds, 1, 0, 0, 0, 0, s));
-    HIPRET(launch_expand(c->ddesc, c->G, c->total_ex, 1, 0, 0, s));
-    HIPRET(launch_mtilde(c->ddesc, c->G, c->total_mt, 1, 0, -1, nullptr, s));
+    HIPRET(enqueue_phase1(c, 1, 0, 0, c->total_mt, 0, -1, true, s));
     HIPRET(launch_gemm(c->shape, c->ddesc, c->G, c->total_gm[0], 1, 15, 0, s));
     HIPRET(launch_fitness(c->ddesc, c->G, 1, kFlagPlainPen, -1, s));
     HIPRET(launch_update_any(c, 1, 0, -1, nullptr, nullptr, s));
     HIPRET(launch_advance(c->ddesc, c->G, s));
     return hipSuccess;
+}
+
+// one iteration of the merged schedule: two launches with the class-row sums, else three.  The
+// first launch answers the stop rule, the last one ends the iteration; adv: the iteration follows
+// another of the same call
+static hipError_t enqueue_step_merged(tcol_ctx* c, bool adv, hipStream_t s) {
+    HIPRET(enqueue_phase1(c, 1, adv ? 1 : 0, 1, c->total_mt, 0, -1, !c->rows, s));
+    if (c->rows)
+        return launch_class_rows(c->ddesc, c->G, c->total_cr, c->cr_lds, c->kmax, c->update_var, 1, 0, -1, nullptr,
+                                 nullptr, s);
+    HIPRET(launch_gemm(c->shape, c->ddesc, c->G, c->total_gm[0], 1, 7 | 128, 0, s));
+    return launch_update_rows(c->ddesc, c->G, c->total_rows, c->kmax, c->update_var, 1, 0, -1, nullptr, nullptr, 1, s);
 }
 
 // penalty of the fast and epilogue paths: sparse penalty rows or the dense operand, per
@@ -587,7 +626,7 @@ static hipError_t enqueue_step_fast(tcol_ctx* c, bool advance_prev, bool advance
     HIPRET(enqueue_sparse_add(c, true, s));
     // the row update of the graphs whose update did not ride on the sparse rows
     if (!c->all_pfuse)
-        HIPRET(launch_update_rows(c->ddesc, c->G, c->total_rows, c->kmax, c->update_var, 1, 0, -1, nullptr, nullptr, s));
+        HIPRET(launch_update_rows(c->ddesc, c->G, c->total_rows, c->kmax, c->update_var, 1, 0, -1, nullptr, nullptr, 0, s));
     if (advance_own) HIPRET(launch_advance(c->ddesc, c->G, s));
     return hipSuccess;
 }
@@ -621,6 +660,10 @@ static hipError_t enqueue_batch(tcol_ctx* c, int n, hipStream_t s) {
 static hipError_t enqueue_steps(tcol_ctx* c, int n, hipStream_t s) {
     const int path = path_of(c);
     if (path == 3) return enqueue_batch(c, n, s);
+    if (merged(c)) {
+        for (int i = 0; i < n; ++i) HIPRET(enqueue_step_merged(c, i > 0, s));
+        return hipSuccess;
+    }
     for (int i = 0; i < n; ++i)
         HIPRET(path == 2 ? enqueue_step_fused(c, s)
                          : (path == 1 ? enqueue_step_fast(c, i > 0, i == n - 1, s) : enqueue_step_plain(c, s)));
@@ -869,6 +912,7 @@ tcol_status tcol_init(tcol_ctx** out, int32_t G, const tcol_graph_params* p, con
         d.W[0] = W_dev[g];
         d.W[1] = (float*)(b + L.off[B_W2]);
         d.A8 = b + L.off[B_A8];
+        d.Ab = (const unsigned long long*)(b + L.off[B_AB]);
         d.Aop = b + L.off[B_AOP];
         d.Pop = b + L.off[B_POP];
         d.Sop[0] = b + L.off[B_S0];
@@ -919,7 +963,8 @@ tcol_status tcol_init(tcol_ctx** out, int32_t G, const tcol_graph_params* p, con
                 rc = init_fail("demand upload");
         }
         if (rc == TCOL_OK &&
-            launch_pack_graph(A_dev[g], q.n, L.n_pad, op_prec(q.precision), (uint8_t*)d.A8, d.Aop, dbad,
+            launch_pack_graph(A_dev[g], q.n, L.n_pad, op_prec(q.precision), (uint8_t*)d.A8,
+                              const_cast<unsigned long long*>(d.Ab), d.Aop, dbad,
                               (unsigned long long*)(dbad + 2) + g, c->stream) != hipSuccess)
             rc = init_fail("graph packing launch");
     }
@@ -941,6 +986,7 @@ tcol_status tcol_init(tcol_ctx** out, int32_t G, const tcol_graph_params* p, con
         for (auto& x : st) {
             memset(&x, 0, sizeof(x));
             x.legal_d = -1;
+            x.legal_min[0] = x.legal_min[1] = 0x7FFFFFFF;
         }
         if (hipMemcpy(c->dstate, st.data(), sizeof(GraphState) * G, hipMemcpyHostToDevice) != hipSuccess)
             rc = init_fail("state upload");
@@ -997,7 +1043,9 @@ tcol_status tcol_step(tcol_ctx* c, int32_t max_steps, int32_t* steps_done, int32
         const GraphState& st = c->hstate[g];
         done = std::max(done, st.steps_done);
         if (legal_d) legal_d[g] = st.legal_d;
+        // (the merged schedule leaves a non-finite update of its last iteration to the host)
         if (st.error) rc = st.error;
+        else if (st.next_bad && !st.stopped) rc = TCOL_ENONFINITE;
         if (colors_out_dev && colors_out_dev[g] && st.legal_d >= 0)
             HIPCHK(hipMemcpyAsync(colors_out_dev[g], c->hdesc[g].snap,
                                   sizeof(int16_t) * c->params[g].n * c->hdesc[g].cmax, hipMemcpyDeviceToDevice,
@@ -1011,9 +1059,12 @@ tcol_status tcol_conflicts(tcol_ctx* c, int32_t g, int16_t* colors_dev, int64_t*
     if (!c || g < 0 || g >= c->G) return TCOL_EINVAL;
     // steps 1-2 for all graphs of the context (cheap), reporting only
     HIPCHK(launch_colors(c->ddesc, c->G, c->total_rows, 0, c->stream));
-    HIPCHK(launch_prep(c->ddesc, c->G, c->total_mem, c->prep_lds, 0, 0, 0, 0, 0, c->stream));
-    HIPCHK(launch_expand(c->ddesc, c->G, c->total_ex, 0, 0, 0, c->stream));
-    HIPCHK(launch_gemm(c->shape, c->ddesc, c->G, c->total_gm[0], 0, 1, 0, c->stream));
+    HIPCHK(enqueue_phase1(c, 0, 0, 0, 0, 0, -1, !c->rows, c->stream));
+    if (c->rows)
+        HIPCHK(launch_class_rows(c->ddesc, c->G, c->total_cr, c->cr_lds, c->kmax, c->update_var, 0, 2, g, nullptr,
+                                 nullptr, c->stream));
+    else
+        HIPCHK(launch_gemm(c->shape, c->ddesc, c->G, c->total_gm[0], 0, 1, 0, c->stream));
     HIPCHK(launch_fitness(c->ddesc, c->G, 0, kFlagReport, -1, c->stream));
     HIPCHK(launch_copy_report(c->ddesc, g, colors_dev, f_color_dev, f_eq_dev, c->stream));
     return TCOL_OK;
@@ -1022,13 +1073,14 @@ tcol_status tcol_conflicts(tcol_ctx* c, int32_t g, int16_t* colors_dev, int64_t*
 tcol_status tcol_loss_grad(tcol_ctx* c, int32_t g, double* loss_dev, float* gradS_dev, float* gradW_dev) {
     if (!c || g < 0 || g >= c->G) return TCOL_EINVAL;
     HIPCHK(launch_colors(c->ddesc, c->G, c->total_rows, 0, c->stream));
-    HIPCHK(launch_prep(c->ddesc, c->G, c->total_mem, c->prep_lds, 0, 0, 0, 0, 0, c->stream));
-    HIPCHK(launch_expand(c->ddesc, c->G, c->total_ex, 0, 0, 0, c->stream));
-    HIPCHK(launch_mtilde(c->ddesc, c->G, c->total_mt, 0, kFlagLoss | kFlagForcePen, g, nullptr, c->stream));
-    HIPCHK(launch_gemm(c->shape, c->ddesc, c->G, c->total_gm[0], 0, 15, 0, c->stream));
-    HIPCHK(launch_fitness(c->ddesc, c->G, 0, kFlagReport, -1, c->stream));
-    if (loss_dev) HIPCHK(launch_loss(c->ddesc, g, c->layouts[g].mt_tiles, loss_dev, c->stream));
-    if (gradS_dev || gradW_dev) HIPCHK(launch_update_any(c, 0, 1, g, gradS_dev, gradW_dev, c->stream));
+    HIPCHK(enqueue_phase1(c, 0, 0, 0, c->total_mt, kFlagLoss | kFlagForcePen, g, !c->rows, c->stream));
+    if (c->rows)
+        HIPCHK(launch_class_rows(c->ddesc, c->G, c->total_cr, c->cr_lds, c->kmax, c->update_var, 0,
+                                 gradS_dev || gradW_dev ? 1 : 2, g, gradS_dev, gradW_dev, c->stream));
+    else
+        HIPCHK(launch_gemm(c->shape, c->ddesc, c->G, c->total_gm[0], 0, 15, 0, c->stream));
+    HIPCHK(launch_loss(c->ddesc, c->G, g, c->layouts[g].mt_tiles, loss_dev, c->stream));
+    if (!c->rows && (gradS_dev || gradW_dev)) HIPCHK(launch_update_any(c, 0, 1, g, gradS_dev, gradW_dev, c->stream));
     return TCOL_OK;
 }
 
@@ -1506,7 +1558,7 @@ extern "C" tcol_status tcol_conflicts_noalloc(const tcol_graph_params* p, const 
     HIPCHK(launch_zero(base + L.state, L.total - L.state, s));
     HIPCHK(launch_put_desc(d, gd, d.st, s));
     // A is packed without its check (its flag word is ignored): the caller vouches for it
-    HIPCHK(launch_pack_graph(A_dev, p->n, L.n_pad, kPrecFP4, nullptr, d.Aop, (int*)(base + L.ones),
+    HIPCHK(launch_pack_graph(A_dev, p->n, L.n_pad, kPrecFP4, nullptr, nullptr, d.Aop, (int*)(base + L.ones),
                              (unsigned long long*)(base + L.ones + 8), s));
     HIPCHK(launch_colors(gd, 1, total_rows, 0, s));
     HIPCHK(launch_prep(gd, 1, p->D, prep_lds(p->k, p->n, 0), 0, 0, 0, 0, 0, s));

@@ -65,6 +65,9 @@ struct GraphState {
     int pS;             // fused path: which colour / S buffer set is current
     int next_bad;       // fused path: the update produced a non-finite weight
     int pdense;         // sparse penalty graphs: this iteration takes the dense operand pass
+    long long tc;       // merged schedule: t of the iteration in progress (set by its first launch, so that
+                        // the last one may advance t while its other blocks still read this one)
+    int legal_min[2];   // merged schedule: lowest legal member found by the iteration with t mod 2
     int prep_ticket;    // member blocks of the class-size kernel done this iteration (the
                         // last one takes the penalty choice and sets it back to 0)
     // iterations evaluated since init, by the route of their penalty product: none (lambda t =
@@ -95,6 +98,7 @@ struct GraphDev {
     // buffers
     float* W[2];              // [0] caller's weights, [1] fused-path ping-pong buffer
     const uint8_t* A8;        // [n_pad][n_pad] 0/1 bytes (zero padded)
+    const unsigned long long* Ab;   // [n_pad / 64][n_pad] bit b of word (s, j): A[j][64 s + b]
     void* Aop;                // [n_pad][n_pad] A in the operand format
     void* Pop;                // [n_pad][n_pad] penalty operand (fp32, or bf16, halved, with fp4 A and S)
     void* Sop[2];             // [rows_S][n_pad] S^T in the operand format
@@ -136,6 +140,8 @@ struct GraphDev {
     int row_begin;            // rows (d, i) for row kernels
     int mem_begin;            // members d for per-member kernels
     int ps_begin;             // blocks (rows) of the sparse penalty kernel
+    int rows;                 // the class-row sums (k_class_rows) replace the fp32 contraction
+    int cr_begin;             // blocks of the class-row kernel
     int mt_begin;             // tiles of the group-concentration kernel
     int mt_T;                 // tiles per side
     int mt_ts;                // tile side of the group-concentration kernel (32 or 64)

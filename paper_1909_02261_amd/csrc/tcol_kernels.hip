@@ -67,37 +67,61 @@ __device__ inline u32x4n gload16(const void* p) { return *(const __attribute__((
 
 // ------------------------------------------------------ validation, packing --
 
-// Checks A (n x n, row-major 0/1, symmetric, zero diagonal) and writes the
-// zero-padded byte copy A8 (unless A8 is null) and the operand copy Aop ([n_pad][n_pad];
-// in fp4 two entries per byte, the lower column in the low nibble, 1.0 = 0x2).
-__global__ __launch_bounds__(256) void k_pack_graph(const uint8_t* __restrict__ A, int n, int n_pad, int prec,
-                                                    uint8_t* __restrict__ A8, void* __restrict__ Aop,
-                                                    int* __restrict__ bad, unsigned long long* __restrict__ ones) {
+// Checks A (n x n, row-major 0/1, symmetric, zero diagonal; unless A8 is null) and writes the
+// zero-padded byte copy A8, the bit copy Ab (each unless null) and the operand copy Aop
+// ([n_pad][n_pad]; in fp4 two entries per byte, the lower column in the low nibble, 1.0 = 0x2).
+// One block per 64 x 64 tile: a wave reads 64 bytes of a row at a time (A's rows have any
+// alignment) and turns them into one ballot, from which every copy is written; the mirrored tile's
+// ballots go to LDS for the symmetry check.
+__global__ __launch_bounds__(256) void k_pack_graph(const uint8_t* __restrict__ A, int n, int n_pad, int op,
+                                                    uint8_t* __restrict__ A8, unsigned long long* __restrict__ Ab,
+                                                    void* __restrict__ Aop, int* __restrict__ bad,
+                                                    unsigned long long* __restrict__ ones) {
+    __shared__ unsigned long long mir[64];
     __shared__ unsigned int wcount[4];
-    const long long total = (long long)n_pad * n_pad;
-    unsigned int count = 0;   // ones of A seen by this thread (2 |E| over all threads of a valid graph)
-    for (long long e = (long long)blockIdx.x * blockDim.x + threadIdx.x; e < total; e += (long long)gridDim.x * blockDim.x) {
-        const int i = (int)(e / n_pad), j = (int)(e - (long long)i * n_pad);
-        uint8_t a = 0;
-        if (i < n && j < n) {
-            a = A[(size_t)i * n + j];
-            uint8_t b = A[(size_t)j * n + i];
-            if (a > 1 || a != b || (i == j && a != 0)) atomicOr(bad, 1);
-            a = a ? 1 : 0;
-        }
-        count += a;
-        if (A8) A8[e] = a;
-        if (prec == kPrecFP32)
-            ((float*)Aop)[e] = a ? 1.0f : 0.0f;
-        else if ((j & 1) == 0) {
-            // the even column writes the byte of the pair (n_pad is even)
-            const uint8_t a1 = (i < n && j + 1 < n) ? (A[(size_t)i * n + j + 1] ? 1 : 0) : 0;
-            ((uint8_t*)Aop)[e >> 1] = (uint8_t)((a ? 0x2 : 0) | (a1 ? 0x20 : 0));
+    const int T = n_pad / 64;
+    const int ti = blockIdx.x / T, tj = blockIdx.x - ti * T;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int i0 = ti * 64, j0 = tj * 64;
+    const bool check = A8 != nullptr;
+    uint8_t own[16], oth[16];
+#pragma unroll
+    for (int u = 0; u < 16; ++u) {
+        const int r = wave * 16 + u;
+        own[u] = i0 + r < n && j0 + lane < n ? A[(size_t)(i0 + r) * n + j0 + lane] : (uint8_t)0;
+        oth[u] = check && j0 + r < n && i0 + lane < n ? A[(size_t)(j0 + r) * n + i0 + lane] : (uint8_t)0;
+    }
+    if (check) {
+#pragma unroll
+        for (int u = 0; u < 16; ++u) {
+            const unsigned long long m = __ballot(oth[u] != 0);
+            if (lane == 0) mir[wave * 16 + u] = m;
         }
     }
+    __syncthreads();
+    const unsigned long long mcol = check ? mir[lane] : 0ull;   // bit r: A[j0 + lane][i0 + r]
+    unsigned int count = 0;   // ones of A seen by this wave (2 |E| over all waves of a valid graph)
+    bool wrong = false;
+#pragma unroll
+    for (int u = 0; u < 16; ++u) {
+        const int r = wave * 16 + u, i = i0 + r;
+        const bool a = own[u] != 0;
+        const unsigned long long m = __ballot(a);
+        count += (unsigned)__popcll(m);
+        if (check) wrong |= own[u] > 1 || a != (bool)((mcol >> r) & 1ull) || (a && i == j0 + lane);
+        const size_t e = (size_t)i * n_pad + j0 + lane;
+        if (A8) A8[e] = a ? 1 : 0;
+        if (Ab && lane == 0) Ab[(size_t)tj * n_pad + i] = m;
+        if (op == kPrecFP32) {
+            ((float*)Aop)[e] = a ? 1.0f : 0.0f;
+        } else if (lane < 32) {
+            const unsigned int two = (unsigned int)(m >> (2 * lane)) & 3u;
+            ((uint8_t*)Aop)[((size_t)i * n_pad + j0) / 2 + lane] = (uint8_t)(((two & 1u) << 1) | ((two & 2u) << 4));
+        }
+    }
+    if (check && __any(wrong) && lane == 0) atomicOr(bad, 1);
     // one atomic per block
-    for (int sh = 32; sh >= 1; sh >>= 1) count += __shfl_xor(count, sh);
-    if ((threadIdx.x & 63) == 0) wcount[threadIdx.x >> 6] = count;
+    if (lane == 0) wcount[wave] = count;
     __syncthreads();
     if (threadIdx.x == 0) {
         const unsigned long long c = (unsigned long long)wcount[0] + wcount[1] + wcount[2] + wcount[3];
@@ -1062,12 +1086,27 @@ __global__ __launch_bounds__(256) void k_expand(const GraphDev* __restrict__ gd,
 //   P_ij = t * (a_ij ? 2 alpha lambda m^(alpha-1) : -[i != j or bonus_diag] 2 beta mu m^(beta-1)).
 // Optional: Mt to mt_out (int32 [n][n]) and kappa / varpi partial sums.  Each of the
 // 256 threads owns a PT x PT block of the tile (PT = TS / 16).
-constexpr int kMtChunk = 128;   // members per LDS chunk
+//
+// The compares are the work (n^2 D / 2 of them, VALU), so colours are compared packed: the tile's
+// vertices get their colours in LDS vertex-major, four members to a word (BYTES: colours below
+// 126) or two, and for a pair of words (x ^ y) + 0x7f7f7f7f (0x7fff7fff) sets the top bit of
+// every field that differs, which a masked population count adds to the pair's count: three
+// instructions per four (two) members.  Members past D and unselected slots hold 0x7f on the i side and
+// 0x7e on the j side (0x7fff, 0x7ffe), which differ from each other and from every colour.  16-byte
+// pieces of a row are swizzled so that the lanes of a read fall on different banks.
+// G(1000, .5), k = 90, D = 256: 20.8 us with the member and expansion blocks in the same launch,
+// against 30.9 us (16-bit compares, one pair at a time) and 14.6 us for two launches.
+constexpr int kMtWords = 32;    // words per vertex and LDS chunk (over the slots of a multicolouring)
+constexpr int kMtLds = 2 * 64 * kMtWords * 4 + 2 * 256 * 8;   // both sides of a tile, the loss reduction
 
-template <int PT>
+template <int PT, int BYTES>
 __device__ __forceinline__ void mtilde_tile(const GraphDev& d, GraphState* st, int b, int flags, int32_t* __restrict__ mt_out,
-                            int16_t (*ci)[64], int16_t (*cj)[64], double (*red)[256]) {
+                            uint8_t* lds) {
     constexpr int TS = 16 * PT;
+    constexpr int PW = BYTES ? 4 : 2;   // members per word
+    constexpr uint32_t kLow = BYTES ? 0x7f7f7f7fu : 0x7fff7fffu;
+    uint32_t* sw = (uint32_t*)lds;      // [2][TS][kMtWords]
+    double(*red)[256] = (double(*)[256])(lds + 2 * 64 * kMtWords * 4);
     const float tf = (float)st->t;
     const bool pen = (d.lambda * tf != 0.0f) || (d.mu * tf != 0.0f);
     const int p = st->pS;
@@ -1082,57 +1121,71 @@ __device__ __forceinline__ void mtilde_tile(const GraphDev& d, GraphState* st, i
     for (int a = 0; a < PT; ++a)
 #pragma unroll
         for (int q = 0; q < PT; ++q) cnt[a][q] = 0;
-    // rows of colours: members (one colour per vertex), or for multicolouring (member, slot)
-    // pairs of the selection, whose slots of a member must meet in one chunk
+    // planes of colours: the members' (one colour per vertex), or for multicolouring the slots of
+    // the selection, every slot against every slot of the same member
     const int CM = d.cmax;
-    const int16_t* base = CM > 1 ? d.sel : d.c[p];
-    const int vrows = d.D * CM;
-    const int chunk = (kMtChunk / CM) * CM;
-    for (int dbase = 0; dbase < vrows; dbase += chunk) {
-        const int dn = min(chunk, vrows - dbase);
+    const int16_t* __restrict__ base = CM > 1 ? d.sel : d.c[p];
+    const int cs = d.cs, D = d.D, nv = d.n;
+    const int W = (D + PW - 1) / PW;
+    const int wp = CM == 1 ? kMtWords : (kMtWords / CM) & ~3;   // words per plane and chunk
+    int total = 0;      // compares per pair
+    for (int w0 = 0; w0 < W; w0 += wp) {
+        const int wn = (min(wp, W - w0) + 3) & ~3;
+        total += wn * PW * CM * CM;
         __syncthreads();
-        for (int e = threadIdx.x; e < dn * TS; e += 256) {
-            const int dm = e / TS, x = e - dm * TS;
-            const int16_t* cr = base + (size_t)(dbase + dm) * d.cs;
-            // out-of-range vertices and unselected slots get distinct sentinels so they never match
-            const int16_t a = (i0 + x < d.n) ? cr[i0 + x] : (int16_t)-1;
-            const int16_t b = (j0 + x < d.n) ? cr[j0 + x] : (int16_t)-2;
-            ci[dm][x] = a < 0 ? (int16_t)-1 : a;
-            cj[dm][x] = b < 0 ? (int16_t)-2 : b;
-        }
-        __syncthreads();
-        if (CM == 1) {
-            for (int dm = 0; dm < dn; ++dm) {
-                int16_t av[PT], bv[PT];
+        const int per = CM * wn;        // words per vertex
+        for (int e = threadIdx.x; e < 2 * per * TS; e += 256) {
+            const int x = e & (TS - 1);
+            int r = e / TS;
+            const int side = r >= per ? 1 : 0;
+            r -= side * per;
+            const int pl = CM == 1 ? 0 : r / wn, w = r - pl * wn;
+            const int v = (side ? j0 : i0) + x;
+            int16_t cv[PW];
 #pragma unroll
-                for (int a = 0; a < PT; ++a) {
-                    av[a] = ci[dm][ty * PT + a];
-                    bv[a] = cj[dm][tx * PT + a];
-                }
-#pragma unroll
-                for (int a = 0; a < PT; ++a)
-#pragma unroll
-                    for (int q = 0; q < PT; ++q) cnt[a][q] += (av[a] == bv[q]) ? 1 : 0;
+            for (int h = 0; h < PW; ++h) {
+                const int dm = (w0 + w) * PW + h;
+                cv[h] = v < nv && dm < D ? gview(base)[(size_t)(dm * CM + pl) * cs + v] : (int16_t)-1;
             }
-        } else {
-            // the colours i and j share within each member: every slot against every slot
-            for (int mm = 0; mm < dn; mm += CM)
-                for (int s1 = 0; s1 < CM; ++s1) {
-                    int16_t av[PT];
+            uint32_t word = 0;
 #pragma unroll
-                    for (int a = 0; a < PT; ++a) av[a] = ci[mm + s1][ty * PT + a];
-                    for (int s2 = 0; s2 < CM; ++s2) {
-                        int16_t bv[PT];
-#pragma unroll
-                        for (int q = 0; q < PT; ++q) bv[q] = cj[mm + s2][tx * PT + q];
-#pragma unroll
-                        for (int a = 0; a < PT; ++a)
-#pragma unroll
-                            for (int q = 0; q < PT; ++q) cnt[a][q] += (av[a] == bv[q]) ? 1 : 0;
-                    }
-                }
+            for (int h = 0; h < PW; ++h) {
+                const uint32_t f = cv[h] < 0 ? (BYTES ? 0x7fu : 0x7fffu) - (uint32_t)side : (uint32_t)cv[h];
+                word |= f << (h * (32 / PW));
+            }
+            const int slot = (pl * wn + w) >> 2;
+            sw[(side * TS + x) * kMtWords + (((slot ^ (x / PT)) & 7) << 2) + (w & 3)] = word;
         }
+        __syncthreads();
+        auto piece = [&](int side, int r, int slot) {
+            return *(const uint4*)(sw + (side * TS + r) * kMtWords + (((slot ^ (r / PT)) & 7) << 2));
+        };
+        const int np = wn >> 2;
+        for (int s1 = 0; s1 < CM; ++s1)
+            for (int s2 = 0; s2 < CM; ++s2)
+                for (int c4 = 0; c4 < np; ++c4) {
+                    uint4 av[PT], bv[PT];
+#pragma unroll
+                    for (int a = 0; a < PT; ++a) {
+                        av[a] = piece(0, ty * PT + a, s1 * np + c4);
+                        bv[a] = piece(1, tx * PT + a, s2 * np + c4);
+                    }
+#pragma unroll
+                    for (int a = 0; a < PT; ++a)
+#pragma unroll
+                        for (int q = 0; q < PT; ++q) {
+                            cnt[a][q] += __builtin_popcount(((av[a].x ^ bv[q].x) + kLow) & ~kLow);
+                            cnt[a][q] += __builtin_popcount(((av[a].y ^ bv[q].y) + kLow) & ~kLow);
+                            cnt[a][q] += __builtin_popcount(((av[a].z ^ bv[q].z) + kLow) & ~kLow);
+                            cnt[a][q] += __builtin_popcount(((av[a].w ^ bv[q].w) + kLow) & ~kLow);
+                        }
+                }
     }
+    // the fields that agree
+#pragma unroll
+    for (int a = 0; a < PT; ++a)
+#pragma unroll
+        for (int q = 0; q < PT; ++q) cnt[a][q] = total - cnt[a][q];
     const bool mirror = ti != tj;
     double ka = 0.0, vb = 0.0;
     const bool fp32 = d.op == kPrecFP32;
@@ -1249,31 +1302,301 @@ __device__ __forceinline__ void mtilde_tile(const GraphDev& d, GraphState* st, i
     }
 }
 
-// tile b (flattened over the graphs) of the group-concentration kernel; ci, cj, red: its LDS
+// tile b (flattened over the graphs) of the group-concentration kernel (lds: kMtLds bytes); adv:
+// the launch also ends the previous iteration (a pending non-finite update counts as a stop)
 __device__ __forceinline__ void mtilde_block(const GraphDev* __restrict__ gd, int G, int b, int honor_stop, int flags, int gsel,
-                             int32_t* __restrict__ mt_out, int16_t (*ci)[64], int16_t (*cj)[64], double (*red)[256]) {
+                             int32_t* __restrict__ mt_out, uint8_t* lds, int adv = 0) {
     const int g = find_graph(gd, G, b, [](const GraphDev& x) { return x.mt_begin; });
     const GraphDev& d = gd[g];
     GraphState* st = d.st;
-    if (honor_stop && st->stopped) return;
+    if (honor_stop && (st->stopped || (adv && st->next_bad))) return;
     if (gsel >= 0 && g != gsel) return;
     const float tf = (float)st->t;
     const bool pen = (d.lambda * tf != 0.0f) || (d.mu * tf != 0.0f);
     if (!pen && !(flags & (kFlagForcePen | kFlagLoss | kFlagMtOut))) return;
     if ((flags & kFlagGate) && d.psparse && !st->pdense) return;
-    if (d.mt_ts == 32)
-        mtilde_tile<2>(d, st, b, flags, mt_out, ci, cj, red);
-    else
-        mtilde_tile<4>(d, st, b, flags, mt_out, ci, cj, red);
+    if (d.mt_ts == 32) {
+        if (d.k <= 126) mtilde_tile<2, 1>(d, st, b, flags, mt_out, lds);
+        else mtilde_tile<2, 0>(d, st, b, flags, mt_out, lds);
+    } else {
+        if (d.k <= 126) mtilde_tile<4, 1>(d, st, b, flags, mt_out, lds);
+        else mtilde_tile<4, 0>(d, st, b, flags, mt_out, lds);
+    }
 }
 __global__ __launch_bounds__(256) void k_mtilde(const GraphDev* __restrict__ gd, int G, int total_tiles,
                                                 int honor_stop, int flags, int gsel, int32_t* __restrict__ mt_out) {
-    __shared__ int16_t ci[kMtChunk][64];
-    __shared__ int16_t cj[kMtChunk][64];
-    __shared__ double red[2][256];
+    __shared__ __attribute__((aligned(16))) uint8_t lds[kMtLds];
     const int b = blockIdx.x;
     if (b >= total_tiles) return;
-    mtilde_block(gd, G, b, honor_stop, flags, gsel, mt_out, ci, cj, red);
+    mtilde_block(gd, G, b, honor_stop, flags, gsel, mt_out, lds);
+}
+
+// ------------------------------------------------ merged first launch -----------
+
+// Position q of the order in which the fp32 contraction sums the vertices of a class (components
+// of 16-byte chunks, then chunks, within each 16 vertices) -> vertex.  The class-row sums follow it,
+// so they give the contraction's bits.
+__device__ __forceinline__ int vertex_at(int q) { return (q & ~15) | ((q & 3) << 2) | ((q >> 2) & 3); }
+
+// words of the member block's dynamic LDS: scratch, counts, per-wave cursors, per-wave 64-bit batch
+// masks, class starts, then the list
+__host__ __device__ inline size_t member_lds_bytes(int k, int n) {
+    return sizeof(int) * ((size_t)kPrepScratch + 14 * (size_t)k + 2) + sizeof(int16_t) * (size_t)((n + 1) & ~1);
+}
+
+// Member `mem` of the merged first launch (one colour per vertex): class sizes and the added
+// fitness where the problem has one, the class lists in summation order for graphs on the class-row
+// sums, and, with `legal`, whether the member is legal (f = 0), so that the launch that updates the
+// weights knows the stop rule's answer before it starts and no fitness launch stands between.  A
+// member is illegal as soon as one conflicting pair (partitioning: one cut edge) is found, which in
+// all but the last iterations is at once; a full scan of small classes is sum_l #V_l^2 / 2 pairs.
+__device__ __forceinline__ void member_block(const GraphDev* __restrict__ gd, int G, int mem, int honor_stop, int adv,
+                                             int legal, int* sh) {
+    const GraphDev& d = gd[find_graph(gd, G, mem, [](const GraphDev& x) { return x.mem_begin; })];
+    GraphState* st = d.st;
+    // read before this launch writes the state; the write below only turns `stopped` on, exactly when
+    // next_bad is set, so every block of the launch takes the same decision (see prep_member)
+    const bool stop_now = honor_stop && (st->stopped || (adv && st->next_bad));
+    const int tid = threadIdx.x;
+    if (mem == d.mem_begin && tid == 0) {
+        if (adv && !st->stopped && st->next_bad) {
+            st->error = -5;
+            st->stopped = 1;
+        }
+        st->tc = st->t;
+    }
+    if (stop_now || d.cmax > 1) return;
+    const int m = mem - d.mem_begin;
+    const int k = d.k, n = d.n;
+    const bool part = prob_partition(d.problem), added = prob_added(d.problem);
+    // minimum sum colouring always has a colour cost, so no member is legal
+    const bool want_legal = legal && d.stop_on_legal && d.problem != kProbMSCP;
+    const bool lists = d.rows || (want_legal && !part);
+    if (!lists && !want_legal && !added) return;
+    const int16_t* __restrict__ c = d.c[st->pS] + (size_t)m * d.cs;
+    int* part_sum = sh;                                       // [257]
+    long long* fsum = (long long*)(sh + 260);                 // [4]
+    volatile int* found = sh + 276;
+    volatile int* feq_zero = sh + 277;
+    int* cnt = sh + kPrepScratch;                             // [k]
+    int* cw = cnt + k;                                        // [4][k]
+    unsigned long long* msk = (unsigned long long*)(cw + 4 * k + (k & 1));   // [4][k] (8-byte aligned)
+    int* offl = (int*)(msk + 4 * (size_t)k);                  // [k]
+    int16_t* lst = (int16_t*)(offl + k + (k & 1));            // [n]
+    constexpr int NW = 4;
+    const int wv = tid >> 6, lane = tid & 63;
+    const int Q = ((n + NW - 1) / NW + 63) & ~63;             // positions per wave
+    for (int l = tid; l < k; l += 256) cnt[l] = 0;
+    if (lists)
+        for (int l = tid; l < NW * k; l += 256) {
+            cw[l] = 0;
+            msk[l] = 0ull;
+        }
+    if (tid == 0) { *found = 0; *feq_zero = 1; }
+    __syncthreads();
+    const int np16 = (n + 15) & ~15;                          // positions (those of vertices >= n are skipped)
+    const int e0 = wv * Q, e1 = min(np16, (wv + 1) * Q);
+    for (int i0 = e0 + lane; i0 < e1; i0 += 64 * kPrepBatch) {
+        int xs[kPrepBatch];
+#pragma unroll
+        for (int u = 0; u < kPrepBatch; ++u) {
+            const int q = i0 + 64 * u, v = vertex_at(q);
+            xs[u] = q < e1 && v < n ? (int)gview(c)[v] : -1;
+        }
+#pragma unroll
+        for (int u = 0; u < kPrepBatch; ++u)
+            if (xs[u] >= 0) {
+                atomicAdd(&cnt[xs[u]], 1);
+                if (lists) atomicAdd(&cw[wv * k + xs[u]], 1);
+            }
+    }
+    __syncthreads();
+    if (added) {
+        int32_t* V = d.V[st->pS] + (size_t)m * k;
+        const int c1 = d.c1, c2 = d.c2;
+        long long fe = 0;
+        for (int l = tid; l < k; l += 256) {
+            const long long v = cnt[l];
+            V[l] = cnt[l];
+            if (d.problem == kProbMSCP) {
+                fe += (long long)(l + 1) * v;
+            } else {
+                const long long x = v > c1 ? v - c1 : c1 - v;
+                const long long y = v > c2 ? v - c2 : c2 - v;
+                fe += x < y ? x : y;
+            }
+        }
+        for (int o = 32; o >= 1; o >>= 1) fe += __shfl_xor(fe, o);
+        if (lane == 0) fsum[wv] = fe;
+        __syncthreads();
+        if (tid == 0) {
+            const long long f = fsum[0] + fsum[1] + fsum[2] + fsum[3];
+            d.feq[m] = f;
+            *feq_zero = f == 0;
+        }
+    }
+    if (lists) {
+        // exclusive scan of the counts (as in prep_member)
+        const int per = (k + 255) / 256;
+        const int lb = min(k, tid * per), le = min(k, lb + per);
+        int run = 0;
+        for (int l = lb; l < le; ++l) run += cnt[l];
+        part_sum[tid] = run;
+        __syncthreads();
+        if (tid < 64) {
+            const int v0 = part_sum[4 * tid], v1 = part_sum[4 * tid + 1], v2 = part_sum[4 * tid + 2],
+                      v3 = part_sum[4 * tid + 3];
+            const int sum = v0 + v1 + v2 + v3;
+            int incl = sum;
+            for (int o = 1; o < 64; o <<= 1) {
+                const int y = __shfl_up(incl, o);
+                if (tid >= o) incl += y;
+            }
+            const int ex = incl - sum;
+            part_sum[4 * tid] = ex;
+            part_sum[4 * tid + 1] = ex + v0;
+            part_sum[4 * tid + 2] = ex + v0 + v1;
+            part_sum[4 * tid + 3] = ex + v0 + v1 + v2;
+        }
+        __syncthreads();
+        int acc = part_sum[tid];
+        for (int l = lb; l < le; ++l) {
+            offl[l] = acc;
+            if (d.rows) d.cls_off[(size_t)m * (k + 1) + l] = acc;
+            int q = acc;
+#pragma unroll
+            for (int w = 0; w < NW; ++w) {
+                const int x = cw[w * k + l];
+                cw[w * k + l] = q;
+                q += x;
+            }
+            acc += cnt[l];
+        }
+        if (tid == 0 && d.rows) d.cls_off[(size_t)m * (k + 1) + k] = n;
+        __syncthreads();
+        // placement in summation order: each wave walks its positions 64 at a time; lanes of one
+        // colour find their rank among the batch in the colour's batch mask, and the last of them
+        // moves the wave's cursor and clears the mask
+        int* cur = cw + wv * k;
+        unsigned long long* mw = msk + (size_t)wv * k;
+        for (int i0 = e0 + lane; i0 - lane < e1; i0 += 64) {
+            const int v = vertex_at(i0);
+            const bool in = i0 < e1 && v < n;
+            const int x = in ? (int)gview(c)[v] : 0;
+            if (in) atomicOr(&mw[x], 1ull << lane);
+            wave_sync();
+            unsigned long long same = 0;
+            int at = 0;
+            if (in) {
+                same = mw[x];
+                at = cur[x];
+            }
+            wave_sync();
+            if (in) {
+                const int rank = __popcll(same & ((1ull << lane) - 1ull));
+                lst[at + rank] = (int16_t)v;
+                if ((same >> lane) == 1ull) {
+                    cur[x] = at + rank + 1;
+                    mw[x] = 0ull;
+                }
+            }
+            wave_sync();
+        }
+        __syncthreads();
+        if (d.rows) {
+            int16_t* __restrict__ cv = d.cls_v + (size_t)m * d.cs;
+            for (int i = tid; i < n; i += 256) cv[i] = lst[i];
+        }
+    }
+    if (!want_legal) return;
+    __syncthreads();
+    // with an added fitness the member is legal only if that is 0 too
+    if (*feq_zero) {
+        const uint8_t* __restrict__ A8 = d.A8;
+        const size_t n_pad = d.n_pad;
+        if (!part) {
+            for (int q = tid; q < n && !*found; q += 256) {
+                const int v = lst[q];
+                const int x = gview(c)[v];
+                const int e = offl[x] + cnt[x];
+                const uint8_t* __restrict__ row = A8 + (size_t)v * n_pad;
+                for (int r = q + 1; r < e && !*found; r += 4) {
+                    int hit = 0;
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) hit |= r + u < e ? (int)gview(row)[lst[r + u]] : 0;
+                    if (hit) *found = 1;
+                }
+            }
+        } else {
+            // a cut edge: ends of different colours
+            for (int v = tid; v < n && !*found; v += 256) {
+                const int x = gview(c)[v];
+                const uint8_t* __restrict__ row = A8 + (size_t)v * n_pad;
+                for (int j = 0; j < v && !*found; j += 4) {
+                    const uint32_t a4 = gview((const uint32_t*)(row + j))[0];
+                    int hit = 0;
+#pragma unroll
+                    for (int u = 0; u < 4; ++u)
+                        if (j + u < v && ((a4 >> (8 * u)) & 0xFFu)) hit |= gview(c)[j + u] != x;
+                    if (hit) *found = 1;
+                }
+            }
+        }
+        __syncthreads();
+        if (tid == 0 && !*found) atomicMin(&st->legal_min[st->t & 1], m);
+    }
+}
+
+// First launch of a merged iteration: everything that depends only on the colours, in blocks of
+// three kinds: the members (class sizes, lists, legality), the group-concentration tiles with the
+// penalty operand, and the expansion of S^T.  As three launches of 4-5 us each they were most of a
+// small graph's iteration.  t stays as it is here (the launch that updates the weights advances
+// it), so the tiles may read it; a pending non-finite update ends the graph (adv).
+__global__ __launch_bounds__(256) void k_phase1(const GraphDev* __restrict__ gd, int G, int total_mem, int total_mt,
+                                                int total_ex, int honor_stop, int adv, int legal, int mt_flags,
+                                                int gsel) {
+    extern __shared__ __attribute__((aligned(16))) int p1_sh[];
+    int b = blockIdx.x;
+    if (b < total_mem) {
+        member_block(gd, G, b, honor_stop, adv, legal, p1_sh);
+        return;
+    }
+    b -= total_mem;
+    if (b < total_mt) {
+        mtilde_block(gd, G, b, honor_stop, mt_flags, gsel, nullptr, (uint8_t*)p1_sh, adv);
+        return;
+    }
+    b -= total_mt;
+    if (b < total_ex) expand_block(gd, G, b, honor_stop, 0, 1, adv);
+}
+
+// the stop rule's answer for the update launch of a merged iteration: uniform over the launch
+// (legal_min of this iteration is complete, and the entry cleared here is the next one's)
+__device__ __forceinline__ bool merged_stop(const GraphDev& d, const GraphState* st, long long t) {
+    return d.stop_on_legal && st->legal_min[t & 1] != 0x7FFFFFFF;
+}
+
+// End of a merged iteration, by one wave-sized group of lanes (lane of `lanes`) of the launch that
+// updates the weights: the route counters, then either the stop (lowest legal member, its colouring)
+// or t <- t + 1.  The launch's other blocks read st->tc, not t.
+__device__ __forceinline__ void merged_end(const GraphDev& d, GraphState* st, long long t, bool stop, int lane, int lanes) {
+    const int ld = stop ? st->legal_min[t & 1] : -1;
+    if (stop) {
+        const int16_t* c = d.c[st->pS] + (size_t)ld * d.cs;
+        for (int i = lane; i < d.n; i += lanes) d.snap[i] = c[i];
+    }
+    if (lane != 0) return;
+    const float tf = (float)t;
+    if (d.lambda * tf != 0.0f || d.mu * tf != 0.0f) st->it_dense += 1;
+    else st->it_nopen += 1;
+    if (stop) {
+        st->legal_d = ld;
+        st->stopped = 1;
+        return;
+    }
+    st->legal_min[(t + 1) & 1] = 0x7FFFFFFF;
+    st->t = t + 1;
+    st->steps_done += 1;
 }
 
 // ------------------------------------------------------- step 2, stop rule -----
@@ -1434,87 +1757,93 @@ __global__ __launch_bounds__(256) void k_update(const GraphDev* __restrict__ gd,
 // group, k <= 16 KPL: softmax along k (max subtracted), straight-through
 // gradient gW = s^ (G - sum_l s^_l G_l), update, smoothing, and in mode 0 the
 // argmax colouring of the updated row for the next iteration (written over
-// this iteration's colours).  Mode 1 writes gS and gW of graph gsel instead.
+// this iteration's colours).  Mode 1 writes gS and gW instead.
 // VAR bit 0: some graph of the launch has an added fitness term (equity or colour
 // cost), bit 1: some graph takes heavy-ball steps; the plain variant carries neither
 // stream's registers.
+struct RowCtx {
+    float nut, eta, rho, gam;
+    int problem, c1, c2, k;
+    bool smooth;
+};
+
+__device__ __forceinline__ RowCtx row_ctx(const GraphDev& d, long long t) {
+    RowCtx x;
+    x.nut = prob_added(d.problem) ? d.nu * (float)t : 0.0f;
+    x.eta = d.eta;
+    x.rho = d.rho;
+    x.gam = d.momentum;
+    x.problem = d.problem;
+    x.c1 = d.c1;
+    x.c2 = d.c2;
+    x.k = d.k;
+    x.smooth = d.nb_iter > 0 && ((t + 1) % d.nb_iter) == 0;
+    return x;
+}
+
+// loads of a row's weights and, where present, class sizes and velocity (indices clamped into the row inside the last
+// group of 16 instead of per-lane branches, so they are all in flight together).  Groups of 16 past the row's end are
+// skipped whole: KPL is sized for the largest k of the launch, and a row of a graph with fewer
+// colours would otherwise issue every group's loads.
 template <int KPL, int VAR>
-__device__ __forceinline__ void update_row(const GraphDev* __restrict__ gd, int G, int row, int honor_stop, int mode,
-                                           int gsel, float* __restrict__ gS_out, float* __restrict__ gW_out) {
-    const int l16 = threadIdx.x & 15;
-    const int g = graph_of_row(gd, G, row);
-    if (gsel >= 0 && g != gsel) return;
-    const GraphDev& d = gd[g];
-    GraphState* st = d.st;
-    if (honor_stop && st->stopped) return;
-    // the fast path's sparse graphs take their row update in the sparse-rows launch
-    if (mode == 0 && d.pfuse) return;
-    const int r = row - d.row_begin;
-    const int k = d.k;
-    const int m = r / d.n, i = r - m * d.n;
-    float* w = d.W[0] + (size_t)r * k;
-    const float* gs = d.G + (size_t)r * k;
-    const long long t = st->t;
-    const float nut = prob_added(d.problem) ? d.nu * (float)t : 0.0f;
-    const int prob = d.problem;
-    const int32_t* V = d.V[st->pS] + (size_t)m * k;
-    // fields used after the stores below stay in registers (no reload through gd)
-    const int c1 = d.c1, c2 = d.c2;
-    const float eta = d.eta, rho = d.rho;
-    const float gam = d.momentum;
-    float* __restrict__ vel = d.vel ? d.vel + (size_t)r * k : nullptr;
-    int16_t* __restrict__ cnext = d.c[st->pS] + (size_t)m * d.cs;
-    // every load of the row first (indices clamped into the row inside the last group of
-    // 16 instead of per-lane branches, so they are all in flight together), then the
-    // arithmetic.  Groups of 16 past the row's end are skipped whole: KPL is sized for the
-    // largest k of the launch, and a row of a graph with fewer colours would otherwise
-    // issue every group's loads.
-    constexpr bool ADD = (VAR & 1) != 0, MOM = (VAR & 2) != 0;
-    float wv[KPL], gv[KPL], vv[MOM ? KPL : 1];
-    int32_t cv[ADD ? KPL : 1];
+struct RowRegs {
+    float wv[KPL], vv[(VAR & 2) ? KPL : 1];
+    int32_t cv[(VAR & 1) ? KPL : 1];
+};
+
+template <int KPL, int VAR>
+__device__ __forceinline__ void row_load(RowRegs<KPL, VAR>& R, const RowCtx& x, const float* w, const int32_t* V,
+                                         const float* vel, int mode, int l16) {
+    const int k = x.k;
 #pragma unroll
-    for (int q = 0; q < KPL; ++q) {
-        if (16 * q < k) {
-            const int l = min(l16 + 16 * q, k - 1);
-            wv[q] = gview(w)[l];
-            gv[q] = gview(gs)[l];
-        }
-    }
-    if constexpr (ADD) {
-        if (nut != 0.0f) {
+    for (int q = 0; q < KPL; ++q)
+        if (16 * q < k) R.wv[q] = gview(w)[min(l16 + 16 * q, k - 1)];
+    if constexpr ((VAR & 1) != 0) {
+        if (x.nut != 0.0f) {
 #pragma unroll
             for (int q = 0; q < KPL; ++q)
-                if (16 * q < k) cv[q] = gview(V)[min(l16 + 16 * q, k - 1)];
+                if (16 * q < k) R.cv[q] = gview(V)[min(l16 + 16 * q, k - 1)];
         }
     }
-    if constexpr (MOM) {
+    if constexpr ((VAR & 2) != 0) {
         if (vel && mode != 1) {
 #pragma unroll
             for (int q = 0; q < KPL; ++q)
-                if (16 * q < k) vv[q] = gview((const float*)vel)[min(l16 + 16 * q, k - 1)];
+                if (16 * q < k) R.vv[q] = gview(vel)[min(l16 + 16 * q, k - 1)];
         }
     }
+}
+
+// the row's arithmetic; gv: the lane's entries of gS without the added-fitness term.  w, vel: the row's
+// memory (written in mode 0); gS_out, gW_out: the row's outputs (mode 1).  Returns the row's next colour
+// (mode 0), or -1 where the updated row is not finite.
+template <int KPL, int VAR>
+__device__ __forceinline__ int row_step(RowRegs<KPL, VAR>& R, float (&gv)[KPL], const RowCtx& x, float* __restrict__ w,
+                                        float* __restrict__ vel, int mode, float* __restrict__ gS_out,
+                                        float* __restrict__ gW_out, int l16) {
+    constexpr bool ADD = (VAR & 1) != 0, MOM = (VAR & 2) != 0;
+    const int k = x.k;
 #pragma unroll
     for (int q = 0; q < KPL; ++q) {
         const int l = l16 + 16 * q;
         if (l < k) {
             if constexpr (ADD) {
-                if (nut != 0.0f) gv[q] += nut * added_grad(prob, cv[q], l, c1, c2);
+                if (x.nut != 0.0f) gv[q] += x.nut * added_grad(x.problem, R.cv[q], l, x.c1, x.c2);
             }
         } else {
-            wv[q] = -INFINITY;
+            R.wv[q] = -INFINITY;
             gv[q] = 0.0f;
         }
     }
     float mx = -INFINITY;
 #pragma unroll
-    for (int q = 0; q < KPL; ++q) mx = fmaxf(mx, wv[q]);
+    for (int q = 0; q < KPL; ++q) mx = fmaxf(mx, R.wv[q]);
     mx = row16_max(mx);
     float ev[KPL];
     float z = 0.0f, qs = 0.0f;
 #pragma unroll
     for (int q = 0; q < KPL; ++q) {
-        ev[q] = (l16 + 16 * q < k) ? exp_soft(wv[q] - mx) : 0.0f;
+        ev[q] = (l16 + 16 * q < k) ? exp_soft(R.wv[q] - mx) : 0.0f;
         z += ev[q];
         qs += ev[q] * gv[q];
     }
@@ -1527,13 +1856,12 @@ __device__ __forceinline__ void update_row(const GraphDev* __restrict__ gd, int 
         for (int q = 0; q < KPL; ++q) {
             const int l = l16 + 16 * q;
             if (l < k) {
-                if (gS_out) gS_out[(size_t)r * k + l] = gv[q];
-                if (gW_out) gW_out[(size_t)r * k + l] = ev[q] * rz * (gv[q] - rq);
+                if (gS_out) gS_out[l] = gv[q];
+                if (gW_out) gW_out[l] = ev[q] * rz * (gv[q] - rq);
             }
         }
-        return;
+        return 0;
     }
-    const bool smooth = d.nb_iter > 0 && ((t + 1) % d.nb_iter) == 0;
     float best = -INFINITY;
     int bi = 0x7FFFFFFF, bad = 0;
 #pragma unroll
@@ -1543,12 +1871,12 @@ __device__ __forceinline__ void update_row(const GraphDev* __restrict__ gd, int 
             float step = ev[q] * rz * (gv[q] - rq);
             if constexpr (MOM) {
                 if (vel) {
-                    step = gam * vv[q] + step;  // heavy-ball velocity
+                    step = x.gam * R.vv[q] + step;  // heavy-ball velocity
                     vel[l] = step;
                 }
             }
-            float nw = wv[q] - eta * step;
-            if (smooth) nw = nw / rho;
+            float nw = R.wv[q] - x.eta * step;
+            if (x.smooth) nw = nw / x.rho;
             w[l] = nw;
             if (!finite_f(nw)) bad = 1;
             if (nw > best) { best = nw; bi = l; }
@@ -1559,22 +1887,229 @@ __device__ __forceinline__ void update_row(const GraphDev* __restrict__ gd, int 
     const int bmax = row16_max_i(bo);
     bi = row16_min_i(bo == bmax ? bi : 0x7FFFFFFF);
     bad = row16_max_i(bad);
-    if (l16 == 0) {
-        if (bad || bi >= k) {
-            bi = 0;
-            atomicExch(&st->next_bad, 1);
-        }
-        cnext[i] = (int16_t)bi;
+    return bad || bi >= k ? -1 : bi;
+}
+
+// merged: the row belongs to a merged iteration (its t is st->tc, the stop rule is answered by the
+// first launch, and the graph's first row also ends the iteration)
+template <int KPL, int VAR>
+__device__ __forceinline__ void update_row(const GraphDev* __restrict__ gd, int G, int row, int honor_stop, int mode,
+                                           int gsel, float* __restrict__ gS_out, float* __restrict__ gW_out, int merged) {
+    const int l16 = threadIdx.x & 15;
+    const int g = graph_of_row(gd, G, row);
+    if (gsel >= 0 && g != gsel) return;
+    const GraphDev& d = gd[g];
+    GraphState* st = d.st;
+    if (honor_stop && st->stopped) return;
+    // the fast path's sparse graphs take their row update in the sparse-rows launch
+    if (mode == 0 && d.pfuse) return;
+    const int r = row - d.row_begin;
+    const long long t = merged ? st->tc : st->t;
+    if (merged) {
+        const bool stop = merged_stop(d, st, t);
+        if (r == 0) merged_end(d, st, t, stop, l16, 16);
+        if (stop) return;
+    }
+    const int k = d.k;
+    const int m = r / d.n, i = r - m * d.n;
+    float* w = d.W[0] + (size_t)r * k;
+    const float* gs = d.G + (size_t)r * k;
+    const RowCtx x = row_ctx(d, t);
+    float* vel = d.vel ? d.vel + (size_t)r * k : nullptr;
+    int16_t* __restrict__ cnext = d.c[st->pS] + (size_t)m * d.cs;
+    RowRegs<KPL, VAR> R;
+    float gv[KPL];
+#pragma unroll
+    for (int q = 0; q < KPL; ++q)
+        if (16 * q < k) gv[q] = gview(gs)[min(l16 + 16 * q, k - 1)];
+    row_load<KPL, VAR>(R, x, w, d.V[st->pS] + (size_t)m * k, vel, mode, l16);
+    const int c = row_step<KPL, VAR>(R, gv, x, w, vel, mode, gS_out ? gS_out + (size_t)r * k : nullptr,
+                                     gW_out ? gW_out + (size_t)r * k : nullptr, l16);
+    if (mode == 0 && l16 == 0) {
+        if (c < 0) atomicExch(&st->next_bad, 1);
+        cnext[i] = (int16_t)max(c, 0);
     }
 }
 
 template <int KPL, int VAR>
 __global__ __launch_bounds__(256) void k_update_rows(const GraphDev* __restrict__ gd, int G, int total_rows,
                                                      int honor_stop, int mode, int gsel, float* __restrict__ gS_out,
-                                                     float* __restrict__ gW_out) {
+                                                     float* __restrict__ gW_out, int merged) {
     const int row = blockIdx.x * 16 + (threadIdx.x >> 4);
     if (row >= total_rows) return;
-    update_row<KPL, VAR>(gd, G, row, honor_stop, mode, gsel, gS_out, gW_out);
+    update_row<KPL, VAR>(gd, G, row, honor_stop, mode, gsel, gS_out, gW_out, merged);
+}
+
+// ------------------------------------------------------------- class-row sums ----
+
+// Steps 2-4 of a graph in fp32 operands, without a contraction: with one-hot S_d,
+//   G[d, i, l] = sum_{j in class (d, l)} (a_ij + P_ij),
+// so a wave takes 64 vertices i of member d (one per lane) and walks the member's vertices j
+// grouped by colour: A and P are symmetric, so row j of each gives its 64 entries in one load (P)
+// or one 64-bit word (A).  n^2 D additions instead of the contraction's n^2 D k multiply-adds: at
+// the 157 TFLOP/s of the fp32 matrix instructions the additions win from k of about 4 up, and the
+// walk takes the same time whatever the class sizes.  The counts come first, exactly, then the P_ij in FP32 one
+// after the other in the order of the member's list, which is the order of the fp32 contraction's
+// accumulation: the same bits.  The block's four waves share the colours by quarters of the list;
+// the 64 gradient rows meet in LDS and the same block takes the row update (or writes the gradients).
+// n = 500, k = 50, D = 64: 27 us against 44 us (contraction) + 8 us (row update); gradients at n = 1000,
+// k = 85, D = 48: 49 us against 162 + 11 us.
+//
+// mode 0: step (merged iteration); 1: gS / gW of graph gsel and 2 f_color; 2: 2 f_color alone.
+template <int KPL, int VAR>
+__global__ __launch_bounds__(256) void k_class_rows(const GraphDev* __restrict__ gd, int G, int total_blocks,
+                                                    int honor_stop, int mode, int gsel, float* __restrict__ gS_out,
+                                                    float* __restrict__ gW_out) {
+    extern __shared__ __attribute__((aligned(16))) uint8_t cr_sh[];
+    const int b = blockIdx.x;
+    if (b >= total_blocks) return;
+    const int g = find_graph(gd, G, b, [](const GraphDev& x) { return x.cr_begin; });
+    if (gsel >= 0 && g != gsel) return;
+    const GraphDev& d = gd[g];
+    GraphState* st = d.st;
+    if (honor_stop && st->stopped) return;
+    const long long t = st->tc;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    if (mode == 0) {
+        const bool stop = merged_stop(d, st, t);
+        if (b == d.cr_begin && tid < 64) merged_end(d, st, t, stop, tid, 64);
+        if (stop) return;
+    }
+    const int n = d.n, k = d.k, D = d.D;
+    const int loc = b - d.cr_begin;
+    const int strip = loc / D, m = loc - strip * D;      // the members of a strip are neighbours: they share P's columns in L2
+    const size_t n_pad = d.n_pad;
+    const int KS = k | 1;                                // odd row stride: the lanes of a column on different banks
+    float* Gt = (float*)cr_sh;                           // [64][KS]
+    unsigned long long* msk = (unsigned long long*)(cr_sh + ((size_t)64 * KS * 4 + 15) / 16 * 16);   // [n]
+    int* off = (int*)(msk + n);                          // [k + 1]
+    int16_t* lst = (int16_t*)(off + k + 1);              // [n]
+    const float tf = (float)t;
+    const bool pen = mode == 1 || (mode == 0 && ((d.lambda * tf != 0.0f) || (d.mu * tf != 0.0f)));
+    const float sgn = prob_partition(d.problem) ? -1.0f : 1.0f;
+    {
+        const int16_t* __restrict__ cv = d.cls_v + (size_t)m * d.cs;
+        const unsigned long long* __restrict__ Ab = d.Ab + (size_t)strip * n_pad;
+        for (int q = tid; q < n; q += 256) {
+            const int j = gview(cv)[q];
+            lst[q] = (int16_t)j;
+            msk[q] = gview(Ab)[j];
+        }
+        const int32_t* __restrict__ co = d.cls_off + (size_t)m * (k + 1);
+        for (int l = tid; l <= k; l += 256) off[l] = gview(co)[l];
+    }
+    __syncthreads();
+    // this wave's colours: those whose list starts in its quarter
+    int l0 = 0, l1 = 0;
+    for (int lb = 0; lb < k; lb += 64) {
+        const int l = lb + lane;
+        const long long o = l < k ? 4LL * off[l] : (long long)1 << 40;
+        l0 += __popcll(__ballot(o < (long long)wave * n));
+        l1 += __popcll(__ballot(o < (long long)(wave + 1) * n));
+    }
+    if (wave == 3) l1 = k;      // and the empty classes at the end
+    l0 = __builtin_amdgcn_readfirstlane(l0);
+    l1 = __builtin_amdgcn_readfirstlane(l1);
+    const int p0 = __builtin_amdgcn_readfirstlane(off[l0]);
+    const int p1 = __builtin_amdgcn_readfirstlane(off[l1]);
+    float* __restrict__ Gl = Gt + lane * KS;
+    // the neighbours of vertex i (the lane) in each class
+    {
+        int l = l0, pe = __builtin_amdgcn_readfirstlane(off[l0 < k ? l0 + 1 : l0]);
+        int c = 0;
+        for (int q0 = p0; q0 < p1; q0 += 64) {
+            const unsigned long long mv = q0 + lane < p1 ? msk[q0 + lane] : 0ull;
+            const int lo = (int)(uint32_t)mv, hi = (int)(uint32_t)(mv >> 32);
+            const int nn = min(64, p1 - q0);
+#pragma unroll 8
+            for (int u = 0; u < nn; ++u) {
+                while (q0 + u == pe) {
+                    Gl[l] = (float)c;
+                    c = 0;
+                    ++l;
+                    pe = __builtin_amdgcn_readfirstlane(off[l + 1]);
+                }
+                const unsigned long long mm = (unsigned long long)(uint32_t)__builtin_amdgcn_readlane(lo, u) |
+                                              ((unsigned long long)(uint32_t)__builtin_amdgcn_readlane(hi, u) << 32);
+                c += __builtin_amdgcn_inverse_ballot_w64(mm) ? 1 : 0;
+            }
+        }
+        // the last class with a vertex, then empty ones
+        for (; l < l1; ++l) {
+            Gl[l] = (float)c;
+            c = 0;
+        }
+    }
+    if (mode != 0) {
+        // 2 f_color: the counts at the vertices' own colours
+        __syncthreads();
+        if (wave == 0) {
+            const int i = strip * 64 + lane;
+            int own = i < n ? (int)Gt[lane * KS + gview(d.c[st->pS] + (size_t)m * d.cs)[i]] : 0;
+            for (int o = 32; o >= 1; o >>= 1) own += __shfl_xor(own, o);
+            if (lane == 0 && own) atomicAdd(&d.f2[m], own);
+        }
+        if (mode == 2) return;
+        __syncthreads();
+    }
+    if (pen && p0 < p1) {
+        constexpr int U = 16;       // loads in flight per lane
+        const float* __restrict__ Pc = (const float*)d.Pop + (size_t)strip * 64 + lane;
+        int l = l0, pe = __builtin_amdgcn_readfirstlane(off[l0 + 1]);
+        while (pe == p0) pe = __builtin_amdgcn_readfirstlane(off[++l + 1]);
+        float acc = Gl[l];
+        float v[U];
+        auto fetch = [&](int q0) {
+            const int jl = lst[min(q0 + (lane & (U - 1)), p1 - 1)];
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                v[u] = gview(Pc)[(size_t)(uint32_t)__builtin_amdgcn_readlane(jl, u) * n_pad];
+        };
+        fetch(p0);
+        for (int q0 = p0; q0 < p1; q0 += U) {
+            float x[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) x[u] = v[u];
+            if (q0 + U < p1) fetch(q0 + U);
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                if (q0 + u < p1) {
+                    if (q0 + u == pe) {
+                        Gl[l] = acc;
+                        do { pe = __builtin_amdgcn_readfirstlane(off[++l + 1]); } while (pe == q0 + u);
+                        acc = Gl[l];
+                    }
+                    acc += x[u];
+                }
+            }
+        }
+        Gl[l] = acc;
+    }
+    __syncthreads();
+    // row update, 16 lanes per row
+    const RowCtx x = row_ctx(d, t);
+    const int l16 = tid & 15;
+    const int32_t* V = d.V[st->pS] + (size_t)m * k;
+    int16_t* __restrict__ cnext = d.c[st->pS] + (size_t)m * d.cs;
+    for (int rr = tid >> 4; rr < 64; rr += 16) {
+        const int i = strip * 64 + rr;
+        if (i >= n) break;
+        const size_t ro = ((size_t)m * n + i) * k;
+        float* w = d.W[0] + ro;
+        float* vel = d.vel ? d.vel + ro : nullptr;
+        RowRegs<KPL, VAR> R;
+        float gv[KPL];
+        row_load<KPL, VAR>(R, x, w, V, vel, mode, l16);
+#pragma unroll
+        for (int q = 0; q < KPL; ++q)
+            if (16 * q < k) gv[q] = sgn * Gt[rr * KS + min(l16 + 16 * q, k - 1)];
+        const int c = row_step<KPL, VAR>(R, gv, x, w, vel, mode, gS_out ? gS_out + ro : nullptr,
+                                         gW_out ? gW_out + ro : nullptr, l16);
+        if (mode == 0 && l16 == 0) {
+            if (c < 0) atomicExch(&st->next_bad, 1);
+            cnext[i] = (int16_t)max(c, 0);
+        }
+    }
 }
 
 // t <- t + 1 for every graph still running.
@@ -1584,11 +2119,15 @@ __global__ void k_advance(const GraphDev* __restrict__ gd, int G) {
     advance_graph(gd[g].st);
 }
 
-// FP64 loss of one graph: L = sum main fitness + nu t sum added fitness + lambda t kappa
+// Fitness report of every graph (one block each), then (unless out is null) graph g's FP64 loss: L = sum main fitness + nu t sum added fitness + lambda t kappa
 // - mu t varpi (kappa, varpi from the group-concentration kernel's partials).
-__global__ __launch_bounds__(256) void k_loss(const GraphDev* __restrict__ gd, int g, int ntiles,
+__global__ __launch_bounds__(256) void k_loss(const GraphDev* __restrict__ gd, int G, int g, int ntiles,
                                               double* __restrict__ out) {
     __shared__ double red[4][256];
+    __shared__ int best;
+    fitness_graph(gd, blockIdx.x, 0, kFlagReport, &best);
+    if ((int)blockIdx.x != g || !out) return;
+    __syncthreads();
     const GraphDev& d = gd[g];
     double ka = 0, vb = 0, sf = 0, se = 0;
     for (int u = threadIdx.x; u < ntiles; u += 256) {
@@ -1658,8 +2197,10 @@ __global__ void k_state(const GraphDev* __restrict__ gd, int G, int op, int g_on
     if (op == 0) {            // reset run state (keeps t and the route counters)
         st->stopped = 0; st->error = 0; st->legal_d = -1; st->steps_done = 0; st->next_bad = 0;
         st->prep_ticket = 0;
+        st->legal_min[0] = st->legal_min[1] = 0x7FFFFFFF;
     } else if (op == 1) {     // set t
         st->t = t;
+        st->legal_min[0] = st->legal_min[1] = 0x7FFFFFFF;
     } else if (op == 2) {     // clear steps counter only
         st->steps_done = 0; st->legal_d = -1;
     } else if (op == 3) {     // the caller's buffer holds the weights again
@@ -1796,11 +2337,10 @@ hipError_t launch_init_weights(float* W, long long count, unsigned long long see
     return hipSuccess;
 }
 
-hipError_t launch_pack_graph(const uint8_t* A, int n, int n_pad, int prec, uint8_t* A8, void* Aop, int* bad,
-                             unsigned long long* ones, hipStream_t s) {
-    const long long total = (long long)n_pad * n_pad;
-    const int blocks = (int)std::min<long long>((total + 255) / 256, 4096);
-    hipLaunchKernelGGL(k_pack_graph, dim3(blocks), dim3(256), 0, s, A, n, n_pad, prec, A8, Aop, bad, ones);
+hipError_t launch_pack_graph(const uint8_t* A, int n, int n_pad, int op, uint8_t* A8, unsigned long long* Ab, void* Aop,
+                             int* bad, unsigned long long* ones, hipStream_t s) {
+    const int T = n_pad / 64;
+    hipLaunchKernelGGL(k_pack_graph, dim3(T * T), dim3(256), 0, s, A, n, n_pad, op, A8, Ab, Aop, bad, ones);
     TCOL_LAUNCH_CHECK();
     return hipSuccess;
 }
@@ -1927,20 +2467,20 @@ int update_rows_kpl(int kmax) {
 }
 
 hipError_t launch_update_rows(const GraphDev* gd, int G, int total_rows, int kmax, int var, int honor_stop, int mode,
-                              int gsel, float* gS_out, float* gW_out, hipStream_t s) {
+                              int gsel, float* gS_out, float* gW_out, int merged, hipStream_t s) {
     if (total_rows <= 0) return hipSuccess;
     if (var < 0 || var > 3) return hipErrorInvalidValue;
     const dim3 grid(ceil_div(total_rows, 16)), blk(256);
 #define TCOL_UR(KP)                                                                                                  \
     switch (var) {                                                                                                   \
         case 0: hipLaunchKernelGGL((k_update_rows<KP, 0>), grid, blk, 0, s, gd, G, total_rows, honor_stop, mode, gsel, \
-                                   gS_out, gW_out); break;                                                           \
+                                   gS_out, gW_out, merged); break;                                                           \
         case 1: hipLaunchKernelGGL((k_update_rows<KP, 1>), grid, blk, 0, s, gd, G, total_rows, honor_stop, mode, gsel, \
-                                   gS_out, gW_out); break;                                                           \
+                                   gS_out, gW_out, merged); break;                                                           \
         case 2: hipLaunchKernelGGL((k_update_rows<KP, 2>), grid, blk, 0, s, gd, G, total_rows, honor_stop, mode, gsel, \
-                                   gS_out, gW_out); break;                                                           \
+                                   gS_out, gW_out, merged); break;                                                           \
         default: hipLaunchKernelGGL((k_update_rows<KP, 3>), grid, blk, 0, s, gd, G, total_rows, honor_stop, mode, gsel, \
-                                    gS_out, gW_out); break;                                                          \
+                                    gS_out, gW_out, merged); break;                                                          \
     }
     switch (update_rows_kpl(kmax)) {
         case 2: TCOL_UR(2) break;
@@ -1958,14 +2498,67 @@ hipError_t launch_update_rows(const GraphDev* gd, int G, int total_rows, int kma
     return hipSuccess;
 }
 
+size_t phase1_lds(int kmax, int nmax, int lists) {
+    // without lists only the scratch and the counts are used
+    size_t b = lists ? member_lds_bytes(kmax, nmax) : sizeof(int) * ((size_t)kPrepScratch + kmax);
+    if (b < (size_t)kMtLds) b = kMtLds;
+    return (b + 15) / 16 * 16;
+}
+
+hipError_t phase1_prepare() {
+    return hipFuncSetAttribute((const void*)k_phase1, hipFuncAttributeMaxDynamicSharedMemorySize, kMaxBlockLds);
+}
+
+hipError_t launch_phase1(const GraphDev* gd, int G, int total_mem, int total_mt, int total_ex, size_t lds,
+                         int honor_stop, int adv, int legal, int mt_flags, int gsel, hipStream_t s) {
+    if (lds > (size_t)kMaxBlockLds) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(k_phase1, dim3(total_mem + total_mt + total_ex), dim3(256), lds, s, gd, G, total_mem, total_mt,
+                       total_ex, honor_stop, adv, legal, mt_flags, gsel);
+    TCOL_LAUNCH_CHECK();
+    return hipSuccess;
+}
+
+size_t class_rows_lds(int k, int n) {
+    return ((size_t)64 * (k | 1) * 4 + 15) / 16 * 16 + 8 * (size_t)n + 4 * ((size_t)k + 1) + 2 * (size_t)((n + 1) & ~1);
+}
+
+#define TCOL_CR_KPL(X, V) X(2, V) X(4, V) X(6, V) X(8, V) X(12, V) X(18, V) X(24, V) X(36, V)
+
+hipError_t class_rows_prepare(int kmax, int var) {
+#define TCOL_CR_ATTR(KP, VR)                                                                                   \
+    if (update_rows_kpl(kmax) == KP && var == VR)                                                              \
+        return hipFuncSetAttribute((const void*)k_class_rows<KP, VR>,                                          \
+                                   hipFuncAttributeMaxDynamicSharedMemorySize, kMaxBlockLds);
+    TCOL_CR_KPL(TCOL_CR_ATTR, 0) TCOL_CR_KPL(TCOL_CR_ATTR, 1) TCOL_CR_KPL(TCOL_CR_ATTR, 2) TCOL_CR_KPL(TCOL_CR_ATTR, 3)
+#undef TCOL_CR_ATTR
+    return hipErrorInvalidValue;
+}
+
+hipError_t launch_class_rows(const GraphDev* gd, int G, int blocks, size_t lds, int kmax, int var, int honor_stop,
+                             int mode, int gsel, float* gS_out, float* gW_out, hipStream_t s) {
+    if (blocks <= 0) return hipSuccess;
+    if (lds > (size_t)kMaxBlockLds) return hipErrorInvalidValue;
+    bool done = false;
+#define TCOL_CR_LAUNCH(KP, VR)                                                                                 \
+    if (!done && update_rows_kpl(kmax) == KP && var == VR) {                                                   \
+        k_class_rows<KP, VR><<<blocks, 256, lds, s>>>(gd, G, blocks, honor_stop, mode, gsel, gS_out, gW_out);  \
+        done = true;                                                                                           \
+    }
+    TCOL_CR_KPL(TCOL_CR_LAUNCH, 0) TCOL_CR_KPL(TCOL_CR_LAUNCH, 1) TCOL_CR_KPL(TCOL_CR_LAUNCH, 2) TCOL_CR_KPL(TCOL_CR_LAUNCH, 3)
+#undef TCOL_CR_LAUNCH
+    if (!done) return hipErrorInvalidValue;
+    TCOL_LAUNCH_CHECK();
+    return hipSuccess;
+}
+
 hipError_t launch_advance(const GraphDev* gd, int G, hipStream_t s) {
     hipLaunchKernelGGL(k_advance, dim3(ceil_div(G, 64)), dim3(64), 0, s, gd, G);
     TCOL_LAUNCH_CHECK();
     return hipSuccess;
 }
 
-hipError_t launch_loss(const GraphDev* gd, int g, int ntiles, double* out, hipStream_t s) {
-    hipLaunchKernelGGL(k_loss, dim3(1), dim3(256), 0, s, gd, g, ntiles, out);
+hipError_t launch_loss(const GraphDev* gd, int G, int g, int ntiles, double* out, hipStream_t s) {
+    hipLaunchKernelGGL(k_loss, dim3(G), dim3(256), 0, s, gd, G, g, ntiles, out);
     TCOL_LAUNCH_CHECK();
     return hipSuccess;
 }

@@ -7,9 +7,9 @@ namespace tcol {
 
 // initial weights N(0, sigma0^2) from Philox4x32-10 (stream 1) and Box-Muller
 hipError_t launch_init_weights(float* W, long long count, unsigned long long seed, double sigma0, hipStream_t s);
-// validates A, writes A8 and the operand copy, adds the number of ones of A to *ones
-hipError_t launch_pack_graph(const uint8_t* A, int n, int n_pad, int prec, uint8_t* A8, void* Aop, int* bad,
-                             unsigned long long* ones, hipStream_t s);
+// validates A and writes A8 and Ab (unless A8 is null) and the operand copy, adds the number of ones of A to *ones
+hipError_t launch_pack_graph(const uint8_t* A, int n, int n_pad, int op, uint8_t* A8, unsigned long long* Ab, void* Aop,
+                             int* bad, unsigned long long* ones, hipStream_t s);
 hipError_t launch_colors(const GraphDev* gd, int G, int total_rows, int honor_stop, hipStream_t s);
 // class sizes and vertex-major colours; with lists != 0 also the class lists of graphs on the
 // sparse penalty (dynamic LDS from prep_lds)
@@ -44,9 +44,22 @@ hipError_t launch_update(const GraphDev* gd, int G, int total_rows, int honor_st
 int update_rows_kpl(int kmax);
 // var: bit 0 some graph has an added fitness term, bit 1 some graph takes heavy-ball steps
 hipError_t launch_update_rows(const GraphDev* gd, int G, int total_rows, int kmax, int var, int honor_stop, int mode,
-                              int gsel, float* gS_out, float* gW_out, hipStream_t s);
+                              int gsel, float* gS_out, float* gW_out, int merged, hipStream_t s);
+// merged iterations: first launch (members, group-concentration tiles, expansion blocks; lists: some
+// graph needs its class lists), and the class-row sums with the row update (graphs with `rows`;
+// modes in k_class_rows)
+constexpr int kMaxBlockLds = 150 * 1024;
+size_t phase1_lds(int kmax, int nmax, int lists);
+hipError_t phase1_prepare();
+hipError_t launch_phase1(const GraphDev* gd, int G, int total_mem, int total_mt, int total_ex, size_t lds,
+                         int honor_stop, int adv, int legal, int mt_flags, int gsel, hipStream_t s);
+size_t class_rows_lds(int k, int n);
+hipError_t class_rows_prepare(int kmax, int var);
+hipError_t launch_class_rows(const GraphDev* gd, int G, int blocks, size_t lds, int kmax, int var, int honor_stop,
+                             int mode, int gsel, float* gS_out, float* gW_out, hipStream_t s);
 hipError_t launch_advance(const GraphDev* gd, int G, hipStream_t s);
-hipError_t launch_loss(const GraphDev* gd, int g, int ntiles, double* out, hipStream_t s);
+// fitness report of every graph and, unless out is null, the loss of graph g
+hipError_t launch_loss(const GraphDev* gd, int G, int g, int ntiles, double* out, hipStream_t s);
 hipError_t launch_copy_report(const GraphDev* gd, int g, int16_t* colors, int64_t* fcol, int64_t* feq,
                               hipStream_t s);
 // graph g's selection as [d][i][s] (s < cmax), -1 past a vertex's demand
