@@ -312,10 +312,9 @@ __device__ __forceinline__ void gemm_sweep(f32x4 (&acc)[tile_mt(BM)][NTW], const
 // when the MFMAs need them.  They become 2.0 rather than 1.0: bf16 2.0 is 0x4000, a
 // single byte, so one shift-and-mask and one byte permute make each pair; the operand
 // P of an fp4 graph is stored halved (exact in bf16), so the products are unchanged.  This avoids a bf16 copy of S and quarters the S bytes
-// staged and read from LDS, so three stage buffers fit where the fp4 A.S sweep keeps
-// two.  The S rows move with 4-byte direct-to-LDS loads (a load writes 4 bytes per lane,
-// 256 per wave: 8 rows of 32 bytes); word w of row r sits at slot w ^ (((r >> 3) & 1) << 2),
-// so a fragment read (16 consecutive rows, one word each) touches 16 different banks
+// staged and read from LDS, so more stage buffers fit than the fp4 A.S sweep has.
+// A direct-to-LDS load of the S rows takes 32 rows of 32 bytes per wave, 16 bytes per lane;
+// word w of row r sits at slot w ^ (((r >> 3) & 1) << 2), so a fragment read (16 consecutive rows, one word each) touches 16 different banks
 // pairs.
 template <int BM, int NTW>
 struct PenTile {
@@ -325,10 +324,15 @@ struct PenTile {
     static constexpr int A_BYTES = BM * kStageRowBytes;
     static constexpr int STAGE = A_BYTES + BN * BROW;
     static constexpr int AG = BM / (8 * T::WAVES);               // 16-byte-lane loads of P per wave per stage
-    static constexpr int BG = BN * BROW / (256 * T::WAVES);      // 4-byte-lane loads of S per wave per stage
-    static_assert(BM % (8 * T::WAVES) == 0 && (BN * BROW) % (256 * T::WAVES) == 0, "penalty load split");
-    static constexpr int NB = 3 * STAGE <= T::NB * T::STAGE ? 3 : 2;   // within the block's stage buffers
-    static_assert(NB * STAGE <= T::NB * T::STAGE, "penalty stages fit");
+    static constexpr int BG = (NTW + T::WAVES - 1) / T::WAVES;   // 16-byte-lane loads of S (32 rows) per wave per stage
+    static_assert(BM % (8 * T::WAVES) == 0 && BN == 32 * NTW, "penalty load split");
+    // as many stages in flight as the block's stage buffers hold, up to eight: a tile of few subtiles
+    // computes a stage in a fraction of the load latency (with the 16-byte S loads, launch with both
+    // passes: (128, 6) at n = 1000, k = 90, D = 256 75.8 -> 71.9 us; (64, 4), 3 -> 6 stages, at n = 1000,
+    // k = 28, D = 128 23.3 -> 22.8 us)
+    static constexpr int FIT = T::NB * T::STAGE / STAGE;
+    static constexpr int NB = FIT > 8 ? 8 : FIT;
+    static_assert(NB >= 2 && (NB - 1) * (AG + BG) < 64, "penalty stages fit");
 };
 
 template <int BM, int NTW>
@@ -388,9 +392,9 @@ __device__ __forceinline__ void pen_mma(f32x4 (&acc)[tile_mt(BM)][NTW], const Pe
         }
 }
 
-// P rows: as stage_load (8-row groups of 128 bytes, 16 bytes per lane); S rows: 8-row
-// groups of 32 bytes, 4 bytes per lane (lane L: row L / 8, slot L % 8, which receives
-// global word (L % 8) ^ (((row >> 3) & 1) << 2))
+// P rows: as stage_load (8-row groups of 128 bytes, 16 bytes per lane); S rows: 32-row
+// groups of 32 bytes, 16 bytes per lane (lane L: row L / 2, half L % 2, which receives
+// global half (L % 2) ^ ((row >> 3) & 1))
 template <int BM, int NTW>
 __device__ __forceinline__ void pen_load(const uint8_t* __restrict__ Prow, const uint8_t* __restrict__ Srow,
                                          size_t ldp, size_t lds_, int s, uint8_t* buf, int lane, int wave) {
@@ -409,14 +413,14 @@ __device__ __forceinline__ void pen_load(const uint8_t* __restrict__ Prow, const
     }
     {
         uint8_t* bb = buf + P::A_BYTES;
-        const int rsub = lane >> 3, slot = lane & 7;
+        // (past the last 32 rows a wave repeats them: every wave counts the same number of loads)
 #pragma unroll
         for (int gi = 0; gi < P::BG; ++gi) {
-            const int grp = wave + T::WAVES * gi;
-            const int r = grp * 8 + rsub;
-            const int w = slot ^ (((r >> 3) & 1) << 2);
-            const uint8_t* src = Srow + (size_t)r * lds_ + (size_t)s * P::BROW + w * 4;
-            __builtin_amdgcn_global_load_lds((gbl_ptr)src, (lds_ptr)(bb + grp * 8 * P::BROW), 4, 0, 0);
+            const int grp = min(wave + T::WAVES * gi, NTW - 1);
+            const int r = grp * 32 + (lane >> 1);
+            const int h = (lane & 1) ^ ((r >> 3) & 1);
+            const uint8_t* src = Srow + (size_t)r * lds_ + (size_t)s * P::BROW + h * 16;
+            __builtin_amdgcn_global_load_lds((gbl_ptr)src, (lds_ptr)(bb + grp * 32 * P::BROW), 16, 0, 0);
         }
     }
 }

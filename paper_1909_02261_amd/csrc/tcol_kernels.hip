@@ -1791,13 +1791,18 @@ struct RowRegs {
     int32_t cv[(VAR & 1) ? KPL : 1];
 };
 
+// gs: the row of G, unless null, into gv.
 template <int KPL, int VAR>
-__device__ __forceinline__ void row_load(RowRegs<KPL, VAR>& R, const RowCtx& x, const float* w, const int32_t* V,
-                                         const float* vel, int mode, int l16) {
+__device__ __forceinline__ void row_load(RowRegs<KPL, VAR>& R, float (&gv)[KPL], const RowCtx& x, const float* w,
+                                         const float* gs, const int32_t* V, const float* vel, int mode, int l16) {
     const int k = x.k;
 #pragma unroll
     for (int q = 0; q < KPL; ++q)
-        if (16 * q < k) R.wv[q] = gview(w)[min(l16 + 16 * q, k - 1)];
+        if (16 * q < k) {
+            const int l = min(l16 + 16 * q, k - 1);
+            R.wv[q] = gview(w)[l];
+            if (gs) gv[q] = gview(gs)[l];
+        }
     if constexpr ((VAR & 1) != 0) {
         if (x.nut != 0.0f) {
 #pragma unroll
@@ -1919,10 +1924,7 @@ __device__ __forceinline__ void update_row(const GraphDev* __restrict__ gd, int 
     int16_t* __restrict__ cnext = d.c[st->pS] + (size_t)m * d.cs;
     RowRegs<KPL, VAR> R;
     float gv[KPL];
-#pragma unroll
-    for (int q = 0; q < KPL; ++q)
-        if (16 * q < k) gv[q] = gview(gs)[min(l16 + 16 * q, k - 1)];
-    row_load<KPL, VAR>(R, x, w, d.V[st->pS] + (size_t)m * k, vel, mode, l16);
+    row_load<KPL, VAR>(R, gv, x, w, gs, d.V[st->pS] + (size_t)m * k, vel, mode, l16);
     const int c = row_step<KPL, VAR>(R, gv, x, w, vel, mode, gS_out ? gS_out + (size_t)r * k : nullptr,
                                      gW_out ? gW_out + (size_t)r * k : nullptr, l16);
     if (mode == 0 && l16 == 0) {
@@ -1987,6 +1989,25 @@ __global__ __launch_bounds__(256) void k_class_rows(const GraphDev* __restrict__
     const float tf = (float)t;
     const bool pen = mode == 1 || (mode == 0 && ((d.lambda * tf != 0.0f) || (d.mu * tf != 0.0f)));
     const float sgn = prob_partition(d.problem) ? -1.0f : 1.0f;
+    // the row update's rows: 16 lanes each, four rows per group of lanes; where they fit in registers
+    // their loads go out now, behind the sums
+    constexpr bool AHEAD = KPL <= 4;
+    const RowCtx x = row_ctx(d, t);
+    const int l16 = tid & 15, g16 = tid >> 4;
+    const int32_t* V = d.V[st->pS] + (size_t)m * k;
+    int16_t* __restrict__ cnext = d.c[st->pS] + (size_t)m * d.cs;
+    const size_t ro0 = ((size_t)m * n + strip * 64 + g16) * k;
+    RowRegs<KPL, VAR> ahead[AHEAD ? 4 : 1];
+    if constexpr (AHEAD) {
+        if (mode != 2) {
+            float none[KPL];
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+                if (strip * 64 + g16 + 16 * u < n)
+                    row_load<KPL, VAR>(ahead[u], none, x, d.W[0] + ro0 + (size_t)16 * u * k, nullptr, V,
+                                       d.vel ? d.vel + ro0 + (size_t)16 * u * k : nullptr, mode, l16);
+        }
+    }
     {
         const int16_t* __restrict__ cv = d.cls_v + (size_t)m * d.cs;
         const unsigned long long* __restrict__ Ab = d.Ab + (size_t)strip * n_pad;
@@ -2087,22 +2108,24 @@ __global__ __launch_bounds__(256) void k_class_rows(const GraphDev* __restrict__
     }
     __syncthreads();
     // row update, 16 lanes per row
-    const RowCtx x = row_ctx(d, t);
-    const int l16 = tid & 15;
-    const int32_t* V = d.V[st->pS] + (size_t)m * k;
-    int16_t* __restrict__ cnext = d.c[st->pS] + (size_t)m * d.cs;
-    for (int rr = tid >> 4; rr < 64; rr += 16) {
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+        const int rr = g16 + 16 * u;
         const int i = strip * 64 + rr;
         if (i >= n) break;
-        const size_t ro = ((size_t)m * n + i) * k;
-        float* w = d.W[0] + ro;
-        float* vel = d.vel ? d.vel + ro : nullptr;
+        float* w = d.W[0] + ro0 + (size_t)16 * u * k;
+        float* vel = d.vel ? d.vel + ro0 + (size_t)16 * u * k : nullptr;
         RowRegs<KPL, VAR> R;
         float gv[KPL];
-        row_load<KPL, VAR>(R, x, w, V, vel, mode, l16);
+        if constexpr (AHEAD) {
+            R = ahead[u];
+        } else {
+            row_load<KPL, VAR>(R, gv, x, w, nullptr, V, vel, mode, l16);
+        }
 #pragma unroll
         for (int q = 0; q < KPL; ++q)
             if (16 * q < k) gv[q] = sgn * Gt[rr * KS + min(l16 + 16 * q, k - 1)];
+        const size_t ro = ro0 + (size_t)16 * u * k;
         const int c = row_step<KPL, VAR>(R, gv, x, w, vel, mode, gS_out ? gS_out + ro : nullptr,
                                          gW_out ? gW_out + ro : nullptr, l16);
         if (mode == 0 && l16 == 0) {
