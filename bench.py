@@ -27,7 +27,7 @@ import numpy as np
 import tcolgen
 
 PEAK = {"fp4": 10.1e15, "fp8": 5.0e15, "bf16": 2.5e15, "fp32": 157.3e12}
-GEMM_SRC = os.path.join(ROOT, "paper_1909_02261_amd", "csrc", "tcol_gemm.hip")
+GEMM_SRC = os.path.join(ROOT, "paper_1909_02261_amd", "csrc", "tcol_gemm_tile.h")
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "k_gemm_c5_hbm_traffic.txt")
 # penalty product: per-iteration choice (auto; the dense pass below a floor on n), dense MFMA
 # pass, sparse rows, per-iteration choice at any size

@@ -186,6 +186,10 @@ struct tcol_ctx {
     bool rows = false;              // fp32 graphs take the class-row sums (fast path, loss, conflicts)
     size_t p1_lds = 0, cr_lds = 0;  // dynamic LDS of the merged first launch and of the class-row sums
     int total_cr = 0;               // blocks of the class-row sums
+    // merged contraction with the row update: tile shape (0: none), largest k and tiles; whether
+    // every graph is updated there
+    int gr_bm = 0, gr_ntw = 0, gr_k = 0, gr_tiles = 0;
+    bool all_gfuse = false;
     int total_ps = 0;               // blocks of the sparse penalty kernel (0: no graph uses it)
     int total_rows = 0, total_mem = 0, total_mt = 0, total_ex = 0;
     int total_gm[2] = {0, 0};
@@ -348,6 +352,86 @@ static bool pick_sparse(int kmax, int dmax, int nmax, int& PM, int& threads) {
 }
 
 static int path_of(const tcol_ctx* c);
+static bool merged(const tcol_ctx* c);
+
+// Tile shapes of a merged contraction (both passes): resident blocks on the chip and time per K-vertex of a
+// full round in ns, fitted to launches of n = 200 to 4000 (single graphs, both passes)
+struct MergedShape {
+    int bm, ntw, slots;
+    double ns;
+};
+constexpr MergedShape kMergedShapes[] = {{64, 2, 768, 9.8},  {64, 4, 512, 15.0},  {64, 6, 512, 19.0},
+                                         {64, 8, 512, 24.0}, {128, 4, 512, 21.0}, {128, 6, 512, 33.0}};
+
+// Whether a graph's column tiles of bn columns hold whole members well enough to update their rows in
+// the contraction (the padding columns of a tile take their share of the matrix work)
+static bool rows_fit(const tcol_graph_params& p, int bn) { return p.k <= bn && 10 * (bn / p.k) * p.k >= 6 * bn; }
+
+// Estimated time in us of a merged iteration's contraction and row update with a shape; fuse: graphs
+// whose members fit the tiles are updated by the contraction.  Rounds of resident blocks (a last one that is
+// partly empty costs about a quarter), then either the epilogue's members one after the other at 2 us
+// each or 8 bytes per weight at 4.7 TB/s, whichever is more, or for graphs updated in their own launch 16 bytes per weight
+// and the launch.  Measured at k = 28, D = 128, n = 1000: 45.7 us with (64 x 128 tiles) against 55.6
+// without; at k = 20, D = 20, n = 200, where a tile's three members follow one another, 18.3 against 16.5.
+static double merged_cost(const tcol_ctx* c, const MergedShape& m, bool fuse, int* kf, bool* all) {
+    const int bn = gemm_bn(m.ntw);
+    double work = 0.0, nmax = 0.0, nsum = 0.0, own = 0.0, other = 0.0;
+    int serial = 0;
+    *kf = 0;
+    *all = true;
+    for (auto& p : c->params) {
+        const bool f = fuse && rows_fit(p, bn);
+        const double tiles = (double)ceil_div(p.n, m.bm) * (f ? ceil_div(p.D, bn / p.k) : ceil_div(p.D * p.k, bn));
+        const double bytes = 8.0 * p.D * (double)p.n * p.k / 4.7e6;
+        work += tiles * p.n;
+        nmax = std::max(nmax, (double)p.n);
+        nsum += p.n;
+        if (f) {
+            *kf = std::max(*kf, p.k);
+            own += bytes;
+            serial = std::max(serial, m.bm / 64 * std::min(p.D, bn / p.k));
+        } else {
+            *all = false;
+            other += 2.0 * bytes;
+        }
+    }
+    const double load = work / m.slots;   // vertices of K per resident block
+    const double k_len = load <= nmax ? nmax : load + 0.25 * nsum / c->G;
+    double cost = k_len * m.ns * 1e-3;
+    if (*kf) cost += std::max(own, 2.0 * serial * std::max(1.0, load / nmax));
+    if (!*all) cost += other + 4.0;
+    return cost;
+}
+
+// tile shape of a merged contraction, and whether it takes the row update
+static void pick_merged_shape(tcol_ctx* c) {
+    c->gr_bm = c->gr_ntw = c->gr_k = 0;
+    c->all_gfuse = false;
+    // (the batch launch, fused = 3, keeps its own tile)
+    if (c->opt.fused != 1 || !merged(c) || c->rows || common_op(c) != kPrecFP4 ||
+        (c->opt.tile_bm && c->opt.tile_ntw))
+        return;
+    double best = 1e30;
+    for (auto& m : kMergedShapes)
+        for (bool fuse : {true, false}) {
+            if (!fuse && !shape_listed(m.bm, m.ntw)) continue;
+            int kf = 0;
+            bool all = false;
+            const double cost = merged_cost(c, m, fuse, &kf, &all);
+            if (cost >= best || (fuse && (kf == 0 || !gemm_rows_built(m.bm, m.ntw, kf, c->update_var)))) continue;
+            best = cost;
+            if (fuse) {
+                c->gr_bm = m.bm;
+                c->gr_ntw = m.ntw;
+                c->gr_k = kf;
+                c->all_gfuse = all;
+            } else {
+                c->gr_bm = 0;
+                c->shape.bm = m.bm;
+                c->shape.ntw = m.ntw;
+            }
+        }
+}
 
 // The batch launch (fused = 3): whether it can run these graphs, and its item segments.  It
 // runs the fast schedule with the dense penalty pass, so no graph may take the sparse rows,
@@ -411,10 +495,8 @@ static tcol_status build_batch(tcol_ctx* c, const std::vector<int>& order) {
 // recompute flattened work offsets for the tile shapes and upload the descriptors
 static tcol_status rebuild_schedule(tcol_ctx* c) {
     pick_shapes(c);
-    HIPCHK(gemm_prepare(c->shape));
     if (c->fused_ok) HIPCHK(gemm_prepare(c->fshape));
     HIPCHK(penalty_sparse_prepare());
-    const int BN0 = gemm_bn(c->shape.ntw);
     const int BN1 = c->fused_ok ? gemm_bn(c->fshape.ntw) : 0;
     // sparse penalty: a graph takes it on request (penalty 2) or when the automatic choice
     // prefers it
@@ -467,10 +549,15 @@ static tcol_status rebuild_schedule(tcol_ctx* c) {
               class_rows_lds(c->kmax, c->nmax) <= (size_t)kMaxBlockLds;
     c->cr_lds = c->rows ? class_rows_lds(c->kmax, c->nmax) : 0;
     if (c->rows) HIPCHK(class_rows_prepare(c->kmax, c->update_var));
+    c->total_ps = ps_k > 0 ? 1 : 0;   // merged() asks whether there are any; counted below
+    pick_merged_shape(c);
+    HIPCHK(gemm_prepare(c->shape));
+    const int BN0 = gemm_bn(c->shape.ntw);
     bool stops = false;
     for (auto& p : c->params) stops = stops || p.stop_on_legal;
     c->p1_lds = phase1_lds(c->kmax, c->nmax, c->rows || (stops && update_rows_kpl(c->kmax) > 0));
     HIPCHK(phase1_prepare());
+    if (c->gr_bm) HIPCHK(gemm_rows_prepare(c->gr_bm, c->gr_ntw, c->gr_k, c->update_var));
     int rows = 0, mem = 0, pg = 0, mt = 0, ex = 0, cr = 0;
     for (int g = 0; g < c->G; ++g) {
         const tcol_graph_params& p = c->params[g];
@@ -494,6 +581,14 @@ static tcol_status rebuild_schedule(tcol_ctx* c) {
         ex += d.ex_cblocks;
         d.gm_tm[0] = ceil_div(p.n, c->shape.bm);
         d.gm_tn[0] = ceil_div(p.D * p.k, BN0);
+        d.gfuse = 0;
+        if (c->gr_bm) {
+            const int bn = gemm_bn(c->gr_ntw);
+            d.gfuse = rows_fit(p, bn) ? 1 : 0;
+            d.gr_mpb = d.gfuse ? bn / p.k : 1;
+            d.gm_tm[2] = ceil_div(p.n, c->gr_bm);
+            d.gm_tn[2] = d.gfuse ? ceil_div(p.D, d.gr_mpb) : ceil_div(p.D * p.k, bn);
+        }
         if (c->fused_ok) {
             d.gm_mpb = BN1 / p.k;
             d.gm_tm[1] = ceil_div(p.n, c->fshape.bm);
@@ -506,11 +601,15 @@ static tcol_status rebuild_schedule(tcol_ctx* c) {
     for (int g = 0; g < c->G; ++g) order[g] = g;
     std::stable_sort(order.begin(), order.end(),
                      [&](int a, int b) { return c->layouts[a].n_pad > c->layouts[b].n_pad; });
-    int gm0 = 0, gm1 = 0;
+    int gm0 = 0, gm1 = 0, gm2 = 0;
     for (int g : order) {
         GraphDev& d = c->hdesc[g];
         d.gm_begin[0] = gm0;
         gm0 += d.gm_tm[0] * d.gm_tn[0];
+        if (c->gr_bm) {
+            d.gm_begin[2] = gm2;
+            gm2 += d.gm_tm[2] * d.gm_tn[2];
+        }
         if (c->fused_ok) {
             d.gm_begin[1] = gm1;
             gm1 += d.gm_tm[1] * d.gm_tn[1];
@@ -524,6 +623,7 @@ static tcol_status rebuild_schedule(tcol_ctx* c) {
     c->total_cr = cr;
     c->total_gm[0] = gm0;
     c->total_gm[1] = gm1;
+    c->gr_tiles = gm2;
     tcol_status bs = build_batch(c, order);
     if (bs != TCOL_OK) return bs;
     HIPCHK(hipMemcpyAsync(c->ddesc, c->hdesc.data(), sizeof(GraphDev) * c->G, hipMemcpyHostToDevice, c->stream));
@@ -571,7 +671,8 @@ static hipError_t enqueue_step_plain(tcol_ctx* c, hipStream_t s) {
     return hipSuccess;
 }
 
-// one iteration of the merged schedule: two launches with the class-row sums, else three.  The
+// one iteration of the merged schedule: two launches where the sums (class rows or contraction) update
+// the rows themselves, else three.  The
 // first launch answers the stop rule, the last one ends the iteration; adv: the iteration follows
 // another of the same call
 static hipError_t enqueue_step_merged(tcol_ctx* c, bool adv, hipStream_t s) {
@@ -579,7 +680,11 @@ static hipError_t enqueue_step_merged(tcol_ctx* c, bool adv, hipStream_t s) {
     if (c->rows)
         return launch_class_rows(c->ddesc, c->G, c->total_cr, c->cr_lds, c->kmax, c->update_var, 1, 0, -1, nullptr,
                                  nullptr, s);
-    HIPRET(launch_gemm(c->shape, c->ddesc, c->G, c->total_gm[0], 1, 7 | 128, 0, s));
+    if (c->gr_bm)
+        HIPRET(launch_gemm_rows(c->gr_bm, c->gr_ntw, c->gr_k, c->update_var, c->ddesc, c->G, c->gr_tiles, s));
+    else
+        HIPRET(launch_gemm(c->shape, c->ddesc, c->G, c->total_gm[0], 1, 7 | 128, 0, s));
+    if (c->gr_bm && c->all_gfuse) return hipSuccess;
     return launch_update_rows(c->ddesc, c->G, c->total_rows, c->kmax, c->update_var, 1, 0, -1, nullptr, nullptr, 1, s);
 }
 
@@ -1007,9 +1112,13 @@ tcol_status tcol_set_options(tcol_ctx* c, const tcol_options* o) {
     if (o->penalty < 0 || o->penalty > 3) return TCOL_EINVAL;
     if (o->fused < 0 || o->fused > 3) return TCOL_EINVAL;
     if ((o->tile_bm || o->tile_ntw) && !shape_listed(o->tile_bm, o->tile_ntw)) return TCOL_EINVAL;
-    tcol_options old = c->opt;
+    tcol_options old = c->opt, shown;
+    if (tcol_get_options(c, &shown) != TCOL_OK) return TCOL_EINVAL;
     c->opt = *o;
     if (c->opt.unroll == 0) c->opt.unroll = 8;
+    // options read back (tcol_get_options names the automatic tile) and given again stay automatic
+    if (!old.tile_bm && c->opt.tile_bm == shown.tile_bm && c->opt.tile_ntw == shown.tile_ntw)
+        c->opt.tile_bm = c->opt.tile_ntw = 0;
     tcol_status s = rebuild_schedule(c);
     if (s != TCOL_OK) {
         c->opt = old;
@@ -1368,6 +1477,15 @@ tcol_status tcol_autotune(tcol_ctx* c, int32_t* best_bm, int32_t* best_ntw) {
         o.tile_bm = o.tile_ntw = 0;
         if (base.fused != 0) cands.push_back(o);
     }
+    if (base.fused != 0)
+        for (int pen : {0, 1}) {
+            // the automatic tiling, whose merged contraction may take the row update
+            tcol_options o = base;
+            o.fused = 1;
+            o.tile_bm = o.tile_ntw = 0;
+            o.penalty = pen;
+            cands.push_back(o);
+        }
     for (int path : paths)
         for (auto& sh : kShapes) {
             tcol_options o = base;

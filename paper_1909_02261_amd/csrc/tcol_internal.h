@@ -147,9 +147,10 @@ struct GraphDev {
     int mt_ts;                // tile side of the group-concentration kernel (32 or 64)
     int ex_begin;             // blocks of the S^T expansion kernel
     int ex_cblocks;           // column blocks per S^T row group
-    int gm_begin[2];          // GEMM tiles of the separate (0) and fused (1) tilings
-    int gm_tm[2], gm_tn[2];   // tiles along rows and along columns
-    int gm_mpb;               // fused tiling: members per column tile
+    int gm_begin[3];          // GEMM tiles of the separate (0), epilogue (1) and merged (2) tilings
+    int gm_tm[3], gm_tn[3];   // tiles along rows and along columns
+    int gm_mpb;               // epilogue tiling: members per column tile
+    int gfuse, gr_mpb;        // merged tiling: whole members per column tile (gr_mpb), updated by the contraction
 };
 
 // run-time flags passed to the kernels of one launch sequence

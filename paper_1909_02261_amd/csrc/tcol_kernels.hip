@@ -7,6 +7,7 @@
 // flattened work index, so one launch serves a batch of graphs of uneven sizes.
 #include "tcol_internal.h"
 #include "tcol_launch.h"
+#include "tcol_rows.h"
 
 #include <math.h>
 
@@ -22,7 +23,6 @@ __device__ inline uint16_t f32_to_bf16_rne(float x) {
     return (uint16_t)(u >> 16);
 }
 
-__device__ inline bool finite_f(float x) { return (__float_as_uint(x) & 0x7F800000u) != 0x7F800000u; }
 
 __device__ inline int graph_of_row(const GraphDev* gd, int G, int w) {
     return find_graph(gd, G, w, [](const GraphDev& x) { return x.row_begin; });
@@ -49,13 +49,6 @@ __device__ inline int equal_halves_in(uint32_t a, uint32_t b, uint32_t valid) {
     return __builtin_popcount(y & ~x & valid);
 }
 
-// global-address-space views: loads through them are not ordered against LDS
-// operations (a flat pointer may alias LDS, which pins every flat load behind
-// the LDS atomics and barriers before it)
-template <typename T>
-__device__ inline const __attribute__((address_space(1))) T* gview(const T* p) {
-    return (const __attribute__((address_space(1))) T*)p;
-}
 typedef unsigned int u32x4n __attribute__((ext_vector_type(4)));
 // order this wave's LDS accesses across lanes (LDS executes a wave's operations in issue order)
 __device__ inline void wave_sync() {
@@ -1570,35 +1563,6 @@ __global__ __launch_bounds__(256) void k_phase1(const GraphDev* __restrict__ gd,
     if (b < total_ex) expand_block(gd, G, b, honor_stop, 0, 1, adv);
 }
 
-// the stop rule's answer for the update launch of a merged iteration: uniform over the launch
-// (legal_min of this iteration is complete, and the entry cleared here is the next one's)
-__device__ __forceinline__ bool merged_stop(const GraphDev& d, const GraphState* st, long long t) {
-    return d.stop_on_legal && st->legal_min[t & 1] != 0x7FFFFFFF;
-}
-
-// End of a merged iteration, by one wave-sized group of lanes (lane of `lanes`) of the launch that
-// updates the weights: the route counters, then either the stop (lowest legal member, its colouring)
-// or t <- t + 1.  The launch's other blocks read st->tc, not t.
-__device__ __forceinline__ void merged_end(const GraphDev& d, GraphState* st, long long t, bool stop, int lane, int lanes) {
-    const int ld = stop ? st->legal_min[t & 1] : -1;
-    if (stop) {
-        const int16_t* c = d.c[st->pS] + (size_t)ld * d.cs;
-        for (int i = lane; i < d.n; i += lanes) d.snap[i] = c[i];
-    }
-    if (lane != 0) return;
-    const float tf = (float)t;
-    if (d.lambda * tf != 0.0f || d.mu * tf != 0.0f) st->it_dense += 1;
-    else st->it_nopen += 1;
-    if (stop) {
-        st->legal_d = ld;
-        st->stopped = 1;
-        return;
-    }
-    st->legal_min[(t + 1) & 1] = 0x7FFFFFFF;
-    st->t = t + 1;
-    st->steps_done += 1;
-}
-
 // ------------------------------------------------------- step 2, stop rule -----
 
 // One block per graph: f_color = f2 / 2 (f2 gathered from A.S); the main
@@ -1753,148 +1717,6 @@ __global__ __launch_bounds__(256) void k_update(const GraphDev* __restrict__ gd,
     }
 }
 
-// Step 4 with the row held in registers, one (member, vertex) row per 16-lane
-// group, k <= 16 KPL: softmax along k (max subtracted), straight-through
-// gradient gW = s^ (G - sum_l s^_l G_l), update, smoothing, and in mode 0 the
-// argmax colouring of the updated row for the next iteration (written over
-// this iteration's colours).  Mode 1 writes gS and gW instead.
-// VAR bit 0: some graph of the launch has an added fitness term (equity or colour
-// cost), bit 1: some graph takes heavy-ball steps; the plain variant carries neither
-// stream's registers.
-struct RowCtx {
-    float nut, eta, rho, gam;
-    int problem, c1, c2, k;
-    bool smooth;
-};
-
-__device__ __forceinline__ RowCtx row_ctx(const GraphDev& d, long long t) {
-    RowCtx x;
-    x.nut = prob_added(d.problem) ? d.nu * (float)t : 0.0f;
-    x.eta = d.eta;
-    x.rho = d.rho;
-    x.gam = d.momentum;
-    x.problem = d.problem;
-    x.c1 = d.c1;
-    x.c2 = d.c2;
-    x.k = d.k;
-    x.smooth = d.nb_iter > 0 && ((t + 1) % d.nb_iter) == 0;
-    return x;
-}
-
-// loads of a row's weights and, where present, class sizes and velocity (indices clamped into the row inside the last
-// group of 16 instead of per-lane branches, so they are all in flight together).  Groups of 16 past the row's end are
-// skipped whole: KPL is sized for the largest k of the launch, and a row of a graph with fewer
-// colours would otherwise issue every group's loads.
-template <int KPL, int VAR>
-struct RowRegs {
-    float wv[KPL], vv[(VAR & 2) ? KPL : 1];
-    int32_t cv[(VAR & 1) ? KPL : 1];
-};
-
-// gs: the row of G, unless null, into gv.
-template <int KPL, int VAR>
-__device__ __forceinline__ void row_load(RowRegs<KPL, VAR>& R, float (&gv)[KPL], const RowCtx& x, const float* w,
-                                         const float* gs, const int32_t* V, const float* vel, int mode, int l16) {
-    const int k = x.k;
-#pragma unroll
-    for (int q = 0; q < KPL; ++q)
-        if (16 * q < k) {
-            const int l = min(l16 + 16 * q, k - 1);
-            R.wv[q] = gview(w)[l];
-            if (gs) gv[q] = gview(gs)[l];
-        }
-    if constexpr ((VAR & 1) != 0) {
-        if (x.nut != 0.0f) {
-#pragma unroll
-            for (int q = 0; q < KPL; ++q)
-                if (16 * q < k) R.cv[q] = gview(V)[min(l16 + 16 * q, k - 1)];
-        }
-    }
-    if constexpr ((VAR & 2) != 0) {
-        if (vel && mode != 1) {
-#pragma unroll
-            for (int q = 0; q < KPL; ++q)
-                if (16 * q < k) R.vv[q] = gview(vel)[min(l16 + 16 * q, k - 1)];
-        }
-    }
-}
-
-// the row's arithmetic; gv: the lane's entries of gS without the added-fitness term.  w, vel: the row's
-// memory (written in mode 0); gS_out, gW_out: the row's outputs (mode 1).  Returns the row's next colour
-// (mode 0), or -1 where the updated row is not finite.
-template <int KPL, int VAR>
-__device__ __forceinline__ int row_step(RowRegs<KPL, VAR>& R, float (&gv)[KPL], const RowCtx& x, float* __restrict__ w,
-                                        float* __restrict__ vel, int mode, float* __restrict__ gS_out,
-                                        float* __restrict__ gW_out, int l16) {
-    constexpr bool ADD = (VAR & 1) != 0, MOM = (VAR & 2) != 0;
-    const int k = x.k;
-#pragma unroll
-    for (int q = 0; q < KPL; ++q) {
-        const int l = l16 + 16 * q;
-        if (l < k) {
-            if constexpr (ADD) {
-                if (x.nut != 0.0f) gv[q] += x.nut * added_grad(x.problem, R.cv[q], l, x.c1, x.c2);
-            }
-        } else {
-            R.wv[q] = -INFINITY;
-            gv[q] = 0.0f;
-        }
-    }
-    float mx = -INFINITY;
-#pragma unroll
-    for (int q = 0; q < KPL; ++q) mx = fmaxf(mx, R.wv[q]);
-    mx = row16_max(mx);
-    float ev[KPL];
-    float z = 0.0f, qs = 0.0f;
-#pragma unroll
-    for (int q = 0; q < KPL; ++q) {
-        ev[q] = (l16 + 16 * q < k) ? exp_soft(R.wv[q] - mx) : 0.0f;
-        z += ev[q];
-        qs += ev[q] * gv[q];
-    }
-    z = row16_sum(z);
-    qs = row16_sum(qs);
-    const float rz = 1.0f / z;
-    const float rq = qs * rz;
-    if (mode == 1) {
-#pragma unroll
-        for (int q = 0; q < KPL; ++q) {
-            const int l = l16 + 16 * q;
-            if (l < k) {
-                if (gS_out) gS_out[l] = gv[q];
-                if (gW_out) gW_out[l] = ev[q] * rz * (gv[q] - rq);
-            }
-        }
-        return 0;
-    }
-    float best = -INFINITY;
-    int bi = 0x7FFFFFFF, bad = 0;
-#pragma unroll
-    for (int q = 0; q < KPL; ++q) {
-        const int l = l16 + 16 * q;
-        if (l < k) {
-            float step = ev[q] * rz * (gv[q] - rq);
-            if constexpr (MOM) {
-                if (vel) {
-                    step = x.gam * R.vv[q] + step;  // heavy-ball velocity
-                    vel[l] = step;
-                }
-            }
-            float nw = R.wv[q] - x.eta * step;
-            if (x.smooth) nw = nw / x.rho;
-            w[l] = nw;
-            if (!finite_f(nw)) bad = 1;
-            if (nw > best) { best = nw; bi = l; }
-        }
-    }
-    // the argmax over the row: the largest value, then the lowest colour holding it
-    const int bo = f32_ord(best);
-    const int bmax = row16_max_i(bo);
-    bi = row16_min_i(bo == bmax ? bi : 0x7FFFFFFF);
-    bad = row16_max_i(bad);
-    return bad || bi >= k ? -1 : bi;
-}
-
 // merged: the row belongs to a merged iteration (its t is st->tc, the stop rule is answered by the
 // first launch, and the graph's first row also ends the iteration)
 template <int KPL, int VAR>
@@ -1908,6 +1730,8 @@ __device__ __forceinline__ void update_row(const GraphDev* __restrict__ gd, int 
     if (honor_stop && st->stopped) return;
     // the fast path's sparse graphs take their row update in the sparse-rows launch
     if (mode == 0 && d.pfuse) return;
+    // and graphs whose contraction updates its rows are done
+    if (merged && d.gfuse) return;
     const int r = row - d.row_begin;
     const long long t = merged ? st->tc : st->t;
     if (merged) {
@@ -1924,8 +1748,10 @@ __device__ __forceinline__ void update_row(const GraphDev* __restrict__ gd, int 
     int16_t* __restrict__ cnext = d.c[st->pS] + (size_t)m * d.cs;
     RowRegs<KPL, VAR> R;
     float gv[KPL];
-    row_load<KPL, VAR>(R, gv, x, w, gs, d.V[st->pS] + (size_t)m * k, vel, mode, l16);
-    const int c = row_step<KPL, VAR>(R, gv, x, w, vel, mode, gS_out ? gS_out + (size_t)r * k : nullptr,
+    RowClasses<KPL, VAR> C;
+    row_load<KPL, VAR>(R, gv, x, w, gs, vel, mode, l16);
+    classes_load<KPL, VAR>(C, x, d.V[st->pS] + (size_t)m * k, l16);
+    const int c = row_step<KPL, VAR>(R, C, gv, x, w, vel, mode, gS_out ? gS_out + (size_t)r * k : nullptr,
                                      gW_out ? gW_out + (size_t)r * k : nullptr, l16);
     if (mode == 0 && l16 == 0) {
         if (c < 0) atomicExch(&st->next_bad, 1);
@@ -2004,7 +1830,7 @@ __global__ __launch_bounds__(256) void k_class_rows(const GraphDev* __restrict__
 #pragma unroll
             for (int u = 0; u < 4; ++u)
                 if (strip * 64 + g16 + 16 * u < n)
-                    row_load<KPL, VAR>(ahead[u], none, x, d.W[0] + ro0 + (size_t)16 * u * k, nullptr, V,
+                    row_load<KPL, VAR>(ahead[u], none, x, d.W[0] + ro0 + (size_t)16 * u * k, nullptr,
                                        d.vel ? d.vel + ro0 + (size_t)16 * u * k : nullptr, mode, l16);
         }
     }
@@ -2108,6 +1934,8 @@ __global__ __launch_bounds__(256) void k_class_rows(const GraphDev* __restrict__
     }
     __syncthreads();
     // row update, 16 lanes per row
+    RowClasses<KPL, VAR> C;
+    classes_load<KPL, VAR>(C, x, V, l16);
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
         const int rr = g16 + 16 * u;
@@ -2120,13 +1948,13 @@ __global__ __launch_bounds__(256) void k_class_rows(const GraphDev* __restrict__
         if constexpr (AHEAD) {
             R = ahead[u];
         } else {
-            row_load<KPL, VAR>(R, gv, x, w, nullptr, V, vel, mode, l16);
+            row_load<KPL, VAR>(R, gv, x, w, nullptr, vel, mode, l16);
         }
 #pragma unroll
         for (int q = 0; q < KPL; ++q)
             if (16 * q < k) gv[q] = sgn * Gt[rr * KS + min(l16 + 16 * q, k - 1)];
         const size_t ro = ro0 + (size_t)16 * u * k;
-        const int c = row_step<KPL, VAR>(R, gv, x, w, vel, mode, gS_out ? gS_out + ro : nullptr,
+        const int c = row_step<KPL, VAR>(R, C, gv, x, w, vel, mode, gS_out ? gS_out + ro : nullptr,
                                          gW_out ? gW_out + ro : nullptr, l16);
         if (mode == 0 && l16 == 0) {
             if (c < 0) atomicExch(&st->next_bad, 1);

@@ -53,6 +53,12 @@ size_t phase1_lds(int kmax, int nmax, int lists);
 hipError_t phase1_prepare();
 hipError_t launch_phase1(const GraphDev* gd, int G, int total_mem, int total_mt, int total_ex, size_t lds,
                          int honor_stop, int adv, int legal, int mt_flags, int gsel, hipStream_t s);
+// contraction of a merged iteration, with the row update for graphs with gfuse (tiles: the graphs' merged
+// tilings; kmax: the largest k of the graphs with gfuse)
+bool gemm_rows_built(int bm, int ntw, int kmax, int var);
+hipError_t gemm_rows_prepare(int bm, int ntw, int kmax, int var);
+hipError_t launch_gemm_rows(int bm, int ntw, int kmax, int var, const GraphDev* gd, int G, int total_tiles,
+                            hipStream_t s);
 size_t class_rows_lds(int k, int n);
 hipError_t class_rows_prepare(int kmax, int var);
 hipError_t launch_class_rows(const GraphDev* gd, int G, int blocks, size_t lds, int kmax, int var, int honor_stop,

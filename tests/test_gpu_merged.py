@@ -142,3 +142,40 @@ def test_graph_check_over_tile_edges(n):
         A[i, j] = (1 - A[i, j]) if v is None else v
         with pytest.raises(pk.TcolError):
             make_solver([case], As=[A])
+
+
+@pytest.mark.parametrize("problem", [KCOL, ECP, BKPART])
+@pytest.mark.parametrize("n,k,D", [(1, 1, 1), (63, 32, 5), (65, 33, 4), (200, 64, 3), (300, 96, 5), (129, 97, 4), (257, 128, 3),
+                                   (520, 45, 16), (190, 256, 6), (130, 200, 9), (1025, 90, 8), (2048, 85, 3)])
+def test_contraction_with_row_update_bits(problem, n, k, D):
+    """The merged contraction whose tiles hold whole members (and, where the shape rule leaves members to the update
+    launch, that one) against the plain schedule, bit for bit, over 5 iterations from t = 203."""
+    case = GraphCase(f"gr_n{n}_k{k}_D{D}", problem, n, k, D, FP4, "gnp", 0.5, graph_seed=n, rho=10.0, lam=1e-3, mu=1e-4,
+                     nu=1e-3 if problem != KCOL else 0.0, stop_on_legal=0, momentum=0.5 if D in (5, 3) else 0.0)
+    out = []
+    for fused in (0, 1):
+        s, _ = make_solver([case], fused=fused, penalty=1)
+        s.set_t(203)
+        done, _ = s.step(5)
+        assert done == 5
+        c, f, _ = s.conflicts(0)
+        out.append((host(s.W[0]), host(c), host(f)))
+        s.close()
+    for a, b in zip(*out):
+        assert np.array_equal(a, b)
+
+
+def test_contraction_with_row_update_in_an_uneven_batch():
+    """Graphs whose members fit the column tiles beside graphs that keep the update launch, stops included."""
+    cases = [GraphCase(f"gb{i}", KCOL, n, k, 6, FP4, "gnp", p, graph_seed=i, lam=1e-3, mu=1e-4, rho=10.0,
+                       stop_on_legal=1 if i == 2 else 0)
+             for i, (n, k, p) in enumerate([(310, 90, 0.5), (90, 11, 0.1), (70, 60, 0.1), (400, 300, 0.9), (257, 128, 0.5)])]
+    out = []
+    for fused in (0, 1):
+        s, _ = make_solver(cases, fused=fused, penalty=1)
+        s.step(40)
+        out.append(([host(w) for w in s.W], [s.get_t(g) for g in range(len(cases))]))
+        s.close()
+    assert out[0][1] == out[1][1]
+    for a, b in zip(out[0][0], out[1][0]):
+        assert np.array_equal(a, b)
