@@ -186,6 +186,7 @@ struct tcol_ctx {
     bool rows = false;              // fp32 graphs take the class-row sums (fast path, loss, conflicts)
     size_t p1_lds = 0, cr_lds = 0;  // dynamic LDS of the merged first launch and of the class-row sums
     int total_cr = 0;               // blocks of the class-row sums
+    int total_cf = 0;               // blocks of the conflict counts
     // merged contraction with the row update: tile shape (0: none), largest k and tiles; whether
     // every graph is updated there
     int gr_bm = 0, gr_ntw = 0, gr_k = 0, gr_tiles = 0;
@@ -558,7 +559,7 @@ static tcol_status rebuild_schedule(tcol_ctx* c) {
     c->p1_lds = phase1_lds(c->kmax, c->nmax, c->rows || (stops && update_rows_kpl(c->kmax) > 0));
     HIPCHK(phase1_prepare());
     if (c->gr_bm) HIPCHK(gemm_rows_prepare(c->gr_bm, c->gr_ntw, c->gr_k, c->update_var));
-    int rows = 0, mem = 0, pg = 0, mt = 0, ex = 0, cr = 0;
+    int rows = 0, mem = 0, pg = 0, mt = 0, ex = 0, cr = 0, cf = 0;
     for (int g = 0; g < c->G; ++g) {
         const tcol_graph_params& p = c->params[g];
         const Layout& L = c->layouts[g];
@@ -570,6 +571,8 @@ static tcol_status rebuild_schedule(tcol_ctx* c) {
         d.rows = c->rows ? 1 : 0;
         d.cr_begin = cr;
         cr += p.D * ceil_div(p.n, 64);
+        d.cf_begin = cf;
+        cf += conflict_blocks(p.D, p.n);
         d.ps_begin = pg;
         if (d.psparse) pg += p.n;
         d.mt_begin = mt;
@@ -621,6 +624,7 @@ static tcol_status rebuild_schedule(tcol_ctx* c) {
     c->total_mt = mt;
     c->total_ex = ex;
     c->total_cr = cr;
+    c->total_cf = cf;
     c->total_gm[0] = gm0;
     c->total_gm[1] = gm1;
     c->gr_tiles = gm2;
@@ -654,9 +658,9 @@ static hipError_t launch_update_any(tcol_ctx* c, int honor, int mode, int gsel, 
 static bool merged(const tcol_ctx* c) { return path_of(c) == 1 && c->total_ps == 0; }
 
 // everything that depends only on the colours, in one launch (S^T where a contraction follows)
-static hipError_t enqueue_phase1(tcol_ctx* c, int honor, int adv, int legal, int tiles, int flags, int gsel,
-                                 bool expand, hipStream_t s) {
-    return launch_phase1(c->ddesc, c->G, c->total_mem, tiles, expand ? c->total_ex : 0, c->p1_lds, honor, adv, legal,
+static hipError_t enqueue_phase1(tcol_ctx* c, int honor, int adv, int want, int tiles, int flags, int gsel,
+                                 bool expand, hipStream_t s, bool conflicts = false) {
+    return launch_phase1(c->ddesc, c->G, c->total_mem, tiles, expand ? c->total_ex : 0, conflicts ? c->total_cf : 0, c->p1_lds, honor, adv, want,
                          flags, gsel, s);
 }
 
@@ -676,7 +680,7 @@ static hipError_t enqueue_step_plain(tcol_ctx* c, hipStream_t s) {
 // first launch answers the stop rule, the last one ends the iteration; adv: the iteration follows
 // another of the same call
 static hipError_t enqueue_step_merged(tcol_ctx* c, bool adv, hipStream_t s) {
-    HIPRET(enqueue_phase1(c, 1, adv ? 1 : 0, 1, c->total_mt, 0, -1, !c->rows, s));
+    HIPRET(enqueue_phase1(c, 1, adv ? 1 : 0, 3, c->total_mt, 0, -1, !c->rows, s));
     if (c->rows)
         return launch_class_rows(c->ddesc, c->G, c->total_cr, c->cr_lds, c->kmax, c->update_var, 1, 0, -1, nullptr,
                                  nullptr, s);
@@ -1166,30 +1170,29 @@ tcol_status tcol_step(tcol_ctx* c, int32_t max_steps, int32_t* steps_done, int32
 
 tcol_status tcol_conflicts(tcol_ctx* c, int32_t g, int16_t* colors_dev, int64_t* f_color_dev, int64_t* f_eq_dev) {
     if (!c || g < 0 || g >= c->G) return TCOL_EINVAL;
-    // steps 1-2 for all graphs of the context (cheap), reporting only
+    // colours and class sizes of all graphs of the context (cheap); the conflicts of graph g, by the
+    // contraction's gather where a vertex has several colours
     HIPCHK(launch_colors(c->ddesc, c->G, c->total_rows, 0, c->stream));
-    HIPCHK(enqueue_phase1(c, 0, 0, 0, 0, 0, -1, !c->rows, c->stream));
-    if (c->rows)
-        HIPCHK(launch_class_rows(c->ddesc, c->G, c->total_cr, c->cr_lds, c->kmax, c->update_var, 0, 2, g, nullptr,
-                                 nullptr, c->stream));
-    else
-        HIPCHK(launch_gemm(c->shape, c->ddesc, c->G, c->total_gm[0], 0, 1, 0, c->stream));
-    HIPCHK(launch_fitness(c->ddesc, c->G, 0, kFlagReport, -1, c->stream));
-    HIPCHK(launch_copy_report(c->ddesc, g, colors_dev, f_color_dev, f_eq_dev, c->stream));
+    HIPCHK(enqueue_phase1(c, 0, 0, 0, 0, 0, g, c->any_mcol, c->stream, !c->any_mcol));
+    if (c->any_mcol) HIPCHK(launch_gemm(c->shape, c->ddesc, c->G, c->total_gm[0], 0, 1, 0, c->stream));
+    HIPCHK(launch_report(c->ddesc, c->G, g, c->any_mcol ? 0 : kFlagFoldCounts, colors_dev, f_color_dev, f_eq_dev, c->stream));
     return TCOL_OK;
 }
 
 tcol_status tcol_loss_grad(tcol_ctx* c, int32_t g, double* loss_dev, float* gradS_dev, float* gradW_dev) {
     if (!c || g < 0 || g >= c->G) return TCOL_EINVAL;
     HIPCHK(launch_colors(c->ddesc, c->G, c->total_rows, 0, c->stream));
-    HIPCHK(enqueue_phase1(c, 0, 0, 0, c->total_mt, kFlagLoss | kFlagForcePen, g, !c->rows, c->stream));
-    if (c->rows)
-        HIPCHK(launch_class_rows(c->ddesc, c->G, c->total_cr, c->cr_lds, c->kmax, c->update_var, 0,
-                                 gradS_dev || gradW_dev ? 1 : 2, g, gradS_dev, gradW_dev, c->stream));
-    else
+    const bool grads = gradS_dev || gradW_dev;
+    // without gradients the conflicts are all the sums that the loss needs
+    const bool count = !grads && !c->any_mcol;
+    HIPCHK(enqueue_phase1(c, 0, 0, grads ? 2 : 0, c->total_mt, kFlagLoss | kFlagForcePen, g, !c->rows && !count, c->stream, count));
+    if (c->rows && grads)
+        HIPCHK(launch_class_rows(c->ddesc, c->G, c->total_cr, c->cr_lds, c->kmax, c->update_var, 0, 1, g, gradS_dev,
+                                 gradW_dev, c->stream));
+    else if (!count)
         HIPCHK(launch_gemm(c->shape, c->ddesc, c->G, c->total_gm[0], 0, 15, 0, c->stream));
-    HIPCHK(launch_loss(c->ddesc, c->G, g, c->layouts[g].mt_tiles, loss_dev, c->stream));
-    if (!c->rows && (gradS_dev || gradW_dev)) HIPCHK(launch_update_any(c, 0, 1, g, gradS_dev, gradW_dev, c->stream));
+    HIPCHK(launch_loss(c->ddesc, c->G, g, c->layouts[g].mt_tiles, count || c->rows ? kFlagFoldCounts : 0, loss_dev, c->stream));
+    if (!c->rows && grads) HIPCHK(launch_update_any(c, 0, 1, g, gradS_dev, gradW_dev, c->stream));
     return TCOL_OK;
 }
 
@@ -1198,7 +1201,6 @@ tcol_status tcol_class_conflicts(tcol_ctx* c, int32_t g, int32_t* C_dev) {
     if (c->params[g].problem == TCOL_MCOL) return TCOL_EINVAL;
     // colours and S of the current W, then A.S stored to G (no penalty pass, no gather)
     HIPCHK(launch_colors(c->ddesc, c->G, c->total_rows, 0, c->stream));
-    HIPCHK(launch_prep(c->ddesc, c->G, c->total_mem, c->prep_lds, 0, 0, 0, 0, 0, c->stream));
     HIPCHK(launch_expand(c->ddesc, c->G, c->total_ex, 0, 0, 0, c->stream));
     HIPCHK(launch_gemm(c->shape, c->ddesc, c->G, c->total_gm[0], 0, 1 | 4 | 16 | 128, 0, c->stream));
     HIPCHK(launch_class_conflicts(c->ddesc, g, c->params[g].D, c->params[g].k, C_dev, c->stream));
@@ -1575,17 +1577,16 @@ tcol_status noalloc_scratch(int dev, uint8_t** out) {
                     hipGetErrorString(e));
             return TCOL_EHIP;
         }
-        for (int ntw : {4, 6}) {
-            const GemmShape sh{kPrecFP4, ntw == 6 ? 128 : 64, ntw, 0};
-            if (gemm_prepare(sh) != hipSuccess) return TCOL_EHIP;
-        }
+        if (phase1_prepare() != hipSuccess) return TCOL_EHIP;
         g_scratch_ptr[dev] = p;
     }
     *out = (uint8_t*)g_scratch_ptr[dev];
     return TCOL_OK;
 }
 
-// the conflict pass's buffers inside the scratch array (A.S in fp4 operands, exact for 0/1)
+// the conflict pass's buffers inside the scratch array; `aop` and `sop` are sized as the operands of a contraction
+// were, which sets what fits (`aop` holds A's bits, `sop` the slots of
+// the conflict counts)
 struct NoAllocLayout {
     size_t desc, state, ones, aop, sop, c, V, cT, f2, fcol, feq, f, total;
     int n_pad, rows_S, cs, cTs;
@@ -1653,8 +1654,8 @@ extern "C" tcol_status tcol_conflicts_noalloc(const tcol_graph_params* p, const 
     d.c2 = (p->n % p->k == 0) ? p->n / p->k : p->n / p->k + 1;
     d.ones_dev = (const unsigned long long*)(base + L.ones + 8);
     d.W[0] = const_cast<float*>(W_dev);
-    d.Aop = base + L.aop;
-    d.Sop[0] = base + L.sop;
+    d.Ab = (const unsigned long long*)(base + L.aop);
+    d.f2p = (int32_t*)(base + L.sop);
     d.c[0] = (int16_t*)(base + L.c);
     d.V[0] = (int32_t*)(base + L.V);
     d.cT = (int16_t*)(base + L.cT);
@@ -1665,25 +1666,17 @@ extern "C" tcol_status tcol_conflicts_noalloc(const tcol_graph_params* p, const 
     d.f = (int64_t*)(base + L.f);
     d.st = (GraphState*)(base + L.state);
     const int total_rows = p->D * p->n;
-    d.ex_cblocks = expand_blocks(p->D, p->k, L.n_pad);
-    const GemmShape sh{kPrecFP4, L.n_pad >= 2048 ? 128 : 64, L.n_pad >= 2048 ? 6 : 4, 0};
-    d.gm_tm[0] = ceil_div(p->n, sh.bm);
-    d.gm_tn[0] = ceil_div(d.ncols, gemm_bn(sh.ntw));
     GraphDev* gd = (GraphDev*)(base + L.desc);
 
-    // the previous call's contents: everything from the state on starts at zero (operand
-    // padding, the slack rows of S^T, the conflict accumulators, the edge count)
-    HIPCHK(launch_zero(base + L.state, L.total - L.state, s));
-    HIPCHK(launch_put_desc(d, gd, d.st, s));
+    // what the kernels add to is cleared with the descriptor; everything else is written before it is read
+    unsigned long long* ones = (unsigned long long*)(base + L.ones + 8);
+    HIPCHK(launch_put_desc(d, gd, d.st, ones, s));
     // A is packed without its check (its flag word is ignored): the caller vouches for it
-    HIPCHK(launch_pack_graph(A_dev, p->n, L.n_pad, kPrecFP4, nullptr, nullptr, d.Aop, (int*)(base + L.ones),
-                             (unsigned long long*)(base + L.ones + 8), s));
+    HIPCHK(launch_pack_graph(A_dev, p->n, L.n_pad, kPrecFP4, nullptr, const_cast<unsigned long long*>(d.Ab), nullptr,
+                             (int*)(base + L.ones), ones, s));
     HIPCHK(launch_colors(gd, 1, total_rows, 0, s));
-    HIPCHK(launch_prep(gd, 1, p->D, prep_lds(p->k, p->n, 0), 0, 0, 0, 0, 0, s));
-    HIPCHK(launch_expand(gd, 1, d.ex_cblocks, 0, 0, 0, s));
-    HIPCHK(launch_gemm(sh, gd, 1, d.gm_tm[0] * d.gm_tn[0], 0, 1, 0, s));
-    HIPCHK(launch_fitness(gd, 1, 0, kFlagReport, -1, s));
-    HIPCHK(launch_copy_report(gd, 0, colors_dev, f_main_dev, f_sec_dev, s));
+    HIPCHK(launch_phase1(gd, 1, p->D, 0, 0, conflict_blocks(p->D, p->n), phase1_lds(p->k, p->n, 0), 0, 0, 0, 0, -1, s));
+    HIPCHK(launch_report(gd, 1, 0, kFlagFoldCounts, colors_dev, f_main_dev, f_sec_dev, s));
     return TCOL_OK;
 }
 

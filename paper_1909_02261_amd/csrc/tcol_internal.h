@@ -142,6 +142,7 @@ struct GraphDev {
     int ps_begin;             // blocks (rows) of the sparse penalty kernel
     int rows;                 // the class-row sums (k_class_rows) replace the fp32 contraction
     int cr_begin;             // blocks of the class-row kernel
+    int cf_begin;             // blocks of the conflict counts
     int mt_begin;             // tiles of the group-concentration kernel
     int mt_T;                 // tiles per side
     int mt_ts;                // tile side of the group-concentration kernel (32 or 64)
@@ -164,6 +165,7 @@ enum : int {
     kFlagPlainPen = 64,   // fitness kernel of the plain path: the penalty took the dense pass
     kFlagFoldSparse = 256,  // fitness kernel of the fast path: graphs whose iteration took the
                             // sparse rows have their f_color in the rows' slots (f2p)
+    kFlagFoldCounts = 1024, // fitness kernel: f_color of every member is in the slots (conflict counts, class-row sums)
     kFlagFlipFused = 512,   // fitness kernel of the fast path: graphs whose row update rode on the
                             // sparse-rows launch (pfuse) accept it by flipping their W and colour
                             // buffers, unless they stop

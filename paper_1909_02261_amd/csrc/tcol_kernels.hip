@@ -61,8 +61,8 @@ __device__ inline u32x4n gload16(const void* p) { return *(const __attribute__((
 // ------------------------------------------------------ validation, packing --
 
 // Checks A (n x n, row-major 0/1, symmetric, zero diagonal; unless A8 is null) and writes the
-// zero-padded byte copy A8, the bit copy Ab (each unless null) and the operand copy Aop
-// ([n_pad][n_pad]; in fp4 two entries per byte, the lower column in the low nibble, 1.0 = 0x2).
+// zero-padded byte copy A8, the bit copy Ab and the operand copy Aop (each unless null;
+// Aop [n_pad][n_pad], in fp4 two entries per byte, the lower column in the low nibble, 1.0 = 0x2).
 // One block per 64 x 64 tile: a wave reads 64 bytes of a row at a time (A's rows have any
 // alignment) and turns them into one ballot, from which every copy is written; the mirrored tile's
 // ballots go to LDS for the symmetry check.
@@ -105,6 +105,7 @@ __global__ __launch_bounds__(256) void k_pack_graph(const uint8_t* __restrict__ 
         const size_t e = (size_t)i * n_pad + j0 + lane;
         if (A8) A8[e] = a ? 1 : 0;
         if (Ab && lane == 0) Ab[(size_t)tj * n_pad + i] = m;
+        if (!Aop) continue;
         if (op == kPrecFP32) {
             ((float*)Aop)[e] = a ? 1.0f : 0.0f;
         } else if (lane < 32) {
@@ -171,9 +172,64 @@ __device__ inline void select_row(const GraphDev& d, GraphState* st, int r, cons
     }
 }
 
-// c_d(i) = argmax_l W[d,i,l], lowest l on ties; 16 lanes per row.
+// c_d(i) = argmax_l W[d,i,l], lowest l on ties; 16 lanes per row, or from 129 colours a wave per row (longer pieces of
+// a row per load: k = 211, n = 2999, D = 25 21.5 -> 18 us; k = 280,
+// n = 4000, D = 32 40 -> 28 us), four rows in flight per wave either way.
 __global__ __launch_bounds__(256) void k_colors(const GraphDev* __restrict__ gd, int G, int total_rows,
                                                 int honor_stop) {
+    {
+        // the wave's four rows, when they belong to one graph with long rows
+        const int r0 = blockIdx.x * 16 + __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)) * 4;
+        if (r0 >= total_rows) return;
+        const GraphDev& d = gd[graph_of_row(gd, G, r0)];
+        const int k = d.k, lane = threadIdx.x & 63;
+        if (d.cmax == 1 && k > 128 && r0 + 3 < d.row_begin + d.D * d.n) {
+            GraphState* st = d.st;
+            if (honor_stop && st->stopped) return;
+            const float* __restrict__ w = d.W[st->pW] + (size_t)(r0 - d.row_begin) * k;
+            int16_t* __restrict__ c = d.c[st->pS];
+            float best[4];
+            int bi[4];
+            bool bad = false;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                best[q] = -INFINITY;
+                bi[q] = 0x7FFFFFFF;
+            }
+            constexpr int U = 4;
+            for (int l0 = 0; l0 < k; l0 += 64 * U) {
+                float x[4][U];
+#pragma unroll
+                for (int u = 0; u < U; ++u)
+                    if (l0 + 64 * u < k) {
+#pragma unroll
+                        for (int q = 0; q < 4; ++q) x[q][u] = gview(w)[(size_t)q * k + min(l0 + 64 * u + lane, k - 1)];
+                    }
+#pragma unroll
+                for (int u = 0; u < U; ++u)
+                    if (l0 + 64 * u < k) {
+#pragma unroll
+                        for (int q = 0; q < 4; ++q) {
+                            if (!finite_f(x[q][u])) bad = true;
+                            if (x[q][u] > best[q]) { best[q] = x[q][u]; bi[q] = min(l0 + 64 * u + lane, k - 1); }
+                        }
+                    }
+            }
+            if (__any(bad) && lane == 0) {
+                atomicExch(&st->error, -5);
+                atomicExch(&st->stopped, 1);
+            }
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const int bo = f32_ord(best[q]);
+                const int arg = wave_min_i(bo == wave_max_i(bo) ? bi[q] : 0x7FFFFFFF);
+                const int r = r0 + q - d.row_begin, m = r / d.n;
+                // (a row of NaN has no maximum; the graph is stopped then)
+                if (lane == 0) c[(size_t)m * d.cs + (r - m * d.n)] = (int16_t)(arg < k ? arg : 0);
+            }
+            return;
+        }
+    }
     const int l16 = threadIdx.x & 15;
     const int row = blockIdx.x * 16 + (threadIdx.x >> 4);
     if (row >= total_rows) return;
@@ -186,21 +242,30 @@ __global__ __launch_bounds__(256) void k_colors(const GraphDev* __restrict__ gd,
         select_row(d, st, r, w, l16);
         return;
     }
+    // eight loads in flight per lane (indices clamped into the row: a repeated last value changes neither the
+    // maximum nor, by the strict comparison, its colour)
+    constexpr int U = 8;
+    const int k = d.k;
     float best = -INFINITY;
     int bi = 0x7FFFFFFF;
     int bad = 0;
-    for (int l = l16; l < d.k; l += 16) {
-        float x = w[l];
-        if (!finite_f(x)) bad = 1;
-        if (x > best) { best = x; bi = l; }
+    for (int l = l16; l < k; l += 16 * U) {
+        float x[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (l - l16 + 16 * u < k) x[u] = gview(w)[min(l + 16 * u, k - 1)];
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (l - l16 + 16 * u < k) {
+                if (!finite_f(x[u])) bad = 1;
+                if (x[u] > best) { best = x[u]; bi = min(l + 16 * u, k - 1); }
+            }
     }
-    for (int m = 8; m >= 1; m >>= 1) {
-        float ob = __shfl_xor(best, m, 16);
-        int oi = __shfl_xor(bi, m, 16);
-        int obad = __shfl_xor(bad, m, 16);
-        bad |= obad;
-        if (ob > best || (ob == best && oi < bi)) { best = ob; bi = oi; }
-    }
+    // the largest value of the 16 lanes, then the lowest colour holding it
+    const int bo = f32_ord(best);
+    const int bmax = row16_max_i(bo);
+    bi = row16_min_i(bo == bmax ? bi : 0x7FFFFFFF);
+    bad = row16_max_i(bad);
     if (l16 == 0) {
         if (bad || bi >= d.k) {
             bi = 0;
@@ -1101,7 +1166,7 @@ __device__ __forceinline__ void mtilde_tile(const GraphDev& d, GraphState* st, i
     uint32_t* sw = (uint32_t*)lds;      // [2][TS][kMtWords]
     double(*red)[256] = (double(*)[256])(lds + 2 * 64 * kMtWords * 4);
     const float tf = (float)st->t;
-    const bool pen = (d.lambda * tf != 0.0f) || (d.mu * tf != 0.0f);
+    const bool pen = !(flags & kFlagMtOut) && ((d.lambda * tf != 0.0f) || (d.mu * tf != 0.0f));
     const int p = st->pS;
     // upper-triangle tile (ti <= tj)
     int u = b - d.mt_begin, ti = 0, T = d.mt_T;
@@ -1179,6 +1244,28 @@ __device__ __forceinline__ void mtilde_tile(const GraphDev& d, GraphState* st, i
     for (int a = 0; a < PT; ++a)
 #pragma unroll
         for (int q = 0; q < PT; ++q) cnt[a][q] = total - cnt[a][q];
+    if (flags & kFlagMtOut) {
+        // the counts alone, through LDS, so that the tile and its mirror leave in whole rows (n = 2999, D = 25: the
+        // launch 37.7 -> 22.5 us)
+        if (!mt_out) return;
+        const int n = d.n;
+        const bool mirror = ti != tj;
+        constexpr int LT = TS + 1;
+        static_assert(TS * LT * 4 <= kMtLds, "count tile fits");
+        int* ct = (int*)lds;
+        __syncthreads();
+#pragma unroll
+        for (int a = 0; a < PT; ++a)
+#pragma unroll
+            for (int q = 0; q < PT; ++q) ct[(ty * PT + a) * LT + tx * PT + q] = cnt[a][q];
+        __syncthreads();
+        const int x = threadIdx.x & (TS - 1);
+        for (int y = threadIdx.x / TS; y < TS; y += 256 / TS) {
+            if (i0 + y < n && j0 + x < n) mt_out[(size_t)(i0 + y) * n + j0 + x] = ct[y * LT + x];
+            if (mirror && j0 + y < n && i0 + x < n) mt_out[(size_t)(j0 + y) * n + i0 + x] = ct[x * LT + y];
+        }
+        return;
+    }
     const bool mirror = ti != tj;
     double ka = 0.0, vb = 0.0;
     const bool fp32 = d.op == kPrecFP32;
@@ -1219,10 +1306,6 @@ __device__ __forceinline__ void mtilde_tile(const GraphDev& d, GraphState* st, i
                     const double wgt = mirror ? 2.0 : 1.0;
                     if (edge) ka += wgt * lut_ka[m];
                     else if (bon) vb += wgt * lut_vb[m];
-                }
-                if ((flags & kFlagMtOut) && mt_out) {
-                    mt_out[(size_t)i * n + j] = m;
-                    if (mirror) mt_out[(size_t)j * n + i] = m;
                 }
             }
             val[a][q] = v;
@@ -1338,13 +1421,13 @@ __host__ __device__ inline size_t member_lds_bytes(int k, int n) {
 }
 
 // Member `mem` of the merged first launch (one colour per vertex): class sizes and the added
-// fitness where the problem has one, the class lists in summation order for graphs on the class-row
-// sums, and, with `legal`, whether the member is legal (f = 0), so that the launch that updates the
+// fitness where the problem has one, with want & 2 the class lists in summation order for graphs on the
+// class-row sums, and with want & 1 whether the member is legal (f = 0), so that the launch that updates the
 // weights knows the stop rule's answer before it starts and no fitness launch stands between.  A
 // member is illegal as soon as one conflicting pair (partitioning: one cut edge) is found, which in
 // all but the last iterations is at once; a full scan of small classes is sum_l #V_l^2 / 2 pairs.
 __device__ __forceinline__ void member_block(const GraphDev* __restrict__ gd, int G, int mem, int honor_stop, int adv,
-                                             int legal, int* sh) {
+                                             int want, int* sh) {
     const GraphDev& d = gd[find_graph(gd, G, mem, [](const GraphDev& x) { return x.mem_begin; })];
     GraphState* st = d.st;
     // read before this launch writes the state; the write below only turns `stopped` on, exactly when
@@ -1363,8 +1446,9 @@ __device__ __forceinline__ void member_block(const GraphDev* __restrict__ gd, in
     const int k = d.k, n = d.n;
     const bool part = prob_partition(d.problem), added = prob_added(d.problem);
     // minimum sum colouring always has a colour cost, so no member is legal
-    const bool want_legal = legal && d.stop_on_legal && d.problem != kProbMSCP;
-    const bool lists = d.rows || (want_legal && !part);
+    const bool want_legal = (want & 1) && d.stop_on_legal && d.problem != kProbMSCP;
+    const bool rows = d.rows && (want & 2);
+    const bool lists = rows || (want_legal && !part);
     if (!lists && !want_legal && !added) return;
     const int16_t* __restrict__ c = d.c[st->pS] + (size_t)m * d.cs;
     int* part_sum = sh;                                       // [257]
@@ -1455,7 +1539,7 @@ __device__ __forceinline__ void member_block(const GraphDev* __restrict__ gd, in
         int acc = part_sum[tid];
         for (int l = lb; l < le; ++l) {
             offl[l] = acc;
-            if (d.rows) d.cls_off[(size_t)m * (k + 1) + l] = acc;
+            if (rows) d.cls_off[(size_t)m * (k + 1) + l] = acc;
             int q = acc;
 #pragma unroll
             for (int w = 0; w < NW; ++w) {
@@ -1465,7 +1549,7 @@ __device__ __forceinline__ void member_block(const GraphDev* __restrict__ gd, in
             }
             acc += cnt[l];
         }
-        if (tid == 0 && d.rows) d.cls_off[(size_t)m * (k + 1) + k] = n;
+        if (tid == 0 && rows) d.cls_off[(size_t)m * (k + 1) + k] = n;
         __syncthreads();
         // placement in summation order: each wave walks its positions 64 at a time; lanes of one
         // colour find their rank among the batch in the colour's batch mask, and the last of them
@@ -1496,7 +1580,7 @@ __device__ __forceinline__ void member_block(const GraphDev* __restrict__ gd, in
             wave_sync();
         }
         __syncthreads();
-        if (d.rows) {
+        if (rows) {
             int16_t* __restrict__ cv = d.cls_v + (size_t)m * d.cs;
             for (int i = tid; i < n; i += 256) cv[i] = lst[i];
         }
@@ -1540,18 +1624,81 @@ __device__ __forceinline__ void member_block(const GraphDev* __restrict__ gd, in
     }
 }
 
+// even bits of x to the low half, odd bits to the high half
+__device__ __forceinline__ uint32_t unshuffle(uint32_t x) {
+    uint32_t t = (x ^ (x >> 1)) & 0x22222222u;
+    x ^= t ^ (t << 1);
+    t = (x ^ (x >> 2)) & 0x0C0C0C0Cu;
+    x ^= t ^ (t << 2);
+    t = (x ^ (x >> 4)) & 0x00F000F0u;
+    x ^= t ^ (t << 4);
+    t = (x ^ (x >> 8)) & 0x0000FF00u;
+    return x ^ t ^ (t << 8);
+}
+
+// 2 f_color without a contraction (one colour per vertex): a block takes 64 vertices i of one member, one
+// per lane, and each of its waves a quarter of the vertices j, of which it counts the neighbours of i with i's colour.  Lane i's adjacency to 64
+// vertices is one word (A is symmetric), their colours come two to a scalar word; a pair of colours
+// takes four instructions: (c_i ^ c_j) + 0x7fff7fff sets bits 15 and 31 where they differ, the complemented adjacency
+// bits of the two vertices are shifted onto the same bits, and a masked population count adds the pairs that are no
+// conflict.  n^2 D compares, the same time for any colouring.
+// n = 2999, k = 211, D = 25: 25 us for the launch against 12 (expansion) + 38 (contraction) + 8 us; n = 1000,
+// k = 90, D = 64: 10.7 against 8.5 + 16 + 4 us.
+__device__ __forceinline__ void conflict_block(const GraphDev* __restrict__ gd, int G, int b, int gsel, int* sh) {
+    const int g = find_graph(gd, G, b, [](const GraphDev& x) { return x.cf_begin; });
+    if (gsel >= 0 && g != gsel) return;
+    const GraphDev& d = gd[g];
+    const int n = d.n;
+    const int strips = (n + 63) / 64;
+    const int loc = b - d.cf_begin;
+    const int m = loc / strips, strip = loc - m * strips;
+    const int part = (strips + 3) / 4;
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int s0 = min(strips, wave * part), s1 = min(strips, s0 + part);
+    const int lane = threadIdx.x & 63;
+    const int i = strip * 64 + lane;
+    const int16_t* __restrict__ c = d.c[d.st->pS] + (size_t)m * d.cs;
+    const uint32_t ci = (uint16_t)gview(c)[i];      // rows are padded to 64 entries
+    const uint32_t ci2 = ci | (ci << 16);
+    const unsigned long long* __restrict__ Ab = d.Ab + i;
+    const size_t n_pad = d.n_pad;
+    typedef const __attribute__((address_space(4))) uint32_t* scalar_ptr;
+    int none = 0;
+    unsigned long long a = s0 < s1 ? gview(Ab)[(size_t)s0 * n_pad] : 0ull;
+    for (int s = s0; s < s1; ++s) {
+        const unsigned long long an = s + 1 < s1 ? gview(Ab)[(size_t)(s + 1) * n_pad] : 0ull;
+        const uint32_t lo = ~unshuffle((uint32_t)a), hi = ~unshuffle((uint32_t)(a >> 32));
+        const scalar_ptr cw = (scalar_ptr)(c + 64 * s);
+#pragma unroll
+        for (int w = 0; w < 16; ++w) {
+            const uint32_t y = ((ci2 ^ cw[w]) + 0x7fff7fffu) | (lo << (15 - w));
+            const uint32_t z = ((ci2 ^ cw[16 + w]) + 0x7fff7fffu) | (hi << (15 - w));
+            none += __builtin_popcount(y & 0x80008000u);
+            none += __builtin_popcount(z & 0x80008000u);
+        }
+        a = an;
+    }
+    int f = i < n ? 64 * (s1 - s0) - none : 0;
+    for (int o = 32; o >= 1; o >>= 1) f += __shfl_xor(f, o);
+    // one add per block, spread over the member's slots (the fitness folds them): adds of every wave to the
+    // members' counters, a few cache lines, took longer than the counting
+    if (lane == 0) sh[wave] = f;
+    __syncthreads();
+    if (threadIdx.x == 0) atomicAdd(&d.f2p[(size_t)m * kF2Slots + (strip & (kF2Slots - 1))], sh[0] + sh[1] + sh[2] + sh[3]);
+}
+
 // First launch of a merged iteration: everything that depends only on the colours, in blocks of
-// three kinds: the members (class sizes, lists, legality), the group-concentration tiles with the
-// penalty operand, and the expansion of S^T.  As three launches of 4-5 us each they were most of a
+// several kinds: the members (class sizes, lists, legality), the group-concentration tiles with the
+// penalty operand, the expansion of S^T, and (where they are asked for) the conflict counts.  As three launches of 4-5 us each they were most of a
 // small graph's iteration.  t stays as it is here (the launch that updates the weights advances
 // it), so the tiles may read it; a pending non-finite update ends the graph (adv).
 __global__ __launch_bounds__(256) void k_phase1(const GraphDev* __restrict__ gd, int G, int total_mem, int total_mt,
-                                                int total_ex, int honor_stop, int adv, int legal, int mt_flags,
+                                                int total_ex, int total_cf, int honor_stop, int adv, int want, int mt_flags,
                                                 int gsel) {
     extern __shared__ __attribute__((aligned(16))) int p1_sh[];
     int b = blockIdx.x;
     if (b < total_mem) {
-        member_block(gd, G, b, honor_stop, adv, legal, p1_sh);
+        member_block(gd, G, b, honor_stop, adv, want, p1_sh);
         return;
     }
     b -= total_mem;
@@ -1560,7 +1707,12 @@ __global__ __launch_bounds__(256) void k_phase1(const GraphDev* __restrict__ gd,
         return;
     }
     b -= total_mt;
-    if (b < total_ex) expand_block(gd, G, b, honor_stop, 0, 1, adv);
+    if (b < total_ex) {
+        expand_block(gd, G, b, honor_stop, 0, 1, adv);
+        return;
+    }
+    b -= total_ex;
+    if (b < total_cf) conflict_block(gd, G, b, gsel, p1_sh);
 }
 
 // ------------------------------------------------------- step 2, stop rule -----
@@ -1578,8 +1730,8 @@ __device__ __forceinline__ void fitness_graph(const GraphDev* __restrict__ gd, i
     const bool sparse_now = d.psparse && !st->pdense && pen_active(d, st);
     const int p = st->pS;
     if (threadIdx.x == 0) best = 0x7FFFFFFF;
-    if ((flags & kFlagFoldSparse) && sparse_now) {
-        // this iteration's sparse rows gathered 2 f_color into slots: fold and clear them
+    if (((flags & kFlagFoldSparse) && sparse_now) || (flags & kFlagFoldCounts)) {
+        // the sparse rows of this iteration (or the conflict counts) gathered 2 f_color into slots: fold and clear them
         for (int m = threadIdx.x; m < d.D; m += blockDim.x) {
             int sum = 0;
             for (int sl = 0; sl < kF2Slots; ++sl) {
@@ -1783,7 +1935,7 @@ __global__ __launch_bounds__(256) void k_update_rows(const GraphDev* __restrict_
 // n = 500, k = 50, D = 64: 27 us against 44 us (contraction) + 8 us (row update); gradients at n = 1000,
 // k = 85, D = 48: 49 us against 162 + 11 us.
 //
-// mode 0: step (merged iteration); 1: gS / gW of graph gsel and 2 f_color; 2: 2 f_color alone.
+// mode 0: step (merged iteration); 1: gS / gW of graph gsel and 2 f_color.
 template <int KPL, int VAR>
 __global__ __launch_bounds__(256) void k_class_rows(const GraphDev* __restrict__ gd, int G, int total_blocks,
                                                     int honor_stop, int mode, int gsel, float* __restrict__ gS_out,
@@ -1813,7 +1965,7 @@ __global__ __launch_bounds__(256) void k_class_rows(const GraphDev* __restrict__
     int* off = (int*)(msk + n);                          // [k + 1]
     int16_t* lst = (int16_t*)(off + k + 1);              // [n]
     const float tf = (float)t;
-    const bool pen = mode == 1 || (mode == 0 && ((d.lambda * tf != 0.0f) || (d.mu * tf != 0.0f)));
+    const bool pen = mode == 1 || ((d.lambda * tf != 0.0f) || (d.mu * tf != 0.0f));
     const float sgn = prob_partition(d.problem) ? -1.0f : 1.0f;
     // the row update's rows: 16 lanes each, four rows per group of lanes; where they fit in registers
     // their loads go out now, behind the sums
@@ -1825,14 +1977,12 @@ __global__ __launch_bounds__(256) void k_class_rows(const GraphDev* __restrict__
     const size_t ro0 = ((size_t)m * n + strip * 64 + g16) * k;
     RowRegs<KPL, VAR> ahead[AHEAD ? 4 : 1];
     if constexpr (AHEAD) {
-        if (mode != 2) {
-            float none[KPL];
+        float none[KPL];
 #pragma unroll
-            for (int u = 0; u < 4; ++u)
-                if (strip * 64 + g16 + 16 * u < n)
-                    row_load<KPL, VAR>(ahead[u], none, x, d.W[0] + ro0 + (size_t)16 * u * k, nullptr,
-                                       d.vel ? d.vel + ro0 + (size_t)16 * u * k : nullptr, mode, l16);
-        }
+        for (int u = 0; u < 4; ++u)
+            if (strip * 64 + g16 + 16 * u < n)
+                row_load<KPL, VAR>(ahead[u], none, x, d.W[0] + ro0 + (size_t)16 * u * k, nullptr,
+                                   d.vel ? d.vel + ro0 + (size_t)16 * u * k : nullptr, mode, l16);
     }
     {
         const int16_t* __restrict__ cv = d.cls_v + (size_t)m * d.cs;
@@ -1894,9 +2044,8 @@ __global__ __launch_bounds__(256) void k_class_rows(const GraphDev* __restrict__
             const int i = strip * 64 + lane;
             int own = i < n ? (int)Gt[lane * KS + gview(d.c[st->pS] + (size_t)m * d.cs)[i]] : 0;
             for (int o = 32; o >= 1; o >>= 1) own += __shfl_xor(own, o);
-            if (lane == 0 && own) atomicAdd(&d.f2[m], own);
+            if (lane == 0) atomicAdd(&d.f2p[(size_t)m * kF2Slots + (strip & (kF2Slots - 1))], own);
         }
-        if (mode == 2) return;
         __syncthreads();
     }
     if (pen && p0 < p1) {
@@ -1972,11 +2121,12 @@ __global__ void k_advance(const GraphDev* __restrict__ gd, int G) {
 
 // Fitness report of every graph (one block each), then (unless out is null) graph g's FP64 loss: L = sum main fitness + nu t sum added fitness + lambda t kappa
 // - mu t varpi (kappa, varpi from the group-concentration kernel's partials).
-__global__ __launch_bounds__(256) void k_loss(const GraphDev* __restrict__ gd, int G, int g, int ntiles,
+// fold: kFlagFoldCounts where the conflicts are in the slots, else 0.
+__global__ __launch_bounds__(256) void k_loss(const GraphDev* __restrict__ gd, int G, int g, int ntiles, int fold,
                                               double* __restrict__ out) {
     __shared__ double red[4][256];
     __shared__ int best;
-    fitness_graph(gd, blockIdx.x, 0, kFlagReport, &best);
+    fitness_graph(gd, blockIdx.x, 0, kFlagReport | fold, &best);
     if ((int)blockIdx.x != g || !out) return;
     __syncthreads();
     const GraphDev& d = gd[g];
@@ -2008,21 +2158,29 @@ __global__ __launch_bounds__(256) void k_loss(const GraphDev* __restrict__ gd, i
     }
 }
 
-// copy fitness / colour outputs of one graph for tcol_conflicts
-__global__ void k_copy_report(const GraphDev* __restrict__ gd, int g, int16_t* colors, int64_t* fcol,
-                              int64_t* feq) {
+// Report of one graph for tcol_conflicts: the first block takes the fitness of every graph
+// (kFlagReport; fold as in k_loss) and copies graph g's out, the others copy its colours.
+__global__ __launch_bounds__(256) void k_report(const GraphDev* __restrict__ gd, int G, int g, int fold, int16_t* colors,
+                                                int64_t* fcol, int64_t* feq) {
+    __shared__ int best;
     const GraphDev& d = gd[g];
-    const int p = d.st->pS;
-    const size_t total = (size_t)d.D * d.n;
-    for (size_t e = (size_t)blockIdx.x * blockDim.x + threadIdx.x; e < total; e += (size_t)gridDim.x * blockDim.x) {
-        if (colors) {
-            const size_t m = e / d.n;
-            colors[e] = d.c[p][m * d.cs + (e - m * d.n)];
+    if (blockIdx.x == 0) {
+        for (int x = 0; x < G; ++x) {
+            fitness_graph(gd, x, 0, kFlagReport | fold, &best);
+            __syncthreads();
         }
-        if (e < (size_t)d.D) {
-            if (fcol) fcol[e] = d.fcol[e];
-            if (feq) feq[e] = d.feq[e];
+        for (int m = threadIdx.x; m < d.D; m += 256) {
+            if (fcol) fcol[m] = d.fcol[m];
+            if (feq) feq[m] = d.feq[m];
         }
+        return;
+    }
+    if (!colors) return;
+    const int16_t* __restrict__ c = d.c[d.st->pS];
+    const size_t total = (size_t)d.D * d.n, step = (size_t)(gridDim.x - 1) * 256;
+    for (size_t e = (size_t)(blockIdx.x - 1) * 256 + threadIdx.x; e < total; e += step) {
+        const size_t m = e / d.n;
+        colors[e] = c[m * d.cs + (e - m * d.n)];
     }
 }
 
@@ -2110,59 +2268,63 @@ __global__ __launch_bounds__(256) void k_init_weights(float* __restrict__ W, lon
 
 // ------------------------------------------------ class-conflict matrix ---------
 
-// C_d = S_d^T (A.S_d) for one graph on fp32 MFMA (16x16x4; the integer entries stay below
-// 2^24, so the FP32 accumulation is exact): the A operand is the one-hot S_d^T, made in
-// registers from the colours (row l, column i: 1 when c_d(i) = l), the B operand the
-// contraction's A.S_d from G ([D][n][k], rows i, columns l').  A block of 4 waves takes
-// member d = blockIdx.z, rows l0 .. l0 + 15 (blockIdx.y) and columns 64 blockIdx.x .. + 63,
-// one 16 x 16 tile per wave; out is [D][k][k] int32.
-typedef float f32x4k __attribute__((ext_vector_type(4)));
+// C_d = S_d^T (A.S_d) for one graph: row l of C_d is the sum of the rows of A.S_d (the contraction's G,
+// [D][n][k]) of the vertices of colour l.  A block takes 16 columns of member d and up to kCcRows
+// colours l, whose sums it holds in LDS: each 16 lanes of it read rows of G (one column per lane, eight rows in
+// flight) and add them to the row of the vertex's colour.  The integers are exact in FP32 and in
+// int32.  G is read once per kCcRows colours, so its bytes bound the kernel: n = 2999, k = 211, D = 25 196 us
+// (a product with the one-hot S_d on fp32 matrix instructions, one row tile at a time) -> 33 us.
+// out is [D][k][k] int32.
+constexpr int kCcRows = 2048, kCcThreads = 1024;
 
-__global__ __launch_bounds__(256) void k_class_conflicts(const GraphDev* __restrict__ gd, int g,
-                                                         int32_t* __restrict__ out) {
+__global__ __launch_bounds__(kCcThreads) void k_class_conflicts(const GraphDev* __restrict__ gd, int g, int row_blocks,
+                                                                int32_t* __restrict__ out) {
+    extern __shared__ __attribute__((aligned(16))) int cc_sh[];     // [rows][16]
     const GraphDev& d = gd[g];
     const int k = d.k, n = d.n;
-    const int dm = blockIdx.z;
-    const int l0 = blockIdx.y * 16;
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const int c0 = blockIdx.x * 64 + wave * 16;
-    if (c0 >= k) return;
+    const int cols = (k + 15) / 16;
+    int b = blockIdx.x;
+    const int rb = b % row_blocks;
+    b /= row_blocks;
+    const int dm = b / cols, c0 = (b - dm * cols) * 16;
+    const int l0 = rb * kCcRows, rows = min(kCcRows, k - l0);
+    const int l16 = threadIdx.x & 15, grp = threadIdx.x >> 4;
+    constexpr int NG = kCcThreads / 16, U = 8;
+    for (int e = threadIdx.x; e < rows * 16; e += kCcThreads) cc_sh[e] = 0;
+    __syncthreads();
     const int16_t* __restrict__ col = d.c[d.st->pS] + (size_t)dm * d.cs;
-    const float* __restrict__ Gd = d.G + (size_t)dm * n * k;
-    const int lrow = l0 + (lane & 15);          // A operand row (colour l)
-    const int ccol = c0 + (lane & 15);          // B operand column (colour l')
-    const int kk = lane >> 4;                   // K index within the step
-    f32x4k acc = {0.f, 0.f, 0.f, 0.f};
-    constexpr int U = 8;                        // K-steps of 4 per round of loads
-    for (int i0 = 0; i0 < n; i0 += 4 * U) {
-        float a[U], b[U];
+    const bool in = c0 + l16 < k;
+    const float* __restrict__ Gd = d.G + (size_t)dm * n * k + (in ? c0 + l16 : 0);
+    for (int i0 = grp; i0 < n; i0 += NG * U) {
+        float x[U];
+        int l[U];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            const int i = i0 + 4 * u + kk;
-            const bool in = i < n;
-            const int ci = in ? (int)gview(col)[i] : -1;
-            a[u] = ci == lrow ? 1.0f : 0.0f;
-            b[u] = (in && ccol < k) ? gview(Gd)[(size_t)i * k + ccol] : 0.0f;
+            const int i = min(i0 + NG * u, n - 1);
+            x[u] = gview(Gd)[(size_t)i * k];
+            l[u] = (int)gview(col)[i] - l0;
         }
 #pragma unroll
-        for (int u = 0; u < U; ++u) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a[u], b[u], acc, 0, 0, 0);
+        for (int u = 0; u < U; ++u)
+            if (i0 + NG * u < n && in && l[u] >= 0 && l[u] < rows) atomicAdd(&cc_sh[l[u] * 16 + l16], (int)x[u]);
     }
-    // lane holds rows 4 (lane / 16) + r, column lane mod 16 of the tile; G holds -A.S for
-    // partitioning
-    const float sg = prob_partition(d.problem) ? -1.0f : 1.0f;
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-        const int l = l0 + (lane >> 4) * 4 + r, lp = c0 + (lane & 15);
-        if (l < k && lp < k) out[((size_t)dm * k + l) * k + lp] = (int32_t)(sg * acc[r]);
-    }
+    __syncthreads();
+    // G holds -A.S for partitioning
+    const int sg = prob_partition(d.problem) ? -1 : 1;
+    if (!in) return;
+    for (int l = grp; l < rows; l += NG) out[((size_t)dm * k + l0 + l) * k + c0 + l16] = sg * cc_sh[l * 16 + l16];
 }
 
 // ------------------------------------------- descriptors from kernel arguments --
 
 // Writes one graph's descriptor and a fresh state (the values travel as kernel arguments,
 // so a captured launch carries them; no host buffer has to outlive the call).
-__global__ void k_put_desc(GraphDev d, GraphDev* __restrict__ gd, GraphState* __restrict__ st) {
-    if (blockIdx.x != 0 || threadIdx.x != 0) return;
+// The conflict counts and the number of ones of A, which the call's kernels add to, start at zero.
+__global__ void k_put_desc(GraphDev d, GraphDev* __restrict__ gd, GraphState* __restrict__ st,
+                           unsigned long long* __restrict__ ones) {
+    for (int e = threadIdx.x; e < d.D * kF2Slots; e += blockDim.x) d.f2p[e] = 0;
+    if (threadIdx.x != 0) return;
+    *ones = 0ull;
     *gd = d;
     GraphState s{};
     s.legal_d = -1;
@@ -2360,11 +2522,11 @@ hipError_t phase1_prepare() {
     return hipFuncSetAttribute((const void*)k_phase1, hipFuncAttributeMaxDynamicSharedMemorySize, kMaxBlockLds);
 }
 
-hipError_t launch_phase1(const GraphDev* gd, int G, int total_mem, int total_mt, int total_ex, size_t lds,
-                         int honor_stop, int adv, int legal, int mt_flags, int gsel, hipStream_t s) {
+hipError_t launch_phase1(const GraphDev* gd, int G, int total_mem, int total_mt, int total_ex, int total_cf, size_t lds,
+                         int honor_stop, int adv, int want, int mt_flags, int gsel, hipStream_t s) {
     if (lds > (size_t)kMaxBlockLds) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_phase1, dim3(total_mem + total_mt + total_ex), dim3(256), lds, s, gd, G, total_mem, total_mt,
-                       total_ex, honor_stop, adv, legal, mt_flags, gsel);
+    hipLaunchKernelGGL(k_phase1, dim3(total_mem + total_mt + total_ex + total_cf), dim3(256), lds, s, gd, G, total_mem,
+                       total_mt, total_ex, total_cf, honor_stop, adv, want, mt_flags, gsel);
     TCOL_LAUNCH_CHECK();
     return hipSuccess;
 }
@@ -2408,28 +2570,32 @@ hipError_t launch_advance(const GraphDev* gd, int G, hipStream_t s) {
     return hipSuccess;
 }
 
-hipError_t launch_loss(const GraphDev* gd, int G, int g, int ntiles, double* out, hipStream_t s) {
-    hipLaunchKernelGGL(k_loss, dim3(G), dim3(256), 0, s, gd, G, g, ntiles, out);
+hipError_t launch_loss(const GraphDev* gd, int G, int g, int ntiles, int fold, double* out, hipStream_t s) {
+    hipLaunchKernelGGL(k_loss, dim3(G), dim3(256), 0, s, gd, G, g, ntiles, fold, out);
     TCOL_LAUNCH_CHECK();
     return hipSuccess;
 }
 
-hipError_t launch_copy_report(const GraphDev* gd, int g, int16_t* colors, int64_t* fcol, int64_t* feq,
-                              hipStream_t s) {
-    hipLaunchKernelGGL(k_copy_report, dim3(256), dim3(256), 0, s, gd, g, colors, fcol, feq);
+hipError_t launch_report(const GraphDev* gd, int G, int g, int fold, int16_t* colors, int64_t* fcol, int64_t* feq, hipStream_t s) {
+    hipLaunchKernelGGL(k_report, dim3(257), dim3(256), 0, s, gd, G, g, fold, colors, fcol, feq);
     TCOL_LAUNCH_CHECK();
     return hipSuccess;
 }
 
 hipError_t launch_class_conflicts(const GraphDev* gd, int g, int D, int k, int32_t* out, hipStream_t s) {
     if (D <= 0 || k <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_class_conflicts, dim3(ceil_div(k, 64), ceil_div(k, 16), D), dim3(256), 0, s, gd, g, out);
+    const int rb = ceil_div(k, kCcRows);
+    const size_t lds = (size_t)std::min(k, kCcRows) * 16 * 4;
+    const hipError_t e = hipFuncSetAttribute((const void*)k_class_conflicts, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                             kMaxBlockLds);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(k_class_conflicts, dim3(D * ceil_div(k, 16) * rb), dim3(kCcThreads), lds, s, gd, g, rb, out);
     TCOL_LAUNCH_CHECK();
     return hipSuccess;
 }
 
-hipError_t launch_put_desc(const GraphDev& d, GraphDev* gd, GraphState* st, hipStream_t s) {
-    hipLaunchKernelGGL(k_put_desc, dim3(1), dim3(64), 0, s, d, gd, st);
+hipError_t launch_put_desc(const GraphDev& d, GraphDev* gd, GraphState* st, unsigned long long* ones, hipStream_t s) {
+    hipLaunchKernelGGL(k_put_desc, dim3(1), dim3(256), 0, s, d, gd, st, ones);
     TCOL_LAUNCH_CHECK();
     return hipSuccess;
 }

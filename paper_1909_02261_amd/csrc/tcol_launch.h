@@ -45,14 +45,14 @@ int update_rows_kpl(int kmax);
 // var: bit 0 some graph has an added fitness term, bit 1 some graph takes heavy-ball steps
 hipError_t launch_update_rows(const GraphDev* gd, int G, int total_rows, int kmax, int var, int honor_stop, int mode,
                               int gsel, float* gS_out, float* gW_out, int merged, hipStream_t s);
-// merged iterations: first launch (members, group-concentration tiles, expansion blocks; lists: some
+// merged iterations: first launch (members, group-concentration tiles, expansion and conflict blocks; want & 1: legality, & 2: class lists for the class-row sums; lists: some
 // graph needs its class lists), and the class-row sums with the row update (graphs with `rows`;
 // modes in k_class_rows)
 constexpr int kMaxBlockLds = 150 * 1024;
 size_t phase1_lds(int kmax, int nmax, int lists);
 hipError_t phase1_prepare();
-hipError_t launch_phase1(const GraphDev* gd, int G, int total_mem, int total_mt, int total_ex, size_t lds,
-                         int honor_stop, int adv, int legal, int mt_flags, int gsel, hipStream_t s);
+hipError_t launch_phase1(const GraphDev* gd, int G, int total_mem, int total_mt, int total_ex, int total_cf, size_t lds,
+                         int honor_stop, int adv, int want, int mt_flags, int gsel, hipStream_t s);
 // contraction of a merged iteration, with the row update for graphs with gfuse (tiles: the graphs' merged
 // tilings; kmax: the largest k of the graphs with gfuse)
 bool gemm_rows_built(int bm, int ntw, int kmax, int var);
@@ -65,16 +65,19 @@ hipError_t launch_class_rows(const GraphDev* gd, int G, int blocks, size_t lds, 
                              int mode, int gsel, float* gS_out, float* gW_out, hipStream_t s);
 hipError_t launch_advance(const GraphDev* gd, int G, hipStream_t s);
 // fitness report of every graph and, unless out is null, the loss of graph g
-hipError_t launch_loss(const GraphDev* gd, int G, int g, int ntiles, double* out, hipStream_t s);
-hipError_t launch_copy_report(const GraphDev* gd, int g, int16_t* colors, int64_t* fcol, int64_t* feq,
-                              hipStream_t s);
+hipError_t launch_loss(const GraphDev* gd, int G, int g, int ntiles, int fold, double* out, hipStream_t s);
+// fitness of every graph (report only) and graph g's results and colours out
+hipError_t launch_report(const GraphDev* gd, int G, int g, int fold, int16_t* colors, int64_t* fcol, int64_t* feq, hipStream_t s);
+// blocks of the conflict counts of a graph (64 vertices of one member each)
+inline int conflict_blocks(int D, int n) { return D * ceil_div(n, 64); }
 // graph g's selection as [d][i][s] (s < cmax), -1 past a vertex's demand
 hipError_t launch_copy_selection(const GraphDev* gd, int g, int16_t* out, hipStream_t s);
 hipError_t launch_state(const GraphDev* gd, int G, int op, int g_only, long long t, hipStream_t s);
 // class-conflict matrices S_d^T (A.S_d) of graph g ([D][k][k] int32) from G = A.S and the colours
 hipError_t launch_class_conflicts(const GraphDev* gd, int g, int D, int k, int32_t* out, hipStream_t s);
-// one graph's descriptor and a fresh state written on the device from kernel arguments
-hipError_t launch_put_desc(const GraphDev& d, GraphDev* gd, GraphState* st, hipStream_t s);
+// one graph's descriptor and a fresh state written on the device from kernel arguments, its conflict
+// counts and *ones cleared
+hipError_t launch_put_desc(const GraphDev& d, GraphDev* gd, GraphState* st, unsigned long long* ones, hipStream_t s);
 // bytes (a multiple of 16) of 16-byte aligned device memory set to zero by a kernel
 hipError_t launch_zero(void* p, size_t bytes, hipStream_t s);
 

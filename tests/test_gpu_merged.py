@@ -179,3 +179,31 @@ def test_contraction_with_row_update_in_an_uneven_batch():
     assert out[0][1] == out[1][1]
     for a, b in zip(out[0][0], out[1][0]):
         assert np.array_equal(a, b)
+
+
+@pytest.mark.parametrize("prec", [FP32, FP4])
+@pytest.mark.parametrize("n,k,D,one", [(1, 1, 1, False), (64, 2, 3, False), (65, 9, 2, False), (257, 129, 4, False), (258, 300, 3, False),
+                                       (600, 5, 2, True), (1100, 40, 67, False)])
+def test_conflict_counts_without_a_contraction(n, k, D, one, prec):
+    """tcol_conflicts, the loss without gradients and the class-conflict matrices against integers, for spread
+    colours and all vertices in one class; a row of equal weights takes its lowest colour."""
+    rng = np.random.default_rng(n)
+    cols = np.full((D, n), k - 1) if one else rng.integers(0, k, (D, n))
+    W = weights_of(cols, k)
+    W[0, 0, :] = 0.25
+    cols[0, 0] = 0
+    case = GraphCase("cf", KCOL, n, k, D, prec, "gnp", 0.5, graph_seed=n)
+    s, (A,) = make_solver([case], Ws=[W])
+    A = A.astype(np.int64)
+    f = [int((A * (cols[d][:, None] == cols[d][None, :])).sum()) // 2 for d in range(D)]
+    for _ in range(2):                                   # the counters are cleared by each call
+        c, fm, fs = s.conflicts(0)
+        assert np.array_equal(host(c), cols) and host(fm).tolist() == f and not host(fs).any()
+        loss, _, _ = s.loss_grad(0, want_gs=False, want_gw=False)
+        assert host(loss)[1] == sum(f)
+    C = host(s.class_conflicts(0))
+    for d in range(D):
+        S = np.zeros((n, k), np.int64)
+        S[np.arange(n), cols[d]] = 1
+        assert np.array_equal(C[d], S.T @ A @ S)
+    s.close()
