@@ -46,7 +46,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
     if (stop) return;
     const float tf = (float)t;
     const bool pen = (d.lambda * tf != 0.0f) || (d.mu * tf != 0.0f);
-    const float sgn = prob_partition(d.problem) ? -1.0f : 1.0f;
+    const uint32_t sign = prob_partition(d.problem) ? 0x80000000u : 0u;
     const int n = d.n, k = d.k;
     const int wm = wave >> 1, wn = wave & 1;
     const int m0 = tm * BM;
@@ -80,7 +80,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
 #pragma unroll
                     for (int r = 0; r < 4; ++r) {
                         const int row = wm * T::RW + mt * 16 + (lane >> 4) * 4 + r;
-                        if (m0 + row < n) o[(size_t)row * k] = sgn * acc[mt][nt][r];
+                        if (m0 + row < n) o[(size_t)row * k] = flip_sign(acc[mt][nt][r], sign);
                     }
             }
         }
@@ -125,7 +125,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
                 float gv[KPL];
 #pragma unroll
                 for (int q = 0; q < KPL; ++q)
-                    if (16 * q < k) gv[q] = sgn * gr[min(l16 + 16 * q, k - 1)];
+                    if (16 * q < k) gv[q] = flip_sign(gr[min(l16 + 16 * q, k - 1)], sign);
                 const int c = row_step<KPL, VAR>(Q[u], C, gv, x, W + ro + (size_t)16 * u * k,
                                                  vel ? vel + ro + (size_t)16 * u * k : nullptr, 0, nullptr, nullptr, l16);
                 if (l16 == 0) {

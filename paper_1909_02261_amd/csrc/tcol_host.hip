@@ -42,7 +42,7 @@ inline size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 
 enum Buf {
     B_LUT_PEN, B_LUT_BON, B_LUT_KA, B_LUT_VB, B_DEM, B_SEL, B_W2, B_A8, B_AB, B_AOP, B_POP, B_S0, B_S1, B_C0, B_C1,
-    B_V0, B_V1, B_G, B_F2, B_F2P, B_FCOL, B_FEQ, B_F, B_PART, B_SNAP, B_CT, B_CLSV, B_CLSOFF, B_CINFO, B_SQ, B_VEL, B_COUNT
+    B_V0, B_V1, B_G, B_F2, B_F2P, B_FCOL, B_FEQ, B_F, B_PART, B_SNAP, B_CT, B_CLSV, B_CLSOFF, B_CLSJ, B_CINFO, B_SQ, B_VEL, B_COUNT
 };
 
 struct Layout {
@@ -79,7 +79,7 @@ Layout make_layout(const tcol_graph_params& p) {
     sz[B_A8] = n2;
     sz[B_AB] = n2 / 8;
     sz[B_AOP] = (size_t)L.n_pad * op_row_bytes(op_prec(p.precision), L.n_pad);
-    sz[B_POP] = n2 * (p.precision == TCOL_FP32 ? 4 : 2);
+    sz[B_POP] = p.precision == TCOL_FP32 ? (n2 + L.n_pad) * 4 : n2 * 2;
     sz[B_S0] = sz[B_S1] = (size_t)L.rows_S * op_row_bytes(op_prec(p.precision), L.n_pad);
     sz[B_C0] = sz[B_C1] = sizeof(int16_t) * ((size_t)p.D * round_up(p.n, 64) + 64);
     sz[B_V0] = sz[B_V1] = sizeof(int32_t) * (size_t)p.D * p.k;
@@ -92,6 +92,8 @@ Layout make_layout(const tcol_graph_params& p) {
     sz[B_CT] = sizeof(int16_t) * (size_t)round_up(p.D, 8) * p.n;
     sz[B_CLSV] = sizeof(int16_t) * (size_t)p.D * round_up(p.n, 64);
     sz[B_CLSOFF] = sizeof(int32_t) * (size_t)p.D * (p.k + 1);
+    // class-row sums: classes padded to multiples of four entries, and what a scalar load reads past the end
+    sz[B_CLSJ] = p.precision == TCOL_FP32 ? sizeof(uint32_t) * ((size_t)p.D * (round_up(p.n, 64) + 4 * p.k) + 64) : 0;
     sz[B_CINFO] = 8 * (size_t)p.D * round_up(p.n, 64);
     sz[B_SQ] = sizeof(long long) * (size_t)p.D;
     sz[B_VEL] = p.momentum != 0.0f ? sizeof(float) * dnk : 0;
@@ -544,11 +546,11 @@ static tcol_status rebuild_schedule(tcol_ctx* c) {
     for (int g = 0; g < c->G; ++g)
         if (!c->hdesc[g].pfuse) c->all_pfuse = false;
     c->prep_lds = prep_lds(c->kmax, c->nmax, ps_k > 0);
-    // class-row sums: fp32 operands, one colour per vertex, a row in registers, and a block's 64
-    // gradient rows with a member's list in LDS; beyond that the fp32 contraction
+    // class-row sums: fp32 operands, one colour per vertex, a row in registers (which also keeps a block's 64
+    // gradient rows within its LDS), and P's row offsets in 32 bits; beyond that the fp32 contraction
     c->rows = common_op(c) == kPrecFP32 && !c->any_mcol && update_rows_kpl(c->kmax) > 0 &&
-              class_rows_lds(c->kmax, c->nmax) <= (size_t)kMaxBlockLds;
-    c->cr_lds = c->rows ? class_rows_lds(c->kmax, c->nmax) : 0;
+              class_rows_lds(c->kmax) <= (size_t)kMaxBlockLds && c->nmax <= 16384;
+    c->cr_lds = c->rows ? class_rows_lds(c->kmax) : 0;
     if (c->rows) HIPCHK(class_rows_prepare(c->kmax, c->update_var));
     c->total_ps = ps_k > 0 ? 1 : 0;   // merged() asks whether there are any; counted below
     pick_merged_shape(c);
@@ -680,7 +682,8 @@ static hipError_t enqueue_step_plain(tcol_ctx* c, hipStream_t s) {
 // first launch answers the stop rule, the last one ends the iteration; adv: the iteration follows
 // another of the same call
 static hipError_t enqueue_step_merged(tcol_ctx* c, bool adv, hipStream_t s) {
-    HIPRET(enqueue_phase1(c, 1, adv ? 1 : 0, 3, c->total_mt, 0, -1, !c->rows, s));
+    // the class-row sums read the adjacency from P's signs, so they need P in every iteration
+    HIPRET(enqueue_phase1(c, 1, adv ? 1 : 0, 3, c->total_mt, c->rows ? kFlagForcePen : 0, -1, !c->rows, s));
     if (c->rows)
         return launch_class_rows(c->ddesc, c->G, c->total_cr, c->cr_lds, c->kmax, c->update_var, 1, 0, -1, nullptr,
                                  nullptr, s);
@@ -1046,6 +1049,8 @@ tcol_status tcol_init(tcol_ctx** out, int32_t G, const tcol_graph_params* p, con
         d.sel = d.cmax > 1 ? (int16_t*)(b + L.off[B_SEL]) : nullptr;
         d.cls_v = (int16_t*)(b + L.off[B_CLSV]);
         d.cls_off = (int32_t*)(b + L.off[B_CLSOFF]);
+        d.cls_j = (uint32_t*)(b + L.off[B_CLSJ]);
+        d.js = round_up(q.n, 64) + 4 * q.k;
         d.cinfo = (int2*)(b + L.off[B_CINFO]);
         d.sq = (long long*)(b + L.off[B_SQ]);
         // look-up tables over the group concentration m = 0..D (host libm, FP64); for

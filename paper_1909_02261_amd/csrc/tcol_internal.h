@@ -100,7 +100,7 @@ struct GraphDev {
     const uint8_t* A8;        // [n_pad][n_pad] 0/1 bytes (zero padded)
     const unsigned long long* Ab;   // [n_pad / 64][n_pad] bit b of word (s, j): A[j][64 s + b]
     void* Aop;                // [n_pad][n_pad] A in the operand format
-    void* Pop;                // [n_pad][n_pad] penalty operand (fp32, or bf16, halved, with fp4 A and S)
+    void* Pop;                // [n_pad][n_pad] penalty operand (fp32, with a row of zeros after it, or bf16, halved, with fp4 A and S)
     void* Sop[2];             // [rows_S][n_pad] S^T in the operand format
     int16_t* c[2];            // colours [D][cs] (member-major; entries n..cs-1 unused)
     int32_t* V[2];            // class sizes [D][k]
@@ -128,7 +128,11 @@ struct GraphDev {
                               // every iteration or in those that ask for them (ps_mode); else
                               // the dense operand pass of the contraction
     int16_t* cls_v;           // [D][cs] vertices of each member grouped by colour
-    int32_t* cls_off;         // [D][k + 1] start of colour l's vertices in cls_v (last entry n)
+    int32_t* cls_off;         // [D][k + 1] start of colour l's vertices in cls_v (last entry n); for the class-row
+                              // sums the padded start in cls_j plus the number of padding entries (0-3)
+    uint32_t* cls_j;          // [D][js] class-row sums: byte offsets of the vertices' rows of Pop, grouped by colour, each
+                              // colour padded to a multiple of four with the row past the last (zero)
+    int js;
     int2* cinfo;              // [D][cs] start in cls_v and size of the class of vertex i in member d
     long long* sq;            // [D] sum over colours of the squared class sizes of each member
     int ps_mode;              // sparse penalty: 1 every iteration, 2 when the classes are small

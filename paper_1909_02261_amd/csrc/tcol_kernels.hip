@@ -1295,7 +1295,9 @@ __device__ __forceinline__ void mtilde_tile(const GraphDev& d, GraphState* st, i
 #pragma unroll
         for (int q = 0; q < PT; ++q) {
             const int j = jb + q;
-            float v = 0.0f;
+            // the sign of an fp32 entry tells edges (+) from the others (-), also where it is zero: the
+            // class-row sums count by it
+            float v = -0.0f;
             if (i < n && j < n) {
                 const int m = cnt[a][q];
                 const bool edge = ((arow >> (8 * q)) & 0xFFu) != 0;
@@ -1415,9 +1417,9 @@ __global__ __launch_bounds__(256) void k_mtilde(const GraphDev* __restrict__ gd,
 __device__ __forceinline__ int vertex_at(int q) { return (q & ~15) | ((q & 3) << 2) | ((q >> 2) & 3); }
 
 // words of the member block's dynamic LDS: scratch, counts, per-wave cursors, per-wave 64-bit batch
-// masks, class starts, then the list
+// masks, class starts, then the list (each class padded to a multiple of four entries)
 __host__ __device__ inline size_t member_lds_bytes(int k, int n) {
-    return sizeof(int) * ((size_t)kPrepScratch + 14 * (size_t)k + 2) + sizeof(int16_t) * (size_t)((n + 1) & ~1);
+    return sizeof(int) * ((size_t)kPrepScratch + 14 * (size_t)k + 2) + sizeof(int16_t) * (((size_t)n + 3 * (size_t)k + 1) & ~(size_t)1);
 }
 
 // Member `mem` of the merged first launch (one colour per vertex): class sizes and the added
@@ -1459,7 +1461,7 @@ __device__ __forceinline__ void member_block(const GraphDev* __restrict__ gd, in
     int* cw = cnt + k;                                        // [4][k]
     unsigned long long* msk = (unsigned long long*)(cw + 4 * k + (k & 1));   // [4][k] (8-byte aligned)
     int* offl = (int*)(msk + 4 * (size_t)k);                  // [k]
-    int16_t* lst = (int16_t*)(offl + k + (k & 1));            // [n]
+    int16_t* lst = (int16_t*)(offl + k + (k & 1));            // [n + 3 k at most]
     constexpr int NW = 4;
     const int wv = tid >> 6, lane = tid & 63;
     const int Q = ((n + NW - 1) / NW + 63) & ~63;             // positions per wave
@@ -1513,11 +1515,11 @@ __device__ __forceinline__ void member_block(const GraphDev* __restrict__ gd, in
         }
     }
     if (lists) {
-        // exclusive scan of the counts (as in prep_member)
+        // exclusive scan of the padded counts (as in prep_member); the padding entries are -1
         const int per = (k + 255) / 256;
         const int lb = min(k, tid * per), le = min(k, lb + per);
         int run = 0;
-        for (int l = lb; l < le; ++l) run += cnt[l];
+        for (int l = lb; l < le; ++l) run += (cnt[l] + 3) & ~3;
         part_sum[tid] = run;
         __syncthreads();
         if (tid < 64) {
@@ -1534,12 +1536,16 @@ __device__ __forceinline__ void member_block(const GraphDev* __restrict__ gd, in
             part_sum[4 * tid + 1] = ex + v0;
             part_sum[4 * tid + 2] = ex + v0 + v1;
             part_sum[4 * tid + 3] = ex + v0 + v1 + v2;
+            if (tid == 63) part_sum[256] = incl;
         }
         __syncthreads();
+        const int total = part_sum[256];
         int acc = part_sum[tid];
         for (int l = lb; l < le; ++l) {
+            const int pads = -cnt[l] & 3;
             offl[l] = acc;
-            if (rows) d.cls_off[(size_t)m * (k + 1) + l] = acc;
+            // start (a multiple of four) and padding in one word
+            if (rows) d.cls_off[(size_t)m * (k + 1) + l] = acc | pads;
             int q = acc;
 #pragma unroll
             for (int w = 0; w < NW; ++w) {
@@ -1547,9 +1553,10 @@ __device__ __forceinline__ void member_block(const GraphDev* __restrict__ gd, in
                 cw[w * k + l] = q;
                 q += x;
             }
-            acc += cnt[l];
+            for (int e = 0; e < pads; ++e) lst[q + e] = (int16_t)-1;
+            acc = q + pads;
         }
-        if (tid == 0 && rows) d.cls_off[(size_t)m * (k + 1) + k] = n;
+        if (tid == 0 && rows) d.cls_off[(size_t)m * (k + 1) + k] = total;
         __syncthreads();
         // placement in summation order: each wave walks its positions 64 at a time; lanes of one
         // colour find their rank among the batch in the colour's batch mask, and the last of them
@@ -1581,8 +1588,10 @@ __device__ __forceinline__ void member_block(const GraphDev* __restrict__ gd, in
         }
         __syncthreads();
         if (rows) {
-            int16_t* __restrict__ cv = d.cls_v + (size_t)m * d.cs;
-            for (int i = tid; i < n; i += 256) cv[i] = lst[i];
+            // the entries as byte offsets of the vertices' rows of P; padding takes the row past the last, which is zero
+            uint32_t* __restrict__ cj = d.cls_j + (size_t)m * d.js;
+            const uint32_t rb = 4u * (uint32_t)d.n_pad;
+            for (int q = tid; q < total; q += 256) cj[q] = (lst[q] < 0 ? (uint32_t)d.n_pad : (uint32_t)lst[q]) * rb;
         }
     }
     if (!want_legal) return;
@@ -1592,8 +1601,10 @@ __device__ __forceinline__ void member_block(const GraphDev* __restrict__ gd, in
         const uint8_t* __restrict__ A8 = d.A8;
         const size_t n_pad = d.n_pad;
         if (!part) {
-            for (int q = tid; q < n && !*found; q += 256) {
+            const int total = part_sum[256];
+            for (int q = tid; q < total && !*found; q += 256) {
                 const int v = lst[q];
+                if (v < 0) continue;
                 const int x = gview(c)[v];
                 const int e = offl[x] + cnt[x];
                 const uint8_t* __restrict__ row = A8 + (size_t)v * n_pad;
@@ -1925,22 +1936,27 @@ __global__ __launch_bounds__(256) void k_update_rows(const GraphDev* __restrict_
 // Steps 2-4 of a graph in fp32 operands, without a contraction: with one-hot S_d,
 //   G[d, i, l] = sum_{j in class (d, l)} (a_ij + P_ij),
 // so a wave takes 64 vertices i of member d (one per lane) and walks the member's vertices j
-// grouped by colour: A and P are symmetric, so row j of each gives its 64 entries in one load (P)
-// or one 64-bit word (A).  n^2 D additions instead of the contraction's n^2 D k multiply-adds: at
-// the 157 TFLOP/s of the fp32 matrix instructions the additions win from k of about 4 up, and the
-// walk takes the same time whatever the class sizes.  The counts come first, exactly, then the P_ij in FP32 one
-// after the other in the order of the member's list, which is the order of the fp32 contraction's
-// accumulation: the same bits.  The block's four waves share the colours by quarters of the list;
-// the 64 gradient rows meet in LDS and the same block takes the row update (or writes the gradients).
-// n = 500, k = 50, D = 64: 27 us against 44 us (contraction) + 8 us (row update); gradients at n = 1000,
-// k = 85, D = 48: 49 us against 162 + 11 us.
+// grouped by colour: P is symmetric, so row j gives its 64 entries in one load, whose sign bits are the
+// adjacency (mtilde_tile).  n^2 D additions instead of the contraction's n^2 D k multiply-adds: at
+// the 157 TFLOP/s of the fp32 matrix instructions the additions win from k of about 4 up.  The counts
+// come first, exactly, then the P_ij in FP32 one after the other in the order of the member's list, which is
+// the order of the fp32 contraction's accumulation: the same bits.  The list holds row offsets, read into scalar
+// registers, and each class is padded to a multiple of four with a row of zeros, so an entry costs one
+// load, two instructions to count and one to add; the next class is loaded while one is summed.  The block's
+// eight waves share the colours by eighths of the list; the 64 gradient rows meet in LDS and the same block takes the row
+// update (or writes the gradients).
+// n = 500, k = 50, D = 64: 16 us per launch against 44 us (contraction) + 8 us (row update) before, n = 125, k = 18,
+// D = 8 7.6 against 16 + 3.7 us; gradients at n = 1000, k = 85, D = 48 41 against 162 + 11 us.  (A first form, with the
+// adjacency from bit masks and lists in LDS, two walks and a check per entry, took 26, 10.6 and 49 us.)
 //
 // mode 0: step (merged iteration); 1: gS / gW of graph gsel and 2 f_color.
+constexpr int kCrThreads = 512;
 template <int KPL, int VAR>
-__global__ __launch_bounds__(256) void k_class_rows(const GraphDev* __restrict__ gd, int G, int total_blocks,
-                                                    int honor_stop, int mode, int gsel, float* __restrict__ gS_out,
-                                                    float* __restrict__ gW_out) {
+__global__ __launch_bounds__(kCrThreads) __attribute__((amdgpu_waves_per_eu(KPL <= 8 ? 4 : 2))) void k_class_rows(const GraphDev* __restrict__ gd, int G, int total_blocks,
+                                                           int honor_stop, int mode, int gsel, float* __restrict__ gS_out,
+                                                           float* __restrict__ gW_out) {
     extern __shared__ __attribute__((aligned(16))) uint8_t cr_sh[];
+    constexpr int NW = kCrThreads / 64;
     const int b = blockIdx.x;
     if (b >= total_blocks) return;
     const int g = find_graph(gd, G, b, [](const GraphDev& x) { return x.cr_begin; });
@@ -1949,7 +1965,8 @@ __global__ __launch_bounds__(256) void k_class_rows(const GraphDev* __restrict__
     GraphState* st = d.st;
     if (honor_stop && st->stopped) return;
     const long long t = st->tc;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     if (mode == 0) {
         const bool stop = merged_stop(d, st, t);
         if (b == d.cr_begin && tid < 64) merged_end(d, st, t, stop, tid, 64);
@@ -1958,140 +1975,151 @@ __global__ __launch_bounds__(256) void k_class_rows(const GraphDev* __restrict__
     const int n = d.n, k = d.k, D = d.D;
     const int loc = b - d.cr_begin;
     const int strip = loc / D, m = loc - strip * D;      // the members of a strip are neighbours: they share P's columns in L2
-    const size_t n_pad = d.n_pad;
     const int KS = k | 1;                                // odd row stride: the lanes of a column on different banks
-    float* Gt = (float*)cr_sh;                           // [64][KS]
-    unsigned long long* msk = (unsigned long long*)(cr_sh + ((size_t)64 * KS * 4 + 15) / 16 * 16);   // [n]
-    int* off = (int*)(msk + n);                          // [k + 1]
-    int16_t* lst = (int16_t*)(off + k + 1);              // [n]
+    int* fsum = (int*)cr_sh;                             // [NW]
+    float* Gt = (float*)(cr_sh + 64);                    // [64][KS]
     const float tf = (float)t;
     const bool pen = mode == 1 || ((d.lambda * tf != 0.0f) || (d.mu * tf != 0.0f));
-    const float sgn = prob_partition(d.problem) ? -1.0f : 1.0f;
-    // the row update's rows: 16 lanes each, four rows per group of lanes; where they fit in registers
+    const uint32_t sign = prob_partition(d.problem) ? 0x80000000u : 0u;
+    // the row update's rows: 16 lanes each, two rows per group of lanes; where they fit in registers
     // their loads go out now, behind the sums
-    constexpr bool AHEAD = KPL <= 4;
+    constexpr bool AHEAD = KPL <= 4 && VAR == 0;
     const RowCtx x = row_ctx(d, t);
     const int l16 = tid & 15, g16 = tid >> 4;
+    constexpr int NG = kCrThreads / 16, NR = 64 / NG;
     const int32_t* V = d.V[st->pS] + (size_t)m * k;
     int16_t* __restrict__ cnext = d.c[st->pS] + (size_t)m * d.cs;
     const size_t ro0 = ((size_t)m * n + strip * 64 + g16) * k;
-    RowRegs<KPL, VAR> ahead[AHEAD ? 4 : 1];
+    RowRegs<KPL, VAR> ahead[AHEAD ? NR : 1];
     if constexpr (AHEAD) {
         float none[KPL];
 #pragma unroll
-        for (int u = 0; u < 4; ++u)
-            if (strip * 64 + g16 + 16 * u < n)
-                row_load<KPL, VAR>(ahead[u], none, x, d.W[0] + ro0 + (size_t)16 * u * k, nullptr,
-                                   d.vel ? d.vel + ro0 + (size_t)16 * u * k : nullptr, mode, l16);
+        for (int u = 0; u < NR; ++u)
+            if (strip * 64 + g16 + NG * u < n)
+                row_load<KPL, VAR>(ahead[u], none, x, d.W[0] + ro0 + (size_t)NG * u * k, nullptr,
+                                   d.vel ? d.vel + ro0 + (size_t)NG * u * k : nullptr, mode, l16);
     }
-    {
-        const int16_t* __restrict__ cv = d.cls_v + (size_t)m * d.cs;
-        const unsigned long long* __restrict__ Ab = d.Ab + (size_t)strip * n_pad;
-        for (int q = tid; q < n; q += 256) {
-            const int j = gview(cv)[q];
-            lst[q] = (int16_t)j;
-            msk[q] = gview(Ab)[j];
-        }
-        const int32_t* __restrict__ co = d.cls_off + (size_t)m * (k + 1);
-        for (int l = tid; l <= k; l += 256) off[l] = gview(co)[l];
-    }
-    __syncthreads();
-    // this wave's colours: those whose list starts in its quarter
+    // the member's list (scalar loads: written by the launch before)
+    typedef const __attribute__((address_space(4))) uint32_t* scalar_ptr;
+    const int32_t* __restrict__ co = d.cls_off + (size_t)m * (k + 1);
+    const scalar_ptr off = (scalar_ptr)co;
+    const scalar_ptr lst = (scalar_ptr)(d.cls_j + (size_t)m * d.js);
+    const char* __restrict__ Pc = (const char*)d.Pop + (size_t)strip * 256;
+    // this wave's colours: those whose list starts in its eighth
     int l0 = 0, l1 = 0;
-    for (int lb = 0; lb < k; lb += 64) {
-        const int l = lb + lane;
-        const long long o = l < k ? 4LL * off[l] : (long long)1 << 40;
-        l0 += __popcll(__ballot(o < (long long)wave * n));
-        l1 += __popcll(__ballot(o < (long long)(wave + 1) * n));
-    }
-    if (wave == 3) l1 = k;      // and the empty classes at the end
-    l0 = __builtin_amdgcn_readfirstlane(l0);
-    l1 = __builtin_amdgcn_readfirstlane(l1);
-    const int p0 = __builtin_amdgcn_readfirstlane(off[l0]);
-    const int p1 = __builtin_amdgcn_readfirstlane(off[l1]);
-    float* __restrict__ Gl = Gt + lane * KS;
-    // the neighbours of vertex i (the lane) in each class
     {
-        int l = l0, pe = __builtin_amdgcn_readfirstlane(off[l0 < k ? l0 + 1 : l0]);
-        int c = 0;
-        for (int q0 = p0; q0 < p1; q0 += 64) {
-            const unsigned long long mv = q0 + lane < p1 ? msk[q0 + lane] : 0ull;
-            const int lo = (int)(uint32_t)mv, hi = (int)(uint32_t)(mv >> 32);
-            const int nn = min(64, p1 - q0);
-#pragma unroll 8
-            for (int u = 0; u < nn; ++u) {
-                while (q0 + u == pe) {
-                    Gl[l] = (float)c;
-                    c = 0;
-                    ++l;
-                    pe = __builtin_amdgcn_readfirstlane(off[l + 1]);
-                }
-                const unsigned long long mm = (unsigned long long)(uint32_t)__builtin_amdgcn_readlane(lo, u) |
-                                              ((unsigned long long)(uint32_t)__builtin_amdgcn_readlane(hi, u) << 32);
-                c += __builtin_amdgcn_inverse_ballot_w64(mm) ? 1 : 0;
+        const long long T = off[k];
+        for (int lb = 0; lb < k; lb += 64) {
+            const int l = lb + lane;
+            const long long o = l < k ? (long long)NW * (gview(co)[l] & ~3) : (long long)1 << 40;
+            l0 += __popcll(__ballot(o < wave * T));
+            l1 += __popcll(__ballot(o < (wave + 1) * T));
+        }
+        if (wave == NW - 1) l1 = k;      // and the empty classes at the end
+        l0 = __builtin_amdgcn_readfirstlane(l0);
+        l1 = __builtin_amdgcn_readfirstlane(l1);
+    }
+    const int i = strip * 64 + lane;
+    const int own_c = mode != 0 && i < n ? (int)gview(cnext)[i] : -1;
+    int own = 0;
+    float* __restrict__ Gl = Gt + lane * KS;
+    // up to 16 entries of the list, in groups of four: loads, count of edges (entries whose sign is clear), sum in
+    // order
+    auto load = [&](float (&v)[16], int p, int ng) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+            if (q < ng) {
+#pragma unroll
+                for (int u = 0; u < 4; ++u) v[4 * q + u] = gview((const float*)(Pc + lst[p + 4 * q + u]))[lane];
+            }
+    };
+    auto edges = [&](const float (&v)[16], int ng, int c) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+            if (q < ng) {
+#pragma unroll
+                for (int u = 0; u < 4; ++u) c += __float_as_int(v[4 * q + u]) >= 0 ? 1 : 0;
+            }
+        return c;
+    };
+    auto add = [&](const float (&v)[16], int ng, float acc) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+            if (q < ng) {
+#pragma unroll
+                for (int u = 0; u < 4; ++u) acc += v[4 * q + u];
+            }
+        return acc;
+    };
+    // class l in v (its first 16 entries), entries [p, e), of which the last `pads` are padding (counted as edges
+    // by their sign, so taken off)
+    auto finish = [&](float (&v)[16], int l, int p, int e, int pads) {
+        int c = edges(v, min(4, (e - p) >> 2), -pads);
+        if (e - p <= 16) {
+            if (mode != 0 && own_c == l) own = c;
+            Gl[l] = pen ? add(v, (e - p) >> 2, (float)c) : (float)c;
+            return;
+        }
+        // a large class: both walks two pieces deep
+        float w[16];
+        for (int q = p + 16; q < e; q += 32) {
+            load(v, q, min(4, (e - q) >> 2));
+            const int n2 = q + 16 < e ? min(4, (e - q - 16) >> 2) : 0;
+            load(w, q + 16, n2);
+            c = edges(v, min(4, (e - q) >> 2), c);
+            c = edges(w, n2, c);
+        }
+        if (mode != 0 && own_c == l) own = c;
+        float acc = (float)c;
+        if (pen) {
+            load(v, p, 4);
+            for (int q = p; q < e; q += 32) {
+                const int n2 = q + 16 < e ? min(4, (e - q - 16) >> 2) : 0;
+                load(w, q + 16, n2);
+                acc = add(v, min(4, (e - q) >> 2), acc);
+                if (q + 32 < e) load(v, q + 32, min(4, (e - q - 32) >> 2));
+                acc = add(w, n2, acc);
             }
         }
-        // the last class with a vertex, then empty ones
-        for (; l < l1; ++l) {
-            Gl[l] = (float)c;
-            c = 0;
+        Gl[l] = acc;
+    };
+    if (l0 < l1) {
+        float va[16], vb[16];
+        int ra = (int)off[l0], rb = (int)off[l0 + 1];
+        load(va, ra & ~3, min(4, ((rb & ~3) - (ra & ~3)) >> 2));
+        for (int l = l0; l < l1; l += 2) {
+            const int rc = l + 1 < l1 ? (int)off[l + 2] : rb;
+            if (l + 1 < l1) load(vb, rb & ~3, min(4, ((rc & ~3) - (rb & ~3)) >> 2));
+            finish(va, l, ra & ~3, rb & ~3, ra & 3);
+            if (l + 1 >= l1) break;
+            const int rd = l + 2 < l1 ? (int)off[l + 3] : rc;
+            if (l + 2 < l1) load(va, rc & ~3, min(4, ((rd & ~3) - (rc & ~3)) >> 2));
+            finish(vb, l + 1, rb & ~3, rc & ~3, rb & 3);
+            ra = rc;
+            rb = rd;
         }
     }
     if (mode != 0) {
         // 2 f_color: the counts at the vertices' own colours
-        __syncthreads();
-        if (wave == 0) {
-            const int i = strip * 64 + lane;
-            int own = i < n ? (int)Gt[lane * KS + gview(d.c[st->pS] + (size_t)m * d.cs)[i]] : 0;
-            for (int o = 32; o >= 1; o >>= 1) own += __shfl_xor(own, o);
-            if (lane == 0) atomicAdd(&d.f2p[(size_t)m * kF2Slots + (strip & (kF2Slots - 1))], own);
-        }
-        __syncthreads();
-    }
-    if (pen && p0 < p1) {
-        constexpr int U = 16;       // loads in flight per lane
-        const float* __restrict__ Pc = (const float*)d.Pop + (size_t)strip * 64 + lane;
-        int l = l0, pe = __builtin_amdgcn_readfirstlane(off[l0 + 1]);
-        while (pe == p0) pe = __builtin_amdgcn_readfirstlane(off[++l + 1]);
-        float acc = Gl[l];
-        float v[U];
-        auto fetch = [&](int q0) {
-            const int jl = lst[min(q0 + (lane & (U - 1)), p1 - 1)];
-#pragma unroll
-            for (int u = 0; u < U; ++u)
-                v[u] = gview(Pc)[(size_t)(uint32_t)__builtin_amdgcn_readlane(jl, u) * n_pad];
-        };
-        fetch(p0);
-        for (int q0 = p0; q0 < p1; q0 += U) {
-            float x[U];
-#pragma unroll
-            for (int u = 0; u < U; ++u) x[u] = v[u];
-            if (q0 + U < p1) fetch(q0 + U);
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-                if (q0 + u < p1) {
-                    if (q0 + u == pe) {
-                        Gl[l] = acc;
-                        do { pe = __builtin_amdgcn_readfirstlane(off[++l + 1]); } while (pe == q0 + u);
-                        acc = Gl[l];
-                    }
-                    acc += x[u];
-                }
-            }
-        }
-        Gl[l] = acc;
+        for (int o = 32; o >= 1; o >>= 1) own += __shfl_xor(own, o);
+        if (lane == 0) fsum[wave] = own;
     }
     __syncthreads();
+    if (mode != 0 && tid == 0) {
+        int f = 0;
+        for (int w = 0; w < NW; ++w) f += fsum[w];
+        atomicAdd(&d.f2p[(size_t)m * kF2Slots + (strip & (kF2Slots - 1))], f);
+    }
     // row update, 16 lanes per row
     RowClasses<KPL, VAR> C;
     classes_load<KPL, VAR>(C, x, V, l16);
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
-        const int rr = g16 + 16 * u;
-        const int i = strip * 64 + rr;
-        if (i >= n) break;
-        float* w = d.W[0] + ro0 + (size_t)16 * u * k;
-        float* vel = d.vel ? d.vel + ro0 + (size_t)16 * u * k : nullptr;
+    for (int u = 0; u < NR; ++u) {
+        const int rr = g16 + NG * u;
+        const int iv = strip * 64 + rr;
+        if (iv >= n) break;
+        float* w = d.W[0] + ro0 + (size_t)NG * u * k;
+        float* vel = d.vel ? d.vel + ro0 + (size_t)NG * u * k : nullptr;
         RowRegs<KPL, VAR> R;
         float gv[KPL];
         if constexpr (AHEAD) {
@@ -2101,13 +2129,13 @@ __global__ __launch_bounds__(256) void k_class_rows(const GraphDev* __restrict__
         }
 #pragma unroll
         for (int q = 0; q < KPL; ++q)
-            if (16 * q < k) gv[q] = sgn * Gt[rr * KS + min(l16 + 16 * q, k - 1)];
-        const size_t ro = ro0 + (size_t)16 * u * k;
+            if (16 * q < k) gv[q] = flip_sign(Gt[rr * KS + min(l16 + 16 * q, k - 1)], sign);
+        const size_t ro = ro0 + (size_t)NG * u * k;
         const int c = row_step<KPL, VAR>(R, C, gv, x, w, vel, mode, gS_out ? gS_out + ro : nullptr,
                                          gW_out ? gW_out + ro : nullptr, l16);
         if (mode == 0 && l16 == 0) {
             if (c < 0) atomicExch(&st->next_bad, 1);
-            cnext[i] = (int16_t)max(c, 0);
+            cnext[iv] = (int16_t)max(c, 0);
         }
     }
 }
@@ -2531,9 +2559,7 @@ hipError_t launch_phase1(const GraphDev* gd, int G, int total_mem, int total_mt,
     return hipSuccess;
 }
 
-size_t class_rows_lds(int k, int n) {
-    return ((size_t)64 * (k | 1) * 4 + 15) / 16 * 16 + 8 * (size_t)n + 4 * ((size_t)k + 1) + 2 * (size_t)((n + 1) & ~1);
-}
+size_t class_rows_lds(int k) { return 64 + ((size_t)64 * (k | 1) * 4 + 15) / 16 * 16; }
 
 #define TCOL_CR_KPL(X, V) X(2, V) X(4, V) X(6, V) X(8, V) X(12, V) X(18, V) X(24, V) X(36, V)
 
@@ -2554,7 +2580,7 @@ hipError_t launch_class_rows(const GraphDev* gd, int G, int blocks, size_t lds, 
     bool done = false;
 #define TCOL_CR_LAUNCH(KP, VR)                                                                                 \
     if (!done && update_rows_kpl(kmax) == KP && var == VR) {                                                   \
-        k_class_rows<KP, VR><<<blocks, 256, lds, s>>>(gd, G, blocks, honor_stop, mode, gsel, gS_out, gW_out);  \
+        k_class_rows<KP, VR><<<blocks, kCrThreads, lds, s>>>(gd, G, blocks, honor_stop, mode, gsel, gS_out, gW_out);  \
         done = true;                                                                                           \
     }
     TCOL_CR_KPL(TCOL_CR_LAUNCH, 0) TCOL_CR_KPL(TCOL_CR_LAUNCH, 1) TCOL_CR_KPL(TCOL_CR_LAUNCH, 2) TCOL_CR_KPL(TCOL_CR_LAUNCH, 3)

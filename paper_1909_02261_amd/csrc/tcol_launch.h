@@ -59,7 +59,7 @@ bool gemm_rows_built(int bm, int ntw, int kmax, int var);
 hipError_t gemm_rows_prepare(int bm, int ntw, int kmax, int var);
 hipError_t launch_gemm_rows(int bm, int ntw, int kmax, int var, const GraphDev* gd, int G, int total_tiles,
                             hipStream_t s);
-size_t class_rows_lds(int k, int n);
+size_t class_rows_lds(int k);
 hipError_t class_rows_prepare(int kmax, int var);
 hipError_t launch_class_rows(const GraphDev* gd, int G, int blocks, size_t lds, int kmax, int var, int honor_stop,
                              int mode, int gsel, float* gS_out, float* gW_out, hipStream_t s);

@@ -18,6 +18,10 @@ template <typename T>
 __device__ inline const __attribute__((address_space(1))) T* gview(const T* p) {
     return (const __attribute__((address_space(1))) T*)p;
 }
+// x with the sign bits of `sign` flipped in.  Not a product with +-1: the compiler could contract that, and not
+// the added fitness term's product, with the addition that follows in row_step, and change its rounding
+__device__ __forceinline__ float flip_sign(float x, uint32_t sign) { return __uint_as_float(__float_as_uint(x) ^ sign); }
+
 // the stop rule's answer for the update launch of a merged iteration: uniform over the launch
 // (legal_min of this iteration is complete, and the entry cleared here is the next one's)
 __device__ __forceinline__ bool merged_stop(const GraphDev& d, const GraphState* st, long long t) {
@@ -138,7 +142,8 @@ __device__ __forceinline__ int row_step(RowRegs<KPL, VAR>& R, const RowClasses<K
         const int l = l16 + 16 * q;
         if (l < k) {
             if constexpr (ADD) {
-                if (x.nut != 0.0f) gv[q] += x.nut * added_grad(x.problem, C.cv[q], l, x.c1, x.c2);
+                // one rounding, by name: contracted or not, the rows of a block must not differ
+                if (x.nut != 0.0f) gv[q] = __builtin_fmaf(x.nut, added_grad(x.problem, C.cv[q], l, x.c1, x.c2), gv[q]);
             }
         } else {
             R.wv[q] = -INFINITY;

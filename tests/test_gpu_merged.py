@@ -144,7 +144,7 @@ def test_graph_check_over_tile_edges(n):
             make_solver([case], As=[A])
 
 
-@pytest.mark.parametrize("problem", [KCOL, ECP, BKPART])
+@pytest.mark.parametrize("problem", [KCOL, ECP, BKPART, MSCP])
 @pytest.mark.parametrize("n,k,D", [(1, 1, 1), (63, 32, 5), (65, 33, 4), (200, 64, 3), (300, 96, 5), (129, 97, 4), (257, 128, 3),
                                    (520, 45, 16), (190, 256, 6), (130, 200, 9), (1025, 90, 8), (2048, 85, 3)])
 def test_contraction_with_row_update_bits(problem, n, k, D):
