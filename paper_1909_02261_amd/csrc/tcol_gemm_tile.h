@@ -463,14 +463,6 @@ __device__ __forceinline__ void pen_sweep(f32x4 (&acc)[tile_mt(BM)][NTW], const 
     }
 }
 
-// XCD-aware order: hardware deals block b to XCD b mod 8, so give each XCD a
-// contiguous range of tiles (neighbouring tiles share operand panels in its L2)
-__device__ inline int xcd_remap(int b, int nb) {
-    const int q = nb >> 3, r = nb & 7;
-    const int x = b & 7, i = b >> 3;
-    return x * q + min(x, r) + i;
-}
-
 // Block -> tile of a batch of graphs (G > 1): the tiles, in decreasing cost, are dealt to the
 // XCDs in chunks of 16 consecutive tiles (in the main 4 row tiles by 4 column tiles of one graph), so every
 // XCD starts on the longest tiles and the short ones fill the end; a single graph keeps

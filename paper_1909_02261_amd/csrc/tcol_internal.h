@@ -142,6 +142,8 @@ struct GraphDev {
                               // A.S counts of its sparse iterations are stored as uint16 in G
     // flattened work offsets (prefix sums over graphs)
     int row_begin;            // rows (d, i) for row kernels
+    int ur_begin, ur_rows;    // merged update launch: the graph's rows (none where the contraction updates them), graphs
+                              // of few colours first
     int mem_begin;            // members d for per-member kernels
     int ps_begin;             // blocks (rows) of the sparse penalty kernel
     int rows;                 // the class-row sums (k_class_rows) replace the fp32 contraction
@@ -253,6 +255,14 @@ __device__ __forceinline__ float wave_sum(float v) {
     return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 63));
 }
 __device__ __forceinline__ float wave_max(float v) { return f32_from_ord(wave_max_i(f32_ord(v))); }
+
+// XCD-aware order: hardware deals block b to XCD b mod 8, so give each XCD a
+// contiguous range of tiles (neighbouring tiles share operand panels in its L2)
+__device__ inline int xcd_remap(int b, int nb) {
+    const int q = nb >> 3, r = nb & 7;
+    const int x = b & 7, i = b >> 3;
+    return x * q + min(x, r) + i;
+}
 
 // find the graph that owns flattened work item `w` given a begin offset per graph
 template <typename F>

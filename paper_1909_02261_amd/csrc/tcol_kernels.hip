@@ -1886,16 +1886,19 @@ template <int KPL, int VAR>
 __device__ __forceinline__ void update_row(const GraphDev* __restrict__ gd, int G, int row, int honor_stop, int mode,
                                            int gsel, float* __restrict__ gS_out, float* __restrict__ gW_out, int merged) {
     const int l16 = threadIdx.x & 15;
-    const int g = graph_of_row(gd, G, row);
+    int g = 0;
+    if (merged) {
+        while (g + 1 < G && (row < gd[g].ur_begin || row >= gd[g].ur_begin + gd[g].ur_rows)) ++g;
+    } else {
+        g = graph_of_row(gd, G, row);
+    }
     if (gsel >= 0 && g != gsel) return;
     const GraphDev& d = gd[g];
     GraphState* st = d.st;
     if (honor_stop && st->stopped) return;
     // the fast path's sparse graphs take their row update in the sparse-rows launch
     if (mode == 0 && d.pfuse) return;
-    // and graphs whose contraction updates its rows are done
-    if (merged && d.gfuse) return;
-    const int r = row - d.row_begin;
+    const int r = row - (merged ? d.ur_begin : d.row_begin);
     const long long t = merged ? st->tc : st->t;
     if (merged) {
         const bool stop = merged_stop(d, st, t);
@@ -1923,11 +1926,11 @@ __device__ __forceinline__ void update_row(const GraphDev* __restrict__ gd, int 
 }
 
 template <int KPL, int VAR>
-__global__ __launch_bounds__(256) void k_update_rows(const GraphDev* __restrict__ gd, int G, int total_rows,
+__global__ __launch_bounds__(256) void k_update_rows(const GraphDev* __restrict__ gd, int G, int row0, int total_rows,
                                                      int honor_stop, int mode, int gsel, float* __restrict__ gS_out,
                                                      float* __restrict__ gW_out, int merged) {
-    const int row = blockIdx.x * 16 + (threadIdx.x >> 4);
-    if (row >= total_rows) return;
+    const int row = row0 + blockIdx.x * 16 + (threadIdx.x >> 4);
+    if (row >= row0 + total_rows) return;
     update_row<KPL, VAR>(gd, G, row, honor_stop, mode, gsel, gS_out, gW_out, merged);
 }
 
@@ -1957,8 +1960,10 @@ __global__ __launch_bounds__(kCrThreads) __attribute__((amdgpu_waves_per_eu(KPL 
                                                            float* __restrict__ gW_out) {
     extern __shared__ __attribute__((aligned(16))) uint8_t cr_sh[];
     constexpr int NW = kCrThreads / 64;
-    const int b = blockIdx.x;
-    if (b >= total_blocks) return;
+    if ((int)blockIdx.x >= total_blocks) return;
+    // where P is larger than an XCD's L2 each XCD takes a contiguous range of strips (n = 1000, D = 48: 41 -> 36.5 us;
+    // at n = 500 the hardware's order is 3 % faster)
+    const int b = G == 1 && gd[0].n_pad >= 1024 ? xcd_remap(blockIdx.x, total_blocks) : (int)blockIdx.x;
     const int g = find_graph(gd, G, b, [](const GraphDev& x) { return x.cr_begin; });
     if (gsel >= 0 && g != gsel) return;
     const GraphDev& d = gd[g];
@@ -2507,20 +2512,20 @@ int update_rows_kpl(int kmax) {
     return 0;
 }
 
-hipError_t launch_update_rows(const GraphDev* gd, int G, int total_rows, int kmax, int var, int honor_stop, int mode,
+hipError_t launch_update_rows(const GraphDev* gd, int G, int row0, int total_rows, int kmax, int var, int honor_stop, int mode,
                               int gsel, float* gS_out, float* gW_out, int merged, hipStream_t s) {
     if (total_rows <= 0) return hipSuccess;
     if (var < 0 || var > 3) return hipErrorInvalidValue;
     const dim3 grid(ceil_div(total_rows, 16)), blk(256);
 #define TCOL_UR(KP)                                                                                                  \
     switch (var) {                                                                                                   \
-        case 0: hipLaunchKernelGGL((k_update_rows<KP, 0>), grid, blk, 0, s, gd, G, total_rows, honor_stop, mode, gsel, \
+        case 0: hipLaunchKernelGGL((k_update_rows<KP, 0>), grid, blk, 0, s, gd, G, row0, total_rows, honor_stop, mode, gsel, \
                                    gS_out, gW_out, merged); break;                                                           \
-        case 1: hipLaunchKernelGGL((k_update_rows<KP, 1>), grid, blk, 0, s, gd, G, total_rows, honor_stop, mode, gsel, \
+        case 1: hipLaunchKernelGGL((k_update_rows<KP, 1>), grid, blk, 0, s, gd, G, row0, total_rows, honor_stop, mode, gsel, \
                                    gS_out, gW_out, merged); break;                                                           \
-        case 2: hipLaunchKernelGGL((k_update_rows<KP, 2>), grid, blk, 0, s, gd, G, total_rows, honor_stop, mode, gsel, \
+        case 2: hipLaunchKernelGGL((k_update_rows<KP, 2>), grid, blk, 0, s, gd, G, row0, total_rows, honor_stop, mode, gsel, \
                                    gS_out, gW_out, merged); break;                                                           \
-        default: hipLaunchKernelGGL((k_update_rows<KP, 3>), grid, blk, 0, s, gd, G, total_rows, honor_stop, mode, gsel, \
+        default: hipLaunchKernelGGL((k_update_rows<KP, 3>), grid, blk, 0, s, gd, G, row0, total_rows, honor_stop, mode, gsel, \
                                     gS_out, gW_out, merged); break;                                                          \
     }
     switch (update_rows_kpl(kmax)) {
