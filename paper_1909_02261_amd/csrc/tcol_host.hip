@@ -689,7 +689,7 @@ static hipError_t enqueue_phase1(tcol_ctx* c, int honor, int adv, int want, int 
 // one Algorithm-1 iteration for every running graph (plain path)
 static hipError_t enqueue_step_plain(tcol_ctx* c, hipStream_t s) {
     HIPRET(launch_colors(c->ddesc, c->G, c->total_rows, 1, s));
-    HIPRET(enqueue_phase1(c, 1, 0, 0, c->total_mt, 0, -1, true, s));
+    HIPRET(enqueue_phase1(c, 1, 0, 4, c->total_mt, 0, -1, true, s));
     HIPRET(launch_gemm(c->shape, c->ddesc, c->G, c->total_gm[0], 1, 15, 0, s));
     HIPRET(launch_fitness(c->ddesc, c->G, 1, kFlagPlainPen, -1, s));
     HIPRET(launch_update_any(c, 1, 0, -1, nullptr, nullptr, s));
@@ -697,13 +697,22 @@ static hipError_t enqueue_step_plain(tcol_ctx* c, hipStream_t s) {
     return hipSuccess;
 }
 
+// row updates of a merged iteration, graphs of few and of many colours
+static hipError_t enqueue_merged_updates(tcol_ctx* c, hipStream_t s) {
+    for (int u = 0, row0 = 0; u < 2; row0 += c->ur_rows[u++])
+        if (c->ur_rows[u])
+            HIPRET(launch_update_rows(c->ddesc, c->G, row0, c->ur_rows[u], c->ur_k[u], c->update_var, 1, 0, -1, nullptr,
+                                      nullptr, 1, s));
+    return hipSuccess;
+}
+
 // one iteration of the merged schedule: two launches where the sums (class rows or contraction) update
 // the rows themselves, else three.  The
-// first launch answers the stop rule, the last one ends the iteration; adv: the iteration follows
-// another of the same call
-static hipError_t enqueue_step_merged(tcol_ctx* c, bool adv, hipStream_t s) {
+// first launch answers the stop rule and ends a graph whose last update was not finite, the last one ends
+// the iteration
+static hipError_t enqueue_step_merged(tcol_ctx* c, hipStream_t s) {
     // the class-row sums read the adjacency from P's signs, so they need P in every iteration
-    HIPRET(enqueue_phase1(c, 1, adv ? 1 : 0, 3, c->total_mt, c->rows ? kFlagForcePen : 0, -1, !c->rows, s));
+    HIPRET(enqueue_phase1(c, 1, 1, 3, c->total_mt, c->rows ? kFlagForcePen : 0, -1, !c->rows, s));
     if (c->rows)
         return launch_class_rows(c->ddesc, c->G, c->total_cr, c->cr_lds, c->kmax, c->update_var, 1, 0, -1, nullptr,
                                  nullptr, s);
@@ -711,11 +720,21 @@ static hipError_t enqueue_step_merged(tcol_ctx* c, bool adv, hipStream_t s) {
         HIPRET(launch_gemm_rows(c->gr_bm, c->gr_ntw, c->gr_k, c->update_var, c->ddesc, c->G, c->gr_tiles, s));
     else
         HIPRET(launch_gemm(c->shape, c->ddesc, c->G, c->total_gm[0], 1, 7 | 128, 0, s));
-    for (int u = 0, row0 = 0; u < 2; row0 += c->ur_rows[u++])
-        if (c->ur_rows[u])
-            HIPRET(launch_update_rows(c->ddesc, c->G, row0, c->ur_rows[u], c->ur_k[u], c->update_var, 1, 0, -1, nullptr,
-                                      nullptr, 1, s));
-    return hipSuccess;
+    return enqueue_merged_updates(c, s);
+}
+
+// the plain path's merged form, for contexts with multicolouring graphs: the update selects the next
+// colours from the rows in its registers and ends the iteration, so three launches stand for six
+// (n = 403, k = 96, D = 20, three colours, a step: 44 -> 31 us).  The stop rule of a multicolouring graph needs the
+// contraction's gather; the update launch reads its counters.
+static bool merged_mcol(const tcol_ctx* c) { return c->any_mcol && c->opt.fused >= 1 && update_rows_kpl(c->kmax) > 0; }
+
+static hipError_t enqueue_step_mcol(tcol_ctx* c, hipStream_t s) {
+    bool stops = false;
+    for (auto& d : c->hdesc) stops = stops || (d.stop_on_legal && d.cmax > 1);
+    HIPRET(enqueue_phase1(c, 1, 1, 1 | 4, c->total_mt, 0, -1, true, s));
+    HIPRET(launch_gemm(c->shape, c->ddesc, c->G, c->total_gm[0], 1, stops ? 15 : 15 | 128, 0, s));
+    return enqueue_merged_updates(c, s);
 }
 
 // penalty of the fast and epilogue paths: sparse penalty rows or the dense operand, per
@@ -795,8 +814,8 @@ static hipError_t enqueue_batch(tcol_ctx* c, int n, hipStream_t s) {
 static hipError_t enqueue_steps(tcol_ctx* c, int n, hipStream_t s) {
     const int path = path_of(c);
     if (path == 3) return enqueue_batch(c, n, s);
-    if (merged(c)) {
-        for (int i = 0; i < n; ++i) HIPRET(enqueue_step_merged(c, i > 0, s));
+    if (merged(c) || merged_mcol(c)) {
+        for (int i = 0; i < n; ++i) HIPRET(merged(c) ? enqueue_step_merged(c, s) : enqueue_step_mcol(c, s));
         return hipSuccess;
     }
     for (int i = 0; i < n; ++i)
@@ -833,7 +852,7 @@ static tcol_status run_steps(tcol_ctx* c, int steps) {
     // the batch launch's abort flag holds for the whole call
     if (path_of(c) == 3) HIPCHK(launch_zero(c->dctl, 4 * sizeof(int), c->stream));
     // the fast and epilogue paths colour the updated rows themselves: one argmax pass first
-    if (path_of(c) != 0) HIPCHK(launch_colors(c->ddesc, c->G, c->total_rows, 1, c->stream));
+    if (path_of(c) != 0 || merged_mcol(c)) HIPCHK(launch_colors(c->ddesc, c->G, c->total_rows, 1, c->stream));
     if (c->opt.use_graph) {
         const int U = std::max(1, std::min(64, c->opt.unroll));
         if (c->graph_unroll != U || !c->gexec[0] || c->graph_fused != path_of(c)) {
@@ -1201,7 +1220,7 @@ tcol_status tcol_conflicts(tcol_ctx* c, int32_t g, int16_t* colors_dev, int64_t*
     // colours and class sizes of all graphs of the context (cheap); the conflicts of graph g, by the
     // contraction's gather where a vertex has several colours
     HIPCHK(launch_colors(c->ddesc, c->G, c->total_rows, 0, c->stream));
-    HIPCHK(enqueue_phase1(c, 0, 0, 0, 0, 0, g, c->any_mcol, c->stream, !c->any_mcol));
+    HIPCHK(enqueue_phase1(c, 0, 0, c->any_mcol ? 4 : 0, 0, 0, g, c->any_mcol, c->stream, !c->any_mcol));
     if (c->any_mcol) HIPCHK(launch_gemm(c->shape, c->ddesc, c->G, c->total_gm[0], 0, 1, 0, c->stream));
     HIPCHK(launch_report(c->ddesc, c->G, g, c->any_mcol ? 0 : kFlagFoldCounts, colors_dev, f_color_dev, f_eq_dev, c->stream));
     return TCOL_OK;
@@ -1213,7 +1232,7 @@ tcol_status tcol_loss_grad(tcol_ctx* c, int32_t g, double* loss_dev, float* grad
     const bool grads = gradS_dev || gradW_dev;
     // without gradients the conflicts are all the sums that the loss needs
     const bool count = !grads && !c->any_mcol;
-    HIPCHK(enqueue_phase1(c, 0, 0, grads ? 2 : 0, c->total_mt, kFlagLoss | kFlagForcePen, g, !c->rows && !count, c->stream, count));
+    HIPCHK(enqueue_phase1(c, 0, 0, (grads ? 2 : 0) | 4, c->total_mt, kFlagLoss | kFlagForcePen, g, !c->rows && !count, c->stream, count));
     if (c->rows && grads)
         HIPCHK(launch_class_rows(c->ddesc, c->G, c->total_cr, c->cr_lds, c->kmax, c->update_var, 0, 1, g, gradS_dev,
                                  gradW_dev, c->stream));
@@ -1320,6 +1339,7 @@ tcol_status tcol_profile(tcol_ctx* c, int32_t steps, int32_t as_only, float* ms)
     // the batch launch's phases are timed as the fast schedule's kernels
     const int path = path_of(c) == 3 ? 1 : path_of(c);
     HIPCHK(launch_state(c->ddesc, c->G, 0, -1, 0, s));
+    HIPCHK(launch_state(c->ddesc, c->G, 4, -1, 0, s));
     if (path != 0) HIPCHK(launch_colors(c->ddesc, c->G, c->total_rows, 1, s));
     for (int it = 0; it < steps; ++it) {
         HIPCHK(hipEventRecord(ev[0], s));

@@ -221,7 +221,7 @@ __global__ __launch_bounds__(256) void k_colors(const GraphDev* __restrict__ gd,
             }
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
-                const int bo = f32_ord(best[q]);
+                const int bo = f32_ord(best[q] + 0.0f);
                 const int arg = wave_min_i(bo == wave_max_i(bo) ? bi[q] : 0x7FFFFFFF);
                 const int r = r0 + q - d.row_begin, m = r / d.n;
                 // (a row of NaN has no maximum; the graph is stopped then)
@@ -262,7 +262,8 @@ __global__ __launch_bounds__(256) void k_colors(const GraphDev* __restrict__ gd,
             }
     }
     // the largest value of the 16 lanes, then the lowest colour holding it
-    const int bo = f32_ord(best);
+    // (adding zero makes -0 and 0 tie across lanes as they compare)
+    const int bo = f32_ord(best + 0.0f);
     const int bmax = row16_max_i(bo);
     bi = row16_min_i(bo == bmax ? bi : 0x7FFFFFFF);
     bad = row16_max_i(bad);
@@ -1424,7 +1425,7 @@ __host__ __device__ inline size_t member_lds_bytes(int k, int n) {
 
 // Member `mem` of the merged first launch (one colour per vertex): class sizes and the added
 // fitness where the problem has one, with want & 2 the class lists in summation order for graphs on the
-// class-row sums, and with want & 1 whether the member is legal (f = 0), so that the launch that updates the
+// class-row sums, with want & 4 its conflict counter cleared, and with want & 1 whether the member is legal (f = 0), so that the launch that updates the
 // weights knows the stop rule's answer before it starts and no fitness launch stands between.  A
 // member is illegal as soon as one conflicting pair (partitioning: one cut edge) is found, which in
 // all but the last iterations is at once; a full scan of small classes is sum_l #V_l^2 / 2 pairs.
@@ -1443,8 +1444,10 @@ __device__ __forceinline__ void member_block(const GraphDev* __restrict__ gd, in
         }
         st->tc = st->t;
     }
-    if (stop_now || d.cmax > 1) return;
     const int m = mem - d.mem_begin;
+    // a gather follows: its counters start at zero
+    if ((want & 4) && !stop_now && tid == 0) d.f2[m] = 0;
+    if (stop_now || d.cmax > 1) return;
     const int k = d.k, n = d.n;
     const bool part = prob_partition(d.problem), added = prob_added(d.problem);
     // minimum sum colouring always has a colour cost, so no member is legal
@@ -1901,7 +1904,16 @@ __device__ __forceinline__ void update_row(const GraphDev* __restrict__ gd, int 
     const int r = row - (merged ? d.ur_begin : d.row_begin);
     const long long t = merged ? st->tc : st->t;
     if (merged) {
-        const bool stop = merged_stop(d, st, t);
+        bool stop;
+        if (d.cmax > 1) {
+            // the contraction's gather has counted the conflicts
+            int legal = 0;
+            if (d.stop_on_legal)
+                for (int x = l16; x < d.D; x += 16) legal |= d.f2[x] == 0;
+            stop = row16_max_i(legal) != 0;
+        } else {
+            stop = merged_stop(d, st, t);
+        }
         if (r == 0) merged_end(d, st, t, stop, l16, 16);
         if (stop) return;
     }
@@ -1919,6 +1931,10 @@ __device__ __forceinline__ void update_row(const GraphDev* __restrict__ gd, int 
     classes_load<KPL, VAR>(C, x, d.V[st->pS] + (size_t)m * k, l16);
     const int c = row_step<KPL, VAR>(R, C, gv, x, w, vel, mode, gS_out ? gS_out + (size_t)r * k : nullptr,
                                      gW_out ? gW_out + (size_t)r * k : nullptr, l16);
+    if (mode == 0 && merged && d.cmax > 1 && c >= 0) {
+        row_select<KPL>(d, R.wv, m, i, l16, cnext);
+        return;
+    }
     if (mode == 0 && l16 == 0) {
         if (c < 0) atomicExch(&st->next_bad, 1);
         cnext[i] = (int16_t)max(c, 0);

@@ -32,8 +32,15 @@ __device__ __forceinline__ bool merged_stop(const GraphDev& d, const GraphState*
 // updates the weights: the route counters, then either the stop (lowest legal member, its colouring)
 // or t <- t + 1.  The launch's other blocks read st->tc, not t.
 __device__ __forceinline__ void merged_end(const GraphDev& d, GraphState* st, long long t, bool stop, int lane, int lanes) {
-    const int ld = stop ? st->legal_min[t & 1] : -1;
-    if (stop) {
+    int ld = stop && d.cmax == 1 ? st->legal_min[t & 1] : -1;
+    if (stop && d.cmax > 1) {
+        // multicolouring: the lowest member without conflicts, and its selection as [i][s]
+        while (d.f2[++ld] != 0) {}
+        for (int e = lane; e < d.n * d.cmax; e += lanes) {
+            const int i = e / d.cmax, sl = e - i * d.cmax;
+            d.snap[e] = d.sel[((size_t)ld * d.cmax + sl) * d.cs + i];
+        }
+    } else if (stop) {
         const int16_t* c = d.c[st->pS] + (size_t)ld * d.cs;
         for (int i = lane; i < d.n; i += lanes) d.snap[i] = c[i];
     }
@@ -129,7 +136,7 @@ __device__ __forceinline__ void row_load(RowRegs<KPL, VAR>& R, float (&gv)[KPL],
 
 // the row's arithmetic; gv: the lane's entries of gS without the added-fitness term.  w, vel: the row's
 // memory (written in mode 0); gS_out, gW_out: the row's outputs (mode 1).  Returns the row's next colour
-// (mode 0), or -1 where the updated row is not finite.
+// (mode 0), or -1 where the updated row is not finite; the updated weights stay in R.wv.
 template <int KPL, int VAR>
 __device__ __forceinline__ int row_step(RowRegs<KPL, VAR>& R, const RowClasses<KPL, VAR>& C, float (&gv)[KPL],
                                         const RowCtx& x, float* __restrict__ w,
@@ -193,6 +200,7 @@ __device__ __forceinline__ int row_step(RowRegs<KPL, VAR>& R, const RowClasses<K
             float nw = R.wv[q] - x.eta * step;
             if (x.smooth) nw = nw / x.rho;
             w[l] = nw;
+            R.wv[q] = nw;
             if (!finite_f(nw)) bad = 1;
             if (nw > best) { best = nw; bi = l; }
         }
@@ -203,6 +211,34 @@ __device__ __forceinline__ int row_step(RowRegs<KPL, VAR>& R, const RowClasses<K
     bi = row16_min_i(bo == bmax ? bi : 0x7FFFFFFF);
     bad = row16_max_i(bad);
     return bad || bi >= k ? -1 : bi;
+}
+
+// Multicolouring: the row's demand of colours from its updated weights (-INFINITY past k) in registers, as the colour
+// kernel's selection: one after the other the largest weight not yet taken, the lowest colour on ties (adding zero makes
+// -0 and 0 tie as they compare).  Slots past the demand take -1; slot 0 is also the vertex's colour.
+template <int KPL>
+__device__ __forceinline__ void row_select(const GraphDev& d, const float (&wv)[KPL], int m, int i, int l16, int16_t* c) {
+    const int k = d.k, CM = d.cmax, ci = d.dem[i];
+    unsigned long long taken = 0;
+    for (int sl = 0; sl < CM; ++sl) {
+        float best = -INFINITY;
+        int bi = 0x7FFFFFFF;
+#pragma unroll
+        for (int q = 0; q < KPL; ++q)
+            if (l16 + 16 * q < k && !((taken >> q) & 1ull) && wv[q] > best) {
+                best = wv[q];
+                bi = l16 + 16 * q;
+            }
+        const int bo = f32_ord(best + 0.0f);
+        const int bmax = row16_max_i(bo);
+        bi = row16_min_i(bo == bmax ? bi : 0x7FFFFFFF);
+        const int pick = (sl < ci && bi < k) ? bi : -1;
+        if (pick >= 0 && (pick & 15) == l16) taken |= 1ull << (pick >> 4);
+        if (l16 == 0) {
+            d.sel[((size_t)m * CM + sl) * d.cs + i] = (int16_t)pick;
+            if (sl == 0) c[i] = (int16_t)pick;
+        }
+    }
 }
 
 }  // namespace tcol

@@ -9,7 +9,7 @@ import numpy as np
 import pytest
 
 import tcolgen
-from tcolgen import BKPART, ECP, FP4, FP32, KCOL, KPART, MSCP, GraphCase
+from tcolgen import BF16, BKPART, ECP, FP4, FP32, KCOL, KPART, MSCP, GraphCase
 
 from gpu_util import host, make_solver, torch_mod
 
@@ -207,3 +207,59 @@ def test_conflict_counts_without_a_contraction(n, k, D, one, prec):
         S[np.arange(n), cols[d]] = 1
         assert np.array_equal(C[d], S.T @ A @ S)
     s.close()
+
+
+@pytest.mark.parametrize("prec", [FP32, BF16])
+@pytest.mark.parametrize("n,k,D,cm,stop", [(31, 5, 1, 2, 0), (130, 17, 4, 3, 0), (70, 200, 3, 8, 0), (5, 5, 3, 2, 1), (90, 96, 5, 2, 1)])
+def test_multicolouring_merged_steps_equal_the_plain_schedule(n, k, D, cm, stop, prec):
+    """The update that selects the next colours and ends the iteration against the plain schedule (fused = 0): weights,
+    selections, counts and stops, bit for bit, over two calls of 7 iterations."""
+    import paper_1909_02261_amd as pk
+    torch = torch_mod()
+    rng = np.random.default_rng(k)
+    A = np.triu(rng.random((n, n)) < (0.5 if not stop else 0.05), 1)
+    A = (A | A.T).astype(np.uint8)
+    if n == 5:
+        A = np.zeros((5, 5), np.uint8)
+        for i in range(5):
+            A[i, (i + 1) % 5] = A[(i + 1) % 5, i] = 1
+    W = rng.normal(0.0, 0.01, (D, n, k)).astype(np.float32)
+    W[0, 0, :] = -0.0
+    W[0, 0, k // 2] = 0.0                                # -0 and 0 tie: the lowest colours
+    dem = rng.integers(1, cm + 1, n)
+    out = []
+    for fused in (0, 1):
+        p = pk.Params(n=n, k=k, D=D, problem=pk.MCOL, precision=prec, lam=1e-3, mu=1e-4, rho=10.0, max_demand=cm,
+                      stop_on_legal=stop)
+        s = pk.Solver([(torch.from_numpy(A).cuda(), torch.from_numpy(W.copy()).cuda())], [p])
+        s.set_options(fused=fused)
+        s.set_demand(dem)
+        s.set_t(40)
+        sel0 = host(s.selection(0))
+        res = [s.step(7), s.step(7)]
+        c, f, _ = s.conflicts(0)
+        out.append((host(s.W[0]), host(s.selection(0)), host(c), host(f), np.array([res[0][0], res[1][0], s.get_t()]),
+                    np.array(res[0][1] + res[1][1]), host(s.loss_grad(0)[0])))
+        assert sel0[0, 0, 0] == 0
+        s.close()
+    for a, b in zip(*out):
+        assert np.array_equal(a, b)
+
+
+@pytest.mark.parametrize("prec", [FP32, FP4])
+def test_merged_non_finite_update_ends_the_run_there(prec):
+    """An update that overflows (at t = 0, in the first of nine iterations, over several replays) stops the graph with an
+    error before the next iteration, as the plain schedule does: the same weights and t."""
+    import paper_1909_02261_amd as pk
+    case = GraphCase("bad", KCOL, 70, 5, 2, prec, "gnp", 0.5, graph_seed=1, stop_on_legal=0)
+    W = case.weights()
+    W[1, 3, :] = [3e38, 3e38, 3e38, 3.0e38, -3e38]
+    case.eta = 3e38
+    out = []
+    for fused in (0, 1):
+        s, _ = make_solver([case], Ws=[W], fused=fused, unroll=4)
+        with pytest.raises(pk.TcolError):
+            s.step(9)
+        out.append((s.get_t(), host(s.W[0]).tobytes()))
+        s.close()
+    assert out[0] == out[1]
