@@ -43,7 +43,8 @@ hipError_t launch_update(const GraphDev* gd, int G, int total_rows, int honor_st
 // register-resident row update for k <= 576 (update_rows_kpl(kmax) != 0); mode 0 also colours the new rows
 int update_rows_kpl(int kmax);
 // rows row0 .. row0 + total_rows - 1 of the flattened order (merged: that of the merged update launch)
-// var: bit 0 some graph has an added fitness term, bit 1 some graph takes heavy-ball steps
+// var: bit 0 some graph has an added fitness term, bit 1 some graph takes heavy-ball steps,
+// bit 2 some graph is a multicolouring
 hipError_t launch_update_rows(const GraphDev* gd, int G, int row0, int total_rows, int kmax, int var, int honor_stop, int mode,
                               int gsel, float* gS_out, float* gW_out, int merged, hipStream_t s);
 // merged iterations: first launch (members, group-concentration tiles, expansion and conflict blocks; want & 1: legality, & 2: class lists for the class-row sums,

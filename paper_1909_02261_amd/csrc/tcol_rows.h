@@ -64,8 +64,8 @@ __device__ __forceinline__ void merged_end(const GraphDev& d, GraphState* st, lo
 // argmax colouring of the updated row for the next iteration (written over
 // this iteration's colours).  Mode 1 writes gS and gW instead.
 // VAR bit 0: some graph of the launch has an added fitness term (equity or colour
-// cost), bit 1: some graph takes heavy-ball steps; the plain variant carries neither
-// stream's registers.
+// cost), bit 1: some graph takes heavy-ball steps, bit 2: some graph is a multicolouring whose next
+// colours are selected from the row; the plain variant carries none of their registers.
 struct RowCtx {
     float nut, eta, rho, gam;
     int problem, c1, c2, k;
@@ -136,7 +136,7 @@ __device__ __forceinline__ void row_load(RowRegs<KPL, VAR>& R, float (&gv)[KPL],
 
 // the row's arithmetic; gv: the lane's entries of gS without the added-fitness term.  w, vel: the row's
 // memory (written in mode 0); gS_out, gW_out: the row's outputs (mode 1).  Returns the row's next colour
-// (mode 0), or -1 where the updated row is not finite; the updated weights stay in R.wv.
+// (mode 0), or -1 where the updated row is not finite; with VAR bit 2 the updated weights stay in R.wv.
 template <int KPL, int VAR>
 __device__ __forceinline__ int row_step(RowRegs<KPL, VAR>& R, const RowClasses<KPL, VAR>& C, float (&gv)[KPL],
                                         const RowCtx& x, float* __restrict__ w,
@@ -200,7 +200,7 @@ __device__ __forceinline__ int row_step(RowRegs<KPL, VAR>& R, const RowClasses<K
             float nw = R.wv[q] - x.eta * step;
             if (x.smooth) nw = nw / x.rho;
             w[l] = nw;
-            R.wv[q] = nw;
+            if constexpr ((VAR & 4) != 0) R.wv[q] = nw;
             if (!finite_f(nw)) bad = 1;
             if (nw > best) { best = nw; bi = l; }
         }
