@@ -55,14 +55,18 @@ struct Layout {
 // colours per vertex of a graph (its multicolouring demands' maximum, else 1)
 int cmax_of(const tcol_graph_params& p) { return p.problem == TCOL_MCOL ? std::max(1, (int)p.max_demand) : 1; }
 
+// group-concentration tiles of ts x ts (the operand stays zero past them)
+void mt_tiling(Layout& L, int n, int ts) {
+    L.mt_ts = ts;
+    L.mt_T = ceil_div(n, ts);
+    L.mt_tiles = L.mt_T * (L.mt_T + 1) / 2;
+}
+
 Layout make_layout(const tcol_graph_params& p) {
     Layout L{};
     L.n_pad = round_up(p.n, kPadN);
     L.rows_S = round_up(p.D * p.k, 16) + kSRowSlack;
-    // group-concentration tiles: 32 x 32 for small graphs (more blocks), else 64 x 64
-    L.mt_ts = L.n_pad <= 2048 ? 32 : 64;
-    L.mt_T = ceil_div(p.n, L.mt_ts);   // the operand stays zero past them
-    L.mt_tiles = L.mt_T * (L.mt_T + 1) / 2;
+    mt_tiling(L, p.n, L.n_pad <= 2048 ? 32 : 64);
     const size_t n2 = (size_t)L.n_pad * L.n_pad;
     const size_t dnk = (size_t)p.D * p.n * p.k;
     size_t sz[B_COUNT];
@@ -358,6 +362,8 @@ static bool pick_sparse(int kmax, int dmax, int nmax, int& PM, int& threads) {
 
 static int path_of(const tcol_ctx* c);
 static bool merged(const tcol_ctx* c);
+// 64 x 64 group-concentration tiles from which they are used at any n: four per CU
+constexpr int kMtFill = 1024;
 
 // Tile shapes of a merged contraction (both passes): resident blocks on the chip and time per K-vertex of a
 // full round in ns, fitted to launches of n = 200 to 4000 (single graphs, both passes)
@@ -548,6 +554,13 @@ static tcol_status rebuild_schedule(tcol_ctx* c) {
     for (int g = 0; g < c->G; ++g)
         if (!c->hdesc[g].pfuse) c->all_pfuse = false;
     c->prep_lds = prep_lds(c->kmax, c->nmax, ps_k > 0);
+    // group-concentration tiles: 64 x 64 beyond n_pad = 2048 and where the context has several of them per CU, else
+    // 32 x 32, four times the blocks.  16 graphs of n = 300 to 1802, 10 iterations: 4800 us with 32 x 32, 4600 with
+    // 64 x 64; one graph of n = 1531 (300 of the larger tiles): 445 against 463 us
+    long long t64 = 0;
+    for (int g = 0; g < c->G; ++g) t64 += (long long)ceil_div(c->params[g].n, 64) * (ceil_div(c->params[g].n, 64) + 1) / 2;
+    for (int g = 0; g < c->G; ++g)
+        mt_tiling(c->layouts[g], c->params[g].n, c->layouts[g].n_pad > 2048 || t64 >= kMtFill ? 64 : 32);
     // class-row sums: fp32 operands, one colour per vertex, a row in registers (which also keeps a block's 64
     // gradient rows within its LDS), and P's row offsets in 32 bits; beyond that the fp32 contraction
     c->rows = common_op(c) == kPrecFP32 && !c->any_mcol && update_rows_kpl(c->kmax) > 0 &&
