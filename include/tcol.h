@@ -142,7 +142,7 @@ typedef struct {
                                k <= 576; otherwise the fast path runs.  Its contraction tile
                                is 64 x 128 (tile_bm / tile_ntw do not apply).  Waits are
                                bounded (tcol_set_wait_limit) and cancellable (tcol_cancel) */
-    int32_t use_graph;      /* 1: replay each step from a captured hipGraph (default) */
+    int32_t use_graph;      /* 1: replay whole groups of `unroll` steps from a captured hipGraph (default) */
     int32_t unroll;         /* steps per captured graph (1..64, default 8) */
     int32_t tile_bm;        /* GEMM rows per block (64, 128 or 256); 0 = default or autotuned */
     int32_t tile_ntw;       /* GEMM 16-column subtiles per wave; the instantiated (tile_bm, tile_ntw)
@@ -247,8 +247,8 @@ tcol_status tcol_loss_grad(tcol_ctx *ctx, int32_t g, double *loss_dev, float *gr
  * receives S_d^T A S_d, the number of ordered pairs (i, j) with a_ij = 1, c_d(i) = l and
  * c_d(j) = l' (the edges between colour classes l and l', twice the edges inside class l
  * on the diagonal; its trace is 2 f_color(S_d), Section 3.5 eq. (1) with M_d = S_d S_d^T).
- * Computed as S_d^T (A.S_d): the contraction A.S (stored to G), then an FP32 MFMA
- * contraction over the vertices with the one-hot S_d^T; exact (integers below 2^24).  For
+ * Computed as S_d^T (A.S_d): the contraction A.S (stored to G), then its rows summed by
+ * the vertices' colours; exact (integers below 2^24).  For
  * partitioning the same matrix of the member's groups.  Asynchronous; overwrites the
  * context's G (the next tcol_step recomputes it).  Errors: TCOL_EINVAL, TCOL_EHIP. */
 tcol_status tcol_class_conflicts(tcol_ctx *ctx, int32_t g, int32_t *C_dev);
@@ -348,7 +348,7 @@ tcol_status tcol_mfma_peak(int32_t precision, int32_t iters, double *tflops);
 /* For callers that cannot allocate device memory (code under HIP graph capture, tight
  * serving loops, harnesses that forbid hipMalloc): tcol_conflicts without a context.  Steps
  * 1-2 for one graph with parameters p (p->problem selects the fitness; p->precision is
- * ignored: the contraction A.S runs in fp4 operands, exact for 0/1 in every format):
+ * ignored: the conflicts are counted from A's bits and the colours):
  *   A_dev       n x n uint8 row-major 0/1, symmetric, zero diagonal (not checked here:
  *               nonzero entries count as 1);
  *   W_dev       D x n x k fp32 weights (read only);
