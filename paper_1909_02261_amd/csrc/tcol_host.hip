@@ -193,12 +193,10 @@ struct tcol_ctx {
     size_t p1_lds = 0, cr_lds = 0;  // dynamic LDS of the merged first launch and of the class-row sums
     int total_cr = 0;               // blocks of the class-row sums
     int total_cf = 0;               // blocks of the conflict counts
-    // merged contraction with the row update: tile shape (0: none), largest k and tiles; whether
-    // every graph is updated there
     // merged update launches: rows and largest k of the graphs of few and of many colours (kFewColours)
     int ur_rows[2] = {0, 0}, ur_k[2] = {0, 0};
+    // merged contraction with the row update: tile shape (0: none), largest k and tiles
     int gr_bm = 0, gr_ntw = 0, gr_k = 0, gr_tiles = 0;
-    bool all_gfuse = false;
     int total_ps = 0;               // blocks of the sparse penalty kernel (0: no graph uses it)
     int total_rows = 0, total_mem = 0, total_mt = 0, total_ex = 0;
     int total_gm[2] = {0, 0};
@@ -384,12 +382,12 @@ static bool rows_fit(const tcol_graph_params& p, int bn) { return p.k <= bn && 1
 // each or 8 bytes per weight at 4.7 TB/s, whichever is more, or for graphs updated in their own launch 16 bytes per weight
 // and the launch.  Measured at k = 28, D = 128, n = 1000: 45.7 us with (64 x 128 tiles) against 55.6
 // without; at k = 20, D = 20, n = 200, where a tile's three members follow one another, 18.3 against 16.5.
-static double merged_cost(const tcol_ctx* c, const MergedShape& m, bool fuse, int* kf, bool* all) {
+static double merged_cost(const tcol_ctx* c, const MergedShape& m, bool fuse, int* kf) {
     const int bn = gemm_bn(m.ntw);
     double work = 0.0, nmax = 0.0, nsum = 0.0, own = 0.0, other = 0.0;
     int serial = 0;
     *kf = 0;
-    *all = true;
+    bool all = true;
     for (auto& p : c->params) {
         const bool f = fuse && rows_fit(p, bn);
         const double tiles = (double)ceil_div(p.n, m.bm) * (f ? ceil_div(p.D, bn / p.k) : ceil_div(p.D * p.k, bn));
@@ -402,7 +400,7 @@ static double merged_cost(const tcol_ctx* c, const MergedShape& m, bool fuse, in
             own += bytes;
             serial = std::max(serial, m.bm / 64 * std::min(p.D, bn / p.k));
         } else {
-            *all = false;
+            all = false;
             other += 2.0 * bytes;
         }
     }
@@ -410,14 +408,13 @@ static double merged_cost(const tcol_ctx* c, const MergedShape& m, bool fuse, in
     const double k_len = load <= nmax ? nmax : load + 0.25 * nsum / c->G;
     double cost = k_len * m.ns * 1e-3;
     if (*kf) cost += std::max(own, 2.0 * serial * std::max(1.0, load / nmax));
-    if (!*all) cost += other + 4.0;
+    if (!all) cost += other + 4.0;
     return cost;
 }
 
 // tile shape of a merged contraction, and whether it takes the row update
 static void pick_merged_shape(tcol_ctx* c) {
     c->gr_bm = c->gr_ntw = c->gr_k = 0;
-    c->all_gfuse = false;
     // (the batch launch, fused = 3, keeps its own tile)
     if (c->opt.fused != 1 || !merged(c) || c->rows || common_op(c) != kPrecFP4 ||
         (c->opt.tile_bm && c->opt.tile_ntw))
@@ -427,15 +424,13 @@ static void pick_merged_shape(tcol_ctx* c) {
         for (bool fuse : {true, false}) {
             if (!fuse && !shape_listed(m.bm, m.ntw)) continue;
             int kf = 0;
-            bool all = false;
-            const double cost = merged_cost(c, m, fuse, &kf, &all);
+            const double cost = merged_cost(c, m, fuse, &kf);
             if (cost >= best || (fuse && (kf == 0 || !gemm_rows_built(m.bm, m.ntw, kf, c->update_var)))) continue;
             best = cost;
             if (fuse) {
                 c->gr_bm = m.bm;
                 c->gr_ntw = m.ntw;
                 c->gr_k = kf;
-                c->all_gfuse = all;
             } else {
                 c->gr_bm = 0;
                 c->shape.bm = m.bm;
