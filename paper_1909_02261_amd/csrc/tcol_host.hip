@@ -1646,9 +1646,9 @@ tcol_status noalloc_scratch(int dev, uint8_t** out) {
     return TCOL_OK;
 }
 
-// the conflict pass's buffers inside the scratch array; `aop` and `sop` are sized as the operands of a contraction
-// were, which sets what fits (`aop` holds A's bits, `sop` the slots of
-// the conflict counts)
+// the conflict pass's buffers inside the scratch array.  `aop` (A's bits) and `sop` (the slots of the conflict counts)
+// are at least as large as the operands of a contraction, which sets what the call accepts; the slots need more
+// than those only for one colour, n <= 256 and D >= 585
 struct NoAllocLayout {
     size_t desc, state, ones, aop, sop, c, V, cT, f2, fcol, feq, f, total;
     int n_pad, rows_S, cs, cTs;
@@ -1666,7 +1666,7 @@ NoAllocLayout noalloc_layout(const tcol_graph_params& p) {
     L.state = take(sizeof(GraphState));
     L.ones = take(16);
     L.aop = take((size_t)L.n_pad * op_row_bytes(kPrecFP4, L.n_pad));
-    L.sop = take((size_t)L.rows_S * op_row_bytes(kPrecFP4, L.n_pad));
+    L.sop = take(std::max((size_t)L.rows_S * op_row_bytes(kPrecFP4, L.n_pad), sizeof(int32_t) * (size_t)p.D * kF2Slots));
     L.c = take(sizeof(int16_t) * ((size_t)p.D * L.cs + 64));
     L.V = take(sizeof(int32_t) * (size_t)p.D * p.k);
     L.cT = take(sizeof(int16_t) * (size_t)L.cTs * p.n);
