@@ -203,7 +203,10 @@ tcol_status tcol_set_demand(tcol_ctx *ctx, int32_t g, const int32_t *demand);
  * the argmax colouring.  Asynchronous.  Errors: TCOL_EINVAL, TCOL_EHIP. */
 tcol_status tcol_selection(tcol_ctx *ctx, int32_t g, int16_t *sel_dev);
 
-/* Change execution options (before or between tcol_step calls). */
+/* Change execution options (before or between tcol_step calls).  A named tile is used as named, by the contractions that
+ * store G and by the epilogue path.  tcol_get_options shows the options in effect: the schedule that runs, and for an
+ * automatic tile (0, 0) the shape chosen for those contractions, which fixes it if it is given back to tcol_set_options;
+ * with an automatic tile an iteration of the fast schedule may take its row update in a contraction of another tile. */
 tcol_status tcol_set_options(tcol_ctx *ctx, const tcol_options *opt);
 tcol_status tcol_get_options(tcol_ctx *ctx, tcol_options *opt);
 

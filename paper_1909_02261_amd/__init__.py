@@ -101,6 +101,7 @@ class Solver:
                                  ctypes.c_void_p(self.stream.cuda_stream)), "tcol_init")
         self._ctx = ctx
         self._lib = lib
+        self._tile_fixed = False
 
     # ------------------------------------------------------------------ API --
     def close(self) -> None:
@@ -120,10 +121,15 @@ class Solver:
         return {f: getattr(o, f) for f, _ in o._fields_}
 
     def set_options(self, **kw) -> None:
+        """Change the named options.  options() shows the tile that the automatic choice took, which a call
+        that names no tile must not turn into a fixed one: until one is named (or autotuned) it stays 0."""
         cur = self.options()
+        if not self._tile_fixed and not kw.keys() & {"tile_bm", "tile_ntw"}:
+            cur.update(tile_bm=0, tile_ntw=0)
         cur.update(kw)
         o = _lib.Options(**cur)
         _lib.check(self._lib.tcol_set_options(self._ctx, ctypes.byref(o)), "tcol_set_options")
+        self._tile_fixed = bool(o.tile_bm or o.tile_ntw)
 
     def step(self, max_steps: int, colors_out: Optional[List] = None):
         """Run up to max_steps iterations; returns (steps_done, legal_d list)."""
@@ -226,6 +232,7 @@ class Solver:
     def autotune(self):
         bm, ntw = ctypes.c_int32(0), ctypes.c_int32(0)
         _lib.check(self._lib.tcol_autotune(self._ctx, ctypes.byref(bm), ctypes.byref(ntw)), "tcol_autotune")
+        self._tile_fixed = True
         return bm.value, ntw.value
 
 

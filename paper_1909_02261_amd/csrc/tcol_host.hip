@@ -1177,13 +1177,9 @@ tcol_status tcol_set_options(tcol_ctx* c, const tcol_options* o) {
     if (o->penalty < 0 || o->penalty > 3) return TCOL_EINVAL;
     if (o->fused < 0 || o->fused > 3) return TCOL_EINVAL;
     if ((o->tile_bm || o->tile_ntw) && !shape_listed(o->tile_bm, o->tile_ntw)) return TCOL_EINVAL;
-    tcol_options old = c->opt, shown;
-    if (tcol_get_options(c, &shown) != TCOL_OK) return TCOL_EINVAL;
+    tcol_options old = c->opt;
     c->opt = *o;
     if (c->opt.unroll == 0) c->opt.unroll = 8;
-    // options read back (tcol_get_options names the automatic tile) and given again stay automatic
-    if (!old.tile_bm && c->opt.tile_bm == shown.tile_bm && c->opt.tile_ntw == shown.tile_ntw)
-        c->opt.tile_bm = c->opt.tile_ntw = 0;
     tcol_status s = rebuild_schedule(c);
     if (s != TCOL_OK) {
         c->opt = old;
