@@ -170,6 +170,7 @@ struct tcol_ctx {
     GemmShape fshape{};             // fused-path tiling
     bool fused_ok = false;          // the fused path is available for these graphs
     bool any_momentum = false;      // some graph takes heavy-ball steps (no epilogue path)
+    bool tables_finite = true;      // no penalty table entry overflows fp32
     bool any_mcol = false;          // some graph is a multicolouring (plain path only)
     int update_var = 0;             // row-update variant: bit 0 added fitness term, bit 1 momentum, bit 2 multicolouring
     int ps_PM = 0, ps_threads = 0;  // sparse penalty: members per accumulator group, block size
@@ -557,8 +558,9 @@ static tcol_status rebuild_schedule(tcol_ctx* c) {
     for (int g = 0; g < c->G; ++g)
         mt_tiling(c->layouts[g], c->params[g].n, c->layouts[g].n_pad > 2048 || t64 >= kMtFill ? 64 : 32);
     // class-row sums: fp32 operands, one colour per vertex, a row in registers (which also keeps a block's 64
-    // gradient rows within its LDS), and P's row offsets in 32 bits; beyond that the fp32 contraction
-    c->rows = common_op(c) == kPrecFP32 && !c->any_mcol && update_rows_kpl(c->kmax) > 0 &&
+    // gradient rows within its LDS), P's row offsets in 32 bits, and finite tables (the adjacency is the sign of an
+    // entry times t, which 0 times infinity loses); beyond that the fp32 contraction
+    c->rows = common_op(c) == kPrecFP32 && !c->any_mcol && c->tables_finite && update_rows_kpl(c->kmax) > 0 &&
               class_rows_lds(c->kmax) <= (size_t)kMaxBlockLds && c->nmax <= 16384;
     c->cr_lds = c->rows ? class_rows_lds(c->kmax) : 0;
     if (c->rows) HIPCHK(class_rows_prepare(c->kmax, c->update_var));
@@ -1116,8 +1118,11 @@ tcol_status tcol_init(tcol_ctx** out, int32_t G, const tcol_graph_params* p, con
         std::vector<double> lka(nlut), lvb(nlut);
         for (int m = 0; m < nlut; ++m) {
             const double x = prob_partition(q.problem) ? (double)(q.D - m) : (double)m;
-            lp[m] = (float)(2.0 * q.alpha * q.lambda * pow0(x, (double)q.alpha - 1.0));
-            lb[m] = (float)(2.0 * q.beta * q.mu * pow0(x, (double)q.beta - 1.0));
+            // without its weight a term is 0 whatever its exponent (free then: a negative one would give -0, a power that
+            // overflows NaN)
+            lp[m] = q.lambda > 0.0f ? (float)(2.0 * q.alpha * q.lambda * pow0(x, (double)q.alpha - 1.0)) : 0.0f;
+            lb[m] = q.mu > 0.0f ? (float)(2.0 * q.beta * q.mu * pow0(x, (double)q.beta - 1.0)) : 0.0f;
+            if (!isfinite(lp[m]) || !isfinite(lb[m])) c->tables_finite = false;
             lka[m] = pow0(x, q.alpha);
             lvb[m] = pow0(x, q.beta);
         }

@@ -1296,17 +1296,15 @@ __device__ __forceinline__ void mtilde_tile(const GraphDev& d, GraphState* st, i
 #pragma unroll
         for (int q = 0; q < PT; ++q) {
             const int j = jb + q;
-            // the sign of an fp32 entry tells edges (+) from the others (-), also where it is zero or NaN: the
-            // class-row sums count by it.  Set by bits: the tables are not negative, but where a term's weight is 0
-            // its exponent is free, which leaves -0 (a negative exponent) or NaN (a power that overflows) there, and
-            // an infinite entry times t = 0 is a NaN of either sign
+            // the sign of an fp32 entry tells edges (+) from the others (-), also where it is zero: the
+            // class-row sums count by it (their graphs' tables are finite and not negative, -0 included)
             float v = -0.0f;
             if (i < n && j < n) {
                 const int m = cnt[a][q];
                 const bool edge = ((arow >> (8 * q)) & 0xFFu) != 0;
                 const bool bon = !edge && (i != j || bdiag);
-                if (edge) v = __uint_as_float(__float_as_uint(tf * lut_pen[m]) & 0x7FFFFFFFu);
-                else if (bon) v = __uint_as_float(__float_as_uint(tf * lut_bon[m]) | 0x80000000u);
+                if (edge) v = tf * lut_pen[m];
+                else if (bon) v = -(tf * lut_bon[m]);
                 if (flags & kFlagLoss) {
                     const double wgt = mirror ? 2.0 : 1.0;
                     if (edge) ka += wgt * lut_ka[m];
@@ -2006,7 +2004,7 @@ __global__ __launch_bounds__(kCrThreads) __attribute__((amdgpu_waves_per_eu(KPL 
     int* fsum = (int*)cr_sh;                             // [NW]
     float* Gt = (float*)(cr_sh + 64);                    // [64][KS]
     const float tf = (float)t;
-    const bool pen = (d.lambda * tf != 0.0f) || (d.mu * tf != 0.0f);   // inactive, P may hold NaN (tables of infinities)
+    const bool pen = (d.lambda * tf != 0.0f) || (d.mu * tf != 0.0f);
     const uint32_t sign = prob_partition(d.problem) ? 0x80000000u : 0u;
     // the row update's rows: 16 lanes each, two rows per group of lanes; where they fit in registers
     // their loads go out now, behind the sums

@@ -9,10 +9,13 @@ from gpu_util import host, make_solver, torch_mod
 
 pytestmark = pytest.mark.gpu
 
-# the exponent of a term whose weight is 0 is free: its table entries are then -0 (a negative exponent) or, where the
+# the exponent of a term whose weight is 0 is free: its table entries would be -0 (a negative exponent) or, where the
 # power overflows, NaN; with a weight, infinite entries times t = 0 are NaN
-PARAMS = {"alpha_negative": dict(lam=0.0, alpha=-1.0, mu=1e-4, beta=1.2), "beta_negative": dict(lam=1e-3, alpha=2.5, mu=0.0, beta=-1.0),
-          "both_negative": dict(lam=0.0, alpha=-1.0, mu=0.0, beta=-2.0), "both_overflow": dict(lam=0.0, alpha=900.0, mu=0.0, beta=900.0),
+PARAMS = {"alpha_negative": dict(lam=0.0, alpha=-1.0, mu=1e-4, beta=1.2),
+          "beta_negative": dict(lam=1e-3, alpha=2.5, mu=0.0, beta=-1.0),
+          "both_negative": dict(lam=0.0, alpha=-1.0, mu=0.0, beta=-2.0),
+          "alpha_overflow": dict(lam=0.0, alpha=900.0, mu=1e-4, beta=1.2),
+          "both_overflow": dict(lam=0.0, alpha=900.0, mu=0.0, beta=900.0),
           "infinite_table": dict(lam=1e-3, alpha=900.0, mu=1e-3, beta=900.0)}
 
 
