@@ -194,6 +194,7 @@ struct tcol_ctx {
     size_t p1_lds = 0, cr_lds = 0;  // dynamic LDS of the merged first launch and of the class-row sums
     int total_cr = 0;               // blocks of the class-row sums
     int total_cf = 0;               // blocks of the conflict counts
+    int total_lg = 0;               // blocks of the search for legal members (0: no graph stops)
     // merged update launches: rows and largest k of the graphs of few and of many colours (kFewColours)
     int ur_rows[2] = {0, 0}, ur_k[2] = {0, 0};
     // merged contraction with the row update: tile shape (0: none), largest k and tiles
@@ -568,12 +569,10 @@ static tcol_status rebuild_schedule(tcol_ctx* c) {
     pick_merged_shape(c);
     HIPCHK(gemm_prepare(c->shape));
     const int BN0 = gemm_bn(c->shape.ntw);
-    bool stops = false;
-    for (auto& p : c->params) stops = stops || p.stop_on_legal;
-    c->p1_lds = phase1_lds(c->kmax, c->nmax, c->rows || (stops && update_rows_kpl(c->kmax) > 0));
+    c->p1_lds = phase1_lds(c->kmax, c->nmax, c->rows);
     HIPCHK(phase1_prepare());
     if (c->gr_bm) HIPCHK(gemm_rows_prepare(c->gr_bm, c->gr_ntw, c->gr_k, c->update_var));
-    int rows = 0, mem = 0, pg = 0, mt = 0, ex = 0, cr = 0, cf = 0;
+    int rows = 0, mem = 0, pg = 0, mt = 0, ex = 0, cr = 0, cf = 0, lg = 0;
     for (int g = 0; g < c->G; ++g) {
         const tcol_graph_params& p = c->params[g];
         const Layout& L = c->layouts[g];
@@ -587,6 +586,8 @@ static tcol_status rebuild_schedule(tcol_ctx* c) {
         cr += p.D * ceil_div(p.n, 64);
         d.cf_begin = cf;
         cf += conflict_blocks(p.D, p.n);
+        d.lg_begin = lg;
+        if (p.stop_on_legal) lg += p.D * search_parts(p.n);
         d.ps_begin = pg;
         if (d.psparse) pg += p.n;
         d.mt_begin = mt;
@@ -657,6 +658,7 @@ static tcol_status rebuild_schedule(tcol_ctx* c) {
     c->total_ex = ex;
     c->total_cr = cr;
     c->total_cf = cf;
+    c->total_lg = lg;
     c->total_gm[0] = gm0;
     c->total_gm[1] = gm1;
     c->gr_tiles = gm2;
@@ -692,8 +694,8 @@ static bool merged(const tcol_ctx* c) { return path_of(c) == 1 && c->total_ps ==
 // everything that depends only on the colours, in one launch (S^T where a contraction follows)
 static hipError_t enqueue_phase1(tcol_ctx* c, int honor, int adv, int want, int tiles, int flags, int gsel,
                                  bool expand, hipStream_t s, bool conflicts = false) {
-    return launch_phase1(c->ddesc, c->G, c->total_mem, tiles, expand ? c->total_ex : 0, conflicts ? c->total_cf : 0, c->p1_lds, honor, adv, want,
-                         flags, gsel, s);
+    return launch_phase1(c->ddesc, c->G, c->total_mem, tiles, expand ? c->total_ex : 0, conflicts ? c->total_cf : 0,
+                         want & 1 ? c->total_lg : 0, c->p1_lds, honor, adv, want, flags, gsel, s);
 }
 
 // one Algorithm-1 iteration for every running graph (plain path)
@@ -1738,7 +1740,7 @@ extern "C" tcol_status tcol_conflicts_noalloc(const tcol_graph_params* p, const 
     HIPCHK(launch_pack_graph(A_dev, p->n, L.n_pad, kPrecFP4, nullptr, const_cast<unsigned long long*>(d.Ab), nullptr,
                              (int*)(base + L.ones), ones, s));
     HIPCHK(launch_colors(gd, 1, total_rows, 0, s));
-    HIPCHK(launch_phase1(gd, 1, p->D, 0, 0, conflict_blocks(p->D, p->n), phase1_lds(p->k, p->n, 0), 0, 0, 0, 0, -1, s));
+    HIPCHK(launch_phase1(gd, 1, p->D, 0, 0, conflict_blocks(p->D, p->n), 0, phase1_lds(p->k, p->n, 0), 0, 0, 0, 0, -1, s));
     HIPCHK(launch_report(gd, 1, 0, kFlagFoldCounts, colors_dev, f_main_dev, f_sec_dev, s));
     return TCOL_OK;
 }

@@ -109,7 +109,8 @@ struct GraphDev {
     int32_t* f2;              // [D] 2 * f_color accumulated by the GEMM
     int32_t* f2p;             // [D][kF2Slots] 2 * f_color gathered by the sparse rows, spread over
                               // slots (row i adds to slot i mod kF2Slots) so their atomics do not
-                              // pile onto one address; folded into f2 by the rows' last block
+                              // pile onto one address; folded into f2 by the rows' last block.  The merged
+                              // schedule's stop rule counts a member's answers in its first slot
     int64_t* fcol;            // [D] main fitness: f_color, or the cut for partitioning
     int64_t* feq;             // [D] added fitness: f_eq, the colour cost, or 0
     int64_t* f;               // [D] fcol + feq
@@ -149,6 +150,7 @@ struct GraphDev {
     int rows;                 // the class-row sums (k_class_rows) replace the fp32 contraction
     int cr_begin;             // blocks of the class-row kernel
     int cf_begin;             // blocks of the conflict counts
+    int lg_begin;             // blocks of the search for legal members
     int mt_begin;             // tiles of the group-concentration kernel
     int mt_T;                 // tiles per side
     int mt_ts;                // tile side of the group-concentration kernel (32 or 64)
@@ -263,6 +265,10 @@ __device__ inline int xcd_remap(int b, int nb) {
     const int x = b & 7, i = b >> 3;
     return x * q + min(x, r) + i;
 }
+
+// blocks per member of the search for legal members (1024 vertices each: at n = 1000 one block's search to the end
+// takes about 6 us, less than the tiles of the same launch)
+__host__ __device__ inline int search_parts(int n) { return ceil_div(n, 1024); }
 
 // find the graph that owns flattened work item `w` given a begin offset per graph
 template <typename F>

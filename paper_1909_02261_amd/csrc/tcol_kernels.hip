@@ -1423,12 +1423,28 @@ __host__ __device__ inline size_t member_lds_bytes(int k, int n) {
     return sizeof(int) * ((size_t)kPrepScratch + 14 * (size_t)k + 2) + sizeof(int16_t) * (((size_t)n + 3 * (size_t)k + 1) & ~(size_t)1);
 }
 
+// One part's answer to whether member m is illegal: the parts of a member (the blocks of its conflict search and,
+// with an added fitness, its member block) add to one word, and the last of them, which sees that all have answered, clears it and
+// lists a member that none found illegal.  The word is the member's first conflict slot, which is zero between the
+// launches that use it.
+__device__ __forceinline__ void legal_vote(const GraphDev& d, GraphState* st, int m, int parts, bool bad) {
+    int* word = d.f2p + (size_t)m * kF2Slots;
+    const int add = bad ? 0x10000 : 1;
+    const int all = atomicAdd(word, add) + add;
+    if ((all & 0xFFFF) + (all >> 16) != parts) return;
+    atomicExch(word, 0);
+    if ((all >> 16) == 0) atomicMin(&st->legal_min[st->t & 1], m);
+}
+
+// whether an iteration asks for the members' legality (minimum sum colouring always has a colour cost; a
+// multicolouring graph's conflicts come from the contraction)
+__device__ __forceinline__ bool asks_legal(const GraphDev& d, int want) {
+    return (want & 1) && d.stop_on_legal && d.problem != kProbMSCP && d.cmax == 1;
+}
+
 // Member `mem` of the merged first launch (one colour per vertex): class sizes and the added
 // fitness where the problem has one, with want & 2 the class lists in summation order for graphs on the
-// class-row sums, with want & 4 its conflict counter cleared, and with want & 1 whether the member is legal (f = 0), so that the launch that updates the
-// weights knows the stop rule's answer before it starts and no fitness launch stands between.  A
-// member is illegal as soon as one conflicting pair (partitioning: one cut edge) is found, which in
-// all but the last iterations is at once; a full scan of small classes is sum_l #V_l^2 / 2 pairs.
+// class-row sums, and with want & 4 its conflict counter cleared.
 __device__ __forceinline__ void member_block(const GraphDev* __restrict__ gd, int G, int mem, int honor_stop, int adv,
                                              int want, int* sh) {
     const GraphDev& d = gd[find_graph(gd, G, mem, [](const GraphDev& x) { return x.mem_begin; })];
@@ -1449,17 +1465,12 @@ __device__ __forceinline__ void member_block(const GraphDev* __restrict__ gd, in
     if ((want & 4) && !stop_now && tid == 0) d.f2[m] = 0;
     if (stop_now || d.cmax > 1) return;
     const int k = d.k, n = d.n;
-    const bool part = prob_partition(d.problem), added = prob_added(d.problem);
-    // minimum sum colouring always has a colour cost, so no member is legal
-    const bool want_legal = (want & 1) && d.stop_on_legal && d.problem != kProbMSCP;
-    const bool rows = d.rows && (want & 2);
-    const bool lists = rows || (want_legal && !part);
-    if (!lists && !want_legal && !added) return;
+    const bool added = prob_added(d.problem);
+    const bool lists = d.rows && (want & 2);
+    if (!lists && !added) return;
     const int16_t* __restrict__ c = d.c[st->pS] + (size_t)m * d.cs;
     int* part_sum = sh;                                       // [257]
     long long* fsum = (long long*)(sh + 260);                 // [4]
-    volatile int* found = sh + 276;
-    volatile int* feq_zero = sh + 277;
     int* cnt = sh + kPrepScratch;                             // [k]
     int* cw = cnt + k;                                        // [4][k]
     unsigned long long* msk = (unsigned long long*)(cw + 4 * k + (k & 1));   // [4][k] (8-byte aligned)
@@ -1474,7 +1485,6 @@ __device__ __forceinline__ void member_block(const GraphDev* __restrict__ gd, in
             cw[l] = 0;
             msk[l] = 0ull;
         }
-    if (tid == 0) { *found = 0; *feq_zero = 1; }
     __syncthreads();
     const int np16 = (n + 15) & ~15;                          // positions (those of vertices >= n are skipped)
     const int e0 = wv * Q, e1 = min(np16, (wv + 1) * Q);
@@ -1514,7 +1524,8 @@ __device__ __forceinline__ void member_block(const GraphDev* __restrict__ gd, in
         if (tid == 0) {
             const long long f = fsum[0] + fsum[1] + fsum[2] + fsum[3];
             d.feq[m] = f;
-            *feq_zero = f == 0;
+            // with an added fitness the member is legal only if that is 0 too
+            if (asks_legal(d, want)) legal_vote(d, st, m, search_parts(n) + 1, f != 0);
         }
     }
     if (lists) {
@@ -1548,7 +1559,7 @@ __device__ __forceinline__ void member_block(const GraphDev* __restrict__ gd, in
             const int pads = -cnt[l] & 3;
             offl[l] = acc;
             // start (a multiple of four) and padding in one word
-            if (rows) d.cls_off[(size_t)m * (k + 1) + l] = acc | pads;
+            d.cls_off[(size_t)m * (k + 1) + l] = acc | pads;
             int q = acc;
 #pragma unroll
             for (int w = 0; w < NW; ++w) {
@@ -1559,7 +1570,7 @@ __device__ __forceinline__ void member_block(const GraphDev* __restrict__ gd, in
             for (int e = 0; e < pads; ++e) lst[q + e] = (int16_t)-1;
             acc = q + pads;
         }
-        if (tid == 0 && rows) d.cls_off[(size_t)m * (k + 1) + k] = total;
+        if (tid == 0) d.cls_off[(size_t)m * (k + 1) + k] = total;
         __syncthreads();
         // placement in summation order: each wave walks its positions 64 at a time; lanes of one
         // colour find their rank among the batch in the colour's batch mask, and the last of them
@@ -1590,52 +1601,97 @@ __device__ __forceinline__ void member_block(const GraphDev* __restrict__ gd, in
             wave_sync();
         }
         __syncthreads();
-        if (rows) {
-            // the entries as byte offsets of the vertices' rows of P; padding takes the row past the last, which is zero
-            uint32_t* __restrict__ cj = d.cls_j + (size_t)m * d.js;
-            const uint32_t rb = 4u * (uint32_t)d.n_pad;
-            for (int q = tid; q < total; q += 256) cj[q] = (lst[q] < 0 ? (uint32_t)d.n_pad : (uint32_t)lst[q]) * rb;
-        }
+        // the entries as byte offsets of the vertices' rows of P; padding takes the row past the last, which is zero
+        uint32_t* __restrict__ cj = d.cls_j + (size_t)m * d.js;
+        const uint32_t rb = 4u * (uint32_t)d.n_pad;
+        for (int q = tid; q < total; q += 256) cj[q] = (lst[q] < 0 ? (uint32_t)d.n_pad : (uint32_t)lst[q]) * rb;
     }
-    if (!want_legal) return;
-    __syncthreads();
-    // with an added fitness the member is legal only if that is 0 too
-    if (*feq_zero) {
-        const uint8_t* __restrict__ A8 = d.A8;
-        const size_t n_pad = d.n_pad;
-        if (!part) {
-            const int total = part_sum[256];
-            for (int q = tid; q < total && !*found; q += 256) {
-                const int v = lst[q];
-                if (v < 0) continue;
-                const int x = gview(c)[v];
-                const int e = offl[x] + cnt[x];
-                const uint8_t* __restrict__ row = A8 + (size_t)v * n_pad;
-                for (int r = q + 1; r < e && !*found; r += 4) {
-                    int hit = 0;
+}
+
+// words of 64 vertices per piece of the class masks below, and their row stride (odd: rows on different banks), for
+// the LDS of a group-concentration tile; at least one word
+struct ScanShape {
+    int words, stride;
+};
+constexpr int kScanHead = 16;   // ints before the masks
+__host__ __device__ inline ScanShape scan_shape(int n, int k) {
+    constexpr int room = (kMtLds - 4 * kScanHead) / 8;
+    const int all = (n + 63) / 64;
+    int w = room / k;
+    if (w > all) w = all;
+    if (w > 1 && !(w & 1) && k * (w + 1) > room) --w;
+    if (w < 1) w = 1;
+    return {w, w | 1};
+}
+__host__ __device__ inline size_t scan_lds_bytes(int n, int k) {
+    return 4 * kScanHead + 8 * (size_t)k * scan_shape(n, k).stride;
+}
+
+// The stop rule's question for one part of a member: whether some pair of its vertices conflicts (partitioning: is cut).
+// The member's classes are bit masks in LDS, 64 vertices to a word, a piece of the words at a time, and vertex i's adjacency
+// to 64 vertices is one word (A is symmetric, so a wave reads 64 rows' words in one load): i conflicts with those of
+// them that both words hold.  n^2 / 128 words a member whatever its classes are, and a search that finds a pair ends at once,
+// which in all but the last iterations is in the first words.
+// Eight iterations with members one conflict from legal, D = 8 (fp4): n = 2700, k = 2 412 us, 384 without the stop rule; n = 5000,
+// k = 3 647 and 643.  A scan of the pairs of each class, byte by byte, took 9350 and 22040 there.
+__device__ __forceinline__ void legal_block(const GraphDev* __restrict__ gd, int G, int b, int honor_stop, int adv, int want,
+                                            int* sh) {
+    const GraphDev& d = gd[find_graph(gd, G, b, [](const GraphDev& x) { return x.lg_begin; })];
+    GraphState* st = d.st;
+    if (honor_stop && (st->stopped || (adv && st->next_bad))) return;
+    if (!asks_legal(d, want)) return;
+    const int n = d.n, k = d.k, parts = search_parts(n);
+    const int loc = b - d.lg_begin;
+    const int m = loc / parts, part = loc - m * parts;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int strips = (n + 63) / 64;
+    const ScanShape ss = scan_shape(n, k);
+    volatile int* found = sh;
+    unsigned long long* msk = (unsigned long long*)(sh + kScanHead);
+    const auto* __restrict__ c = gview((const int16_t*)d.c[st->pS]) + (size_t)m * d.cs;
+    const size_t n_pad = d.n_pad;
+    const unsigned long long flip = prob_partition(d.problem) ? ~0ull : 0ull;
+    if (tid == 0) *found = 0;
+    for (int s0 = 0; s0 < strips; s0 += ss.words) {
+        const int s1 = min(strips, s0 + ss.words);
+        for (int e = tid; e < k * ss.stride; e += 256) msk[e] = 0ull;
+        __syncthreads();
+        for (int v0 = 64 * s0 + tid; v0 < min(n, 64 * s1); v0 += 256 * 4) {
+            int x[4];
 #pragma unroll
-                    for (int u = 0; u < 4; ++u) hit |= r + u < e ? (int)gview(row)[lst[r + u]] : 0;
-                    if (hit) *found = 1;
-                }
-            }
-        } else {
-            // a cut edge: ends of different colours
-            for (int v = tid; v < n && !*found; v += 256) {
-                const int x = gview(c)[v];
-                const uint8_t* __restrict__ row = A8 + (size_t)v * n_pad;
-                for (int j = 0; j < v && !*found; j += 4) {
-                    const uint32_t a4 = gview((const uint32_t*)(row + j))[0];
-                    int hit = 0;
+            for (int u = 0; u < 4; ++u) x[u] = v0 + 256 * u < min(n, 64 * s1) ? (int)c[v0 + 256 * u] : -1;
 #pragma unroll
-                    for (int u = 0; u < 4; ++u)
-                        if (j + u < v && ((a4 >> (8 * u)) & 0xFFu)) hit |= gview(c)[j + u] != x;
-                    if (hit) *found = 1;
-                }
+            for (int u = 0; u < 4; ++u) {
+                const int v = v0 + 256 * u;
+                if (x[u] >= 0)
+                    atomicOr((uint32_t*)(msk + x[u] * ss.stride + (v >> 6) - s0) + ((v >> 5) & 1), 1u << (v & 31));
             }
         }
         __syncthreads();
-        if (tid == 0 && !*found) atomicMin(&st->legal_min[st->t & 1], m);
+        // this part's strips, the longest rows first; vertex i looks at the words up to its own
+        for (int q = (strips - 1 - part) / parts - wave; q >= 0; q -= 4) {
+            const int strip = part + q * parts;
+            if (strip < s0 || *found) break;
+            const int i = strip * 64 + lane;
+            const unsigned long long* row = msk + (i < n ? (int)c[i] : 0) * ss.stride - s0;
+            const auto* __restrict__ a = gview(d.Ab) + i;
+            const int e = min(s1, strip + 1);
+            for (int s = s0; s < e && !*found; s += 8) {
+                unsigned long long w[8];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) w[u] = s + u < e ? a[(size_t)(s + u) * n_pad] : 0ull;
+                unsigned long long hit = 0;
+#pragma unroll
+                for (int u = 0; u < 8; ++u)
+                    if (s + u < e) hit |= w[u] & (row[s + u] ^ flip);
+                if (__any(hit != 0ull)) *found = 1;
+            }
+        }
+        __syncthreads();
+        if (*found) break;      // no wave writes it before the next piece's barriers: the same answer for all
     }
+    if (tid == 0) legal_vote(d, st, m, parts + (prob_added(d.problem) ? 1 : 0), *found != 0);
 }
 
 // even bits of x to the low half, odd bits to the high half
@@ -1702,15 +1758,17 @@ __device__ __forceinline__ void conflict_block(const GraphDev* __restrict__ gd, 
 }
 
 // First launch of a merged iteration: everything that depends only on the colours, in blocks of
-// several kinds: the members (class sizes, lists, legality), the group-concentration tiles with the
+// several kinds: the members (class sizes, lists), the search for legal members, the group-concentration tiles with the
 // penalty operand, the expansion of S^T, and (where they are asked for) the conflict counts.  As three launches of 4-5 us each they were most of a
 // small graph's iteration.  t stays as it is here (the launch that updates the weights advances
 // it), so the tiles may read it; a pending non-finite update ends the graph (adv).
 // Held to 64 registers (eight waves per SIMD, no spills; 95 without): the blocks of the later kinds start
-// beside the tiles instead of after them (16 graphs, 10 iterations: 4608 -> 4538 us).
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8))) void k_phase1(const GraphDev* __restrict__ gd, int G, int total_mem, int total_mt,
-                                                int total_ex, int total_cf, int honor_stop, int adv, int want, int mt_flags,
-                                                int gsel) {
+// beside the tiles instead of after them (16 graphs, 10 iterations: 4608 -> 4538 us).  With the search for legal members
+// (LEGAL: contexts with a stop rule) the same bound spills in the tiles, so that variant takes seven.
+template <int LEGAL>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(LEGAL ? 7 : 8))) void k_phase1(
+    const GraphDev* __restrict__ gd, int G, int total_mem, int total_mt, int total_ex, int total_cf, int total_lg,
+    int honor_stop, int adv, int want, int mt_flags, int gsel) {
     extern __shared__ __attribute__((aligned(16))) int p1_sh[];
     int b = blockIdx.x;
     if (b < total_mem) {
@@ -1718,6 +1776,13 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8))) void k
         return;
     }
     b -= total_mem;
+    if constexpr (LEGAL != 0) {
+        if (b < total_lg) {
+            legal_block(gd, G, b, honor_stop, adv, want, p1_sh);
+            return;
+        }
+        b -= total_lg;
+    }
     if (b < total_mt) {
         mtilde_block(gd, G, b, honor_stop, mt_flags, gsel, nullptr, (uint8_t*)p1_sh, adv);
         return;
@@ -2576,18 +2641,27 @@ size_t phase1_lds(int kmax, int nmax, int lists) {
     // without lists only the scratch and the counts are used
     size_t b = lists ? member_lds_bytes(kmax, nmax) : sizeof(int) * ((size_t)kPrepScratch + kmax);
     if (b < (size_t)kMtLds) b = kMtLds;
+    if (b < scan_lds_bytes(nmax, kmax)) b = scan_lds_bytes(nmax, kmax);
     return (b + 15) / 16 * 16;
 }
 
 hipError_t phase1_prepare() {
-    return hipFuncSetAttribute((const void*)k_phase1, hipFuncAttributeMaxDynamicSharedMemorySize, kMaxBlockLds);
+    const hipError_t e =
+        hipFuncSetAttribute((const void*)k_phase1<0>, hipFuncAttributeMaxDynamicSharedMemorySize, kMaxBlockLds);
+    if (e != hipSuccess) return e;
+    return hipFuncSetAttribute((const void*)k_phase1<1>, hipFuncAttributeMaxDynamicSharedMemorySize, kMaxBlockLds);
 }
 
-hipError_t launch_phase1(const GraphDev* gd, int G, int total_mem, int total_mt, int total_ex, int total_cf, size_t lds,
-                         int honor_stop, int adv, int want, int mt_flags, int gsel, hipStream_t s) {
+hipError_t launch_phase1(const GraphDev* gd, int G, int total_mem, int total_mt, int total_ex, int total_cf, int total_lg,
+                         size_t lds, int honor_stop, int adv, int want, int mt_flags, int gsel, hipStream_t s) {
     if (lds > (size_t)kMaxBlockLds) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_phase1, dim3(total_mem + total_mt + total_ex + total_cf), dim3(256), lds, s, gd, G, total_mem,
-                       total_mt, total_ex, total_cf, honor_stop, adv, want, mt_flags, gsel);
+    const dim3 grid(total_mem + total_lg + total_mt + total_ex + total_cf), blk(256);
+    if (total_lg > 0)
+        hipLaunchKernelGGL(k_phase1<1>, grid, blk, lds, s, gd, G, total_mem, total_mt, total_ex, total_cf, total_lg,
+                           honor_stop, adv, want, mt_flags, gsel);
+    else
+        hipLaunchKernelGGL(k_phase1<0>, grid, blk, lds, s, gd, G, total_mem, total_mt, total_ex, total_cf, 0, honor_stop,
+                           adv, want, mt_flags, gsel);
     TCOL_LAUNCH_CHECK();
     return hipSuccess;
 }

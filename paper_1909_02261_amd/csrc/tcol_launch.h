@@ -47,15 +47,15 @@ int update_rows_kpl(int kmax);
 // bit 2 some graph is a multicolouring
 hipError_t launch_update_rows(const GraphDev* gd, int G, int row0, int total_rows, int kmax, int var, int honor_stop, int mode,
                               int gsel, float* gS_out, float* gW_out, int merged, hipStream_t s);
-// merged iterations: first launch (members, group-concentration tiles, expansion and conflict blocks; want & 1: legality, & 2: class lists for the class-row sums,
-// & 4: conflict counters cleared for the gather that follows; lists: some
-// graph needs its class lists), and the class-row sums with the row update (graphs with `rows`;
+// merged iterations: first launch (members, search for legal members, group-concentration tiles, expansion and conflict
+// blocks; want & 1: legality, & 2: class lists for the class-row sums, & 4: conflict counters cleared for the gather that
+// follows; lists: some graph needs its class lists), and the class-row sums with the row update (graphs with `rows`;
 // modes in k_class_rows)
 constexpr int kMaxBlockLds = 150 * 1024;
 size_t phase1_lds(int kmax, int nmax, int lists);
 hipError_t phase1_prepare();
-hipError_t launch_phase1(const GraphDev* gd, int G, int total_mem, int total_mt, int total_ex, int total_cf, size_t lds,
-                         int honor_stop, int adv, int want, int mt_flags, int gsel, hipStream_t s);
+hipError_t launch_phase1(const GraphDev* gd, int G, int total_mem, int total_mt, int total_ex, int total_cf, int total_lg,
+                         size_t lds, int honor_stop, int adv, int want, int mt_flags, int gsel, hipStream_t s);
 // contraction of a merged iteration, with the row update for graphs with gfuse (tiles: the graphs' merged
 // tilings; kmax: the largest k of the graphs with gfuse)
 bool gemm_rows_built(int bm, int ntw, int kmax, int var);

@@ -1,0 +1,83 @@
+"""Calls whose time must not depend on the colouring, or grow with a batch or with few colours, beside another route of
+the same build to the same numbers.  Each bound stands far from both sides: a route that loses its split loses several
+times, and the routes compared share the box and the moment."""
+import time
+
+import numpy as np
+import pytest
+
+from paper_1909_02261_amd import FP4, FP32, KCOL, KPART, MCOL
+
+from gpu_util import host, torch_mod
+
+pytestmark = pytest.mark.gpu
+
+
+def us_of(f, reps=8):
+    """Microseconds a call, the least of five runs of `reps`."""
+    torch = torch_mod()
+    f(), f()
+    best = float("inf")
+    for _ in range(5):
+        torch.cuda.synchronize()
+        t0 = time.perf_counter()
+        for _ in range(reps):
+            f()
+        torch.cuda.synchronize()
+        best = min(best, (time.perf_counter() - t0) / reps * 1e6)
+    return best
+
+
+def solver(n, k, D, prec, cols=None, G=1, problem=KCOL, A=None, **kw):
+    """A solver whose colours stay as they are (a step moves the weights by about 1e-9)."""
+    import paper_1909_02261_amd as pk
+    torch = torch_mod()
+    rng = np.random.default_rng(n + k)
+    graphs, params = [], []
+    for g in range(G):
+        if A is None:
+            a = np.triu(rng.random((n, n), dtype=np.float32) < 0.5, 1)
+            a = (a | a.T).astype(np.uint8)
+        else:
+            a = A
+        c = rng.integers(0, k, (D, n)) if cols is None else cols
+        W = rng.normal(0.0, 0.01, (D, n, k)).astype(np.float32)
+        np.put_along_axis(W, c[:, :, None], 1.0, axis=2)
+        graphs.append((torch.from_numpy(a).cuda(), torch.from_numpy(W).cuda()))
+        params.append(pk.Params(n=n, k=k, D=D, problem=problem, precision=prec, eta=1e-9, rho=1.0,
+                                max_demand=1 if problem == MCOL else 0, **{"stop_on_legal": 0, **kw}))
+    s = pk.Solver(graphs, params)
+    for g in range(G):
+        s.set_t(100, g)
+    return s
+
+
+def one_conflict(n, k, part):
+    """A graph and a colouring with one conflicting (partitioning: cut) edge, between the vertices that a scan reaches
+    last."""
+    rng = np.random.default_rng(n)
+    base = np.sort(np.arange(n) % k)
+    a = np.triu(rng.random((n, n), dtype=np.float32) < 0.5, 1)
+    same = base[:, None] == base[None, :]
+    a &= same if part else ~same
+    i, j = (n - 1, 0) if part else (n - 1, n - 2)
+    a[min(i, j), max(i, j)] = True
+    return (a | a.T).astype(np.uint8), base
+
+
+@pytest.mark.parametrize("problem,n,k,D,prec", [(KCOL, 2700, 2, 8, FP4), (KCOL, 5000, 3, 8, FP4), (KPART, 2000, 4, 8, FP4),
+                                                (KCOL, 1000, 3, 32, FP32)])
+def test_stop_rule_of_nearly_legal_members(problem, n, k, D, prec):
+    """Eight iterations with the stop rule on members one conflict away from legal against the same without it."""
+    A, base = one_conflict(n, k, problem == KPART)
+    us = []
+    for stop in (0, 1):
+        s = solver(n, k, D, prec, cols=np.tile(base, (D, 1)), A=A, problem=problem, stop_on_legal=stop)
+        if problem == KPART:
+            s.set_options(penalty=1)
+        assert s.conflicts(0)[1].tolist() == [1] * D
+        us.append(us_of(lambda: s.step(8)))
+        assert s.conflicts(0)[1].tolist() == [1] * D
+        s.close()
+    # (a scan of the pairs of the classes, one byte at a time, took 2.4 to 37 times)
+    assert us[1] < 1.35 * us[0] + 40, us
