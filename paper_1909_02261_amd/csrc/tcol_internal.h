@@ -269,6 +269,8 @@ __device__ inline int xcd_remap(int b, int nb) {
 // blocks per member of the search for legal members (1024 vertices each: at n = 1000 one block's search to the end
 // takes about 6 us, less than the tiles of the same launch)
 __host__ __device__ inline int search_parts(int n) { return ceil_div(n, 1024); }
+// and of the conflict counts (256 vertices each, 64 a wave)
+__host__ __device__ inline int count_parts(int n) { return ceil_div(n, 256); }
 
 // find the graph that owns flattened work item `w` given a begin offset per graph
 template <typename F>

@@ -1627,6 +1627,27 @@ __host__ __device__ inline size_t scan_lds_bytes(int n, int k) {
     return 4 * kScanHead + 8 * (size_t)k * scan_shape(n, k).stride;
 }
 
+// the class masks of words [s0, s1) of the vertices with colours c, by the block's 256 threads (which have read the last
+// ones before): msk[l * stride + w] holds the vertices of class l in word s0 + w
+template <typename C>
+__device__ __forceinline__ void class_masks(C c, int n, int k, ScanShape ss, int s0, int s1, unsigned long long* msk) {
+    const int tid = threadIdx.x;
+    for (int e = tid; e < k * ss.stride; e += 256) msk[e] = 0ull;
+    __syncthreads();
+    const int end = min(n, 64 * s1);
+    for (int v0 = 64 * s0 + tid; v0 < end; v0 += 256 * 4) {
+        int x[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) x[u] = v0 + 256 * u < end ? (int)c[v0 + 256 * u] : -1;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int v = v0 + 256 * u;
+            if (x[u] >= 0) atomicOr((uint32_t*)(msk + x[u] * ss.stride + (v >> 6) - s0) + ((v >> 5) & 1), 1u << (v & 31));
+        }
+    }
+    __syncthreads();
+}
+
 // The stop rule's question for one part of a member: whether some pair of its vertices conflicts (partitioning: is cut).
 // The member's classes are bit masks in LDS, 64 vertices to a word, a piece of the words at a time, and vertex i's adjacency
 // to 64 vertices is one word (A is symmetric, so a wave reads 64 rows' words in one load): i conflicts with those of
@@ -1655,20 +1676,7 @@ __device__ __forceinline__ void legal_block(const GraphDev* __restrict__ gd, int
     if (tid == 0) *found = 0;
     for (int s0 = 0; s0 < strips; s0 += ss.words) {
         const int s1 = min(strips, s0 + ss.words);
-        for (int e = tid; e < k * ss.stride; e += 256) msk[e] = 0ull;
-        __syncthreads();
-        for (int v0 = 64 * s0 + tid; v0 < min(n, 64 * s1); v0 += 256 * 4) {
-            int x[4];
-#pragma unroll
-            for (int u = 0; u < 4; ++u) x[u] = v0 + 256 * u < min(n, 64 * s1) ? (int)c[v0 + 256 * u] : -1;
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const int v = v0 + 256 * u;
-                if (x[u] >= 0)
-                    atomicOr((uint32_t*)(msk + x[u] * ss.stride + (v >> 6) - s0) + ((v >> 5) & 1), 1u << (v & 31));
-            }
-        }
-        __syncthreads();
+        class_masks(c, n, k, ss, s0, s1, msk);
         // this part's strips, the longest rows first; vertex i looks at the words up to its own
         for (int q = (strips - 1 - part) / parts - wave; q >= 0; q -= 4) {
             const int strip = part + q * parts;
@@ -1694,67 +1702,55 @@ __device__ __forceinline__ void legal_block(const GraphDev* __restrict__ gd, int
     if (tid == 0) legal_vote(d, st, m, parts + (prob_added(d.problem) ? 1 : 0), *found != 0);
 }
 
-// even bits of x to the low half, odd bits to the high half
-__device__ __forceinline__ uint32_t unshuffle(uint32_t x) {
-    uint32_t t = (x ^ (x >> 1)) & 0x22222222u;
-    x ^= t ^ (t << 1);
-    t = (x ^ (x >> 2)) & 0x0C0C0C0Cu;
-    x ^= t ^ (t << 2);
-    t = (x ^ (x >> 4)) & 0x00F000F0u;
-    x ^= t ^ (t << 4);
-    t = (x ^ (x >> 8)) & 0x0000FF00u;
-    return x ^ t ^ (t << 8);
-}
-
-// 2 f_color without a contraction (one colour per vertex): a block takes 64 vertices i of one member, one
-// per lane, and each of its waves a quarter of the vertices j, of which it counts the neighbours of i with i's colour.  Lane i's adjacency to 64
-// vertices is one word (A is symmetric), their colours come two to a scalar word; a pair of colours
-// takes four instructions: (c_i ^ c_j) + 0x7fff7fff sets bits 15 and 31 where they differ, the complemented adjacency
-// bits of the two vertices are shifted onto the same bits, and a masked population count adds the pairs that are no
-// conflict.  n^2 D compares, the same time for any colouring.
-// n = 2999, k = 211, D = 25: 25 us for the launch against 12 (expansion) + 38 (contraction) + 8 us; n = 1000,
-// k = 90, D = 64: 10.7 against 8.5 + 16 + 4 us.
+// 2 f_color without a contraction (one colour per vertex): each wave of a block takes 64 vertices of one member and
+// counts, as the search above looks, the vertices that a word of A and the class's word of masks both hold.  Words before the vertices'
+// own count twice, for the pair's other end.
+// Launch with the member blocks: n = 2999, k = 211, D = 25 12.2 us, n = 1000, k = 90, D = 64 5.1 us (the compares of every pair of
+// colours, two to a register, 25 and 10.7; the contraction and its expansion 50 and 24).
 __device__ __forceinline__ void conflict_block(const GraphDev* __restrict__ gd, int G, int b, int gsel, int* sh) {
     const int g = find_graph(gd, G, b, [](const GraphDev& x) { return x.cf_begin; });
     if (gsel >= 0 && g != gsel) return;
     const GraphDev& d = gd[g];
-    const int n = d.n;
-    const int strips = (n + 63) / 64;
+    const int n = d.n, k = d.k;
+    const int strips = (n + 63) / 64, parts = count_parts(n);
     const int loc = b - d.cf_begin;
-    const int m = loc / strips, strip = loc - m * strips;
-    const int part = (strips + 3) / 4;
-    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    const int s0 = min(strips, wave * part), s1 = min(strips, s0 + part);
+    const int m = loc / parts, part = loc - m * parts;
     const int lane = threadIdx.x & 63;
-    const int i = strip * 64 + lane;
-    const int16_t* __restrict__ c = d.c[d.st->pS] + (size_t)m * d.cs;
-    const uint32_t ci = (uint16_t)gview(c)[i];      // rows are padded to 64 entries
-    const uint32_t ci2 = ci | (ci << 16);
-    const unsigned long long* __restrict__ Ab = d.Ab + i;
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const ScanShape ss = scan_shape(n, k);
+    unsigned long long* msk = (unsigned long long*)(sh + kScanHead);
+    const auto* __restrict__ c = gview((const int16_t*)d.c[d.st->pS]) + (size_t)m * d.cs;
     const size_t n_pad = d.n_pad;
-    typedef const __attribute__((address_space(4))) uint32_t* scalar_ptr;
-    int none = 0;
-    unsigned long long a = s0 < s1 ? gview(Ab)[(size_t)s0 * n_pad] : 0ull;
-    for (int s = s0; s < s1; ++s) {
-        const unsigned long long an = s + 1 < s1 ? gview(Ab)[(size_t)(s + 1) * n_pad] : 0ull;
-        const uint32_t lo = ~unshuffle((uint32_t)a), hi = ~unshuffle((uint32_t)(a >> 32));
-        const scalar_ptr cw = (scalar_ptr)(c + 64 * s);
+    const int last = part + (strips - 1 - part) / parts * parts;    // the block's last strip
+    const int strip = part + wave * parts;                          // past the last: none
+    const int i = strip * 64 + lane;
+    const int ci = i < n ? (int)c[i] : 0;
+    const auto* __restrict__ a = gview(d.Ab) + min(strip, strips - 1) * 64 + lane;
+    int below = 0, own = 0;
+    for (int s0 = 0; s0 <= last; s0 += ss.words) {
+        const int s1 = min(strips, s0 + ss.words);
+        if (s0) __syncthreads();
+        class_masks(c, n, k, ss, s0, s1, msk);
+        if (strip > last) continue;
+        const unsigned long long* row = msk + ci * ss.stride - s0;
+        const int e = min(s1, strip);
+        for (int s = s0; s < e; s += 8) {
+            unsigned long long w[8];
 #pragma unroll
-        for (int w = 0; w < 16; ++w) {
-            const uint32_t y = ((ci2 ^ cw[w]) + 0x7fff7fffu) | (lo << (15 - w));
-            const uint32_t z = ((ci2 ^ cw[16 + w]) + 0x7fff7fffu) | (hi << (15 - w));
-            none += __builtin_popcount(y & 0x80008000u);
-            none += __builtin_popcount(z & 0x80008000u);
+            for (int u = 0; u < 8; ++u) w[u] = s + u < e ? a[(size_t)(s + u) * n_pad] : 0ull;
+#pragma unroll
+            for (int u = 0; u < 8; ++u)
+                if (s + u < e) below += __popcll(w[u] & row[s + u]);
         }
-        a = an;
+        if (strip >= s0 && strip < s1) own = __popcll(a[(size_t)strip * n_pad] & row[strip]);
     }
-    int f = i < n ? 64 * (s1 - s0) - none : 0;
+    int f = 2 * below + own;
     for (int o = 32; o >= 1; o >>= 1) f += __shfl_xor(f, o);
     // one add per block, spread over the member's slots (the fitness folds them): adds of every wave to the
     // members' counters, a few cache lines, took longer than the counting
     if (lane == 0) sh[wave] = f;
     __syncthreads();
-    if (threadIdx.x == 0) atomicAdd(&d.f2p[(size_t)m * kF2Slots + (strip & (kF2Slots - 1))], sh[0] + sh[1] + sh[2] + sh[3]);
+    if (threadIdx.x == 0) atomicAdd(&d.f2p[(size_t)m * kF2Slots + (part & (kF2Slots - 1))], sh[0] + sh[1] + sh[2] + sh[3]);
 }
 
 // First launch of a merged iteration: everything that depends only on the colours, in blocks of
