@@ -2272,17 +2272,16 @@ __global__ __launch_bounds__(256) void k_loss(const GraphDev* __restrict__ gd, i
     }
 }
 
-// Report of one graph for tcol_conflicts: the first block takes the fitness of every graph
-// (kFlagReport; fold as in k_loss) and copies graph g's out, the others copy its colours.
+// Report of one graph for tcol_conflicts: the first G blocks take the fitness of a graph each (kFlagReport; fold as in
+// k_loss), graph g's copies it out, the others copy its colours.
 __global__ __launch_bounds__(256) void k_report(const GraphDev* __restrict__ gd, int G, int g, int fold, int16_t* colors,
                                                 int64_t* fcol, int64_t* feq) {
     __shared__ int best;
     const GraphDev& d = gd[g];
-    if (blockIdx.x == 0) {
-        for (int x = 0; x < G; ++x) {
-            fitness_graph(gd, x, 0, kFlagReport | fold, &best);
-            __syncthreads();
-        }
+    if ((int)blockIdx.x < G) {
+        fitness_graph(gd, blockIdx.x, 0, kFlagReport | fold, &best);
+        if ((int)blockIdx.x != g) return;
+        __syncthreads();
         for (int m = threadIdx.x; m < d.D; m += 256) {
             if (fcol) fcol[m] = d.fcol[m];
             if (feq) feq[m] = d.feq[m];
@@ -2291,8 +2290,8 @@ __global__ __launch_bounds__(256) void k_report(const GraphDev* __restrict__ gd,
     }
     if (!colors) return;
     const int16_t* __restrict__ c = d.c[d.st->pS];
-    const size_t total = (size_t)d.D * d.n, step = (size_t)(gridDim.x - 1) * 256;
-    for (size_t e = (size_t)(blockIdx.x - 1) * 256 + threadIdx.x; e < total; e += step) {
+    const size_t total = (size_t)d.D * d.n, step = (size_t)(gridDim.x - G) * 256;
+    for (size_t e = (size_t)(blockIdx.x - G) * 256 + threadIdx.x; e < total; e += step) {
         const size_t m = e / d.n;
         colors[e] = c[m * d.cs + (e - m * d.n)];
     }
@@ -2706,7 +2705,7 @@ hipError_t launch_loss(const GraphDev* gd, int G, int g, int ntiles, int fold, d
 }
 
 hipError_t launch_report(const GraphDev* gd, int G, int g, int fold, int16_t* colors, int64_t* fcol, int64_t* feq, hipStream_t s) {
-    hipLaunchKernelGGL(k_report, dim3(257), dim3(256), 0, s, gd, G, g, fold, colors, fcol, feq);
+    hipLaunchKernelGGL(k_report, dim3(G + 256), dim3(256), 0, s, gd, G, g, fold, colors, fcol, feq);
     TCOL_LAUNCH_CHECK();
     return hipSuccess;
 }

@@ -95,3 +95,15 @@ def test_conflicts_of_few_colours(n, k, D):
         s.close()
     assert np.array_equal(*out)
     assert us[0] < 1.1 * us[1], us
+
+
+def test_conflicts_of_one_graph_of_a_batch():
+    """conflicts() on a context of 128 small graphs: the graphs' fitness side by side.  Against the loss without gradients,
+    which has the same launches and a block per graph (one block for all of them took 2.7 us a graph)."""
+    s = solver(100, 10, 8, FP4, G=128)
+    a = us_of(lambda: s.conflicts(3))
+    b = us_of(lambda: s.loss_grad(3, want_gs=False, want_gw=False))
+    f = host(s.conflicts(3)[1]).sum()
+    assert f == host(s.loss_grad(3)[0])[1]
+    s.close()
+    assert a < 1.5 * b, (a, b)
