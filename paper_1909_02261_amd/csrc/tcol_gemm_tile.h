@@ -561,7 +561,7 @@ __device__ __forceinline__ void gemm_tile(const GraphDev* __restrict__ gd, int g
 
     const size_t ld = op_row_bytes(PREC, d.n_pad);
     // stages up to the last vertex (the operands are zero from n to n_pad)
-    const int nst = ceil_div(n, (int)(d.n_pad * (size_t)kStageRowBytes / ld));
+    const int nst = ceil_div(n, PREC == kPrecFP32 ? kStageRowBytes / 4 : 2 * kStageRowBytes);
 
     // per-lane columns: member and colour of each 16-column subtile
     int cm[NTW], cl[NTW];
