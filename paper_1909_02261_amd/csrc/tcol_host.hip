@@ -360,6 +360,34 @@ static bool pick_sparse(int kmax, int dmax, int nmax, int& PM, int& threads) {
     return false;
 }
 
+// Whether the class-row sums are the faster way to the gradients of fp32 graphs, by estimates in us fitted to iterations of
+// n = 125 to 12000, k = 1 to 400, D = 1 to 64.
+// The contraction: the K-sweeps of one tile, or the matrix instructions at 114 TFLOP/s, then G written and read and a
+// launch more.
+// The sums: P read twice for every member at what its size leaves of the caches' bandwidth, or the rounds of resident
+// blocks, each as long as the wave with the most to walk (its lists twice, and a time per class).  That wave has an eighth of the
+// vertices or one class, or all of them in the iterations after a smoothing that leave every vertex in one class; these count
+// for a fifth (the usual smoothing period is 5).
+// An iteration by sums and by contraction, us: n = 1000, D = 20, k = 100 38 and 105; n = 4000, D = 20, k = 2 234 and 199,
+// k = 14 174 and 323; n = 8000, D = 10, k = 3 486 and 426; n = 300, D = 4, k = 400 57 and 39.
+static bool rows_preferred(const tcol_ctx* c) {
+    double sweep = 0.0, mfma = 0.0, weights = 0.0, bytes = 0.0, even = 0.0, one = 0.0;
+    long long blocks = 0;
+    for (auto& p : c->params) {
+        const double n = p.n, pairs = n * n * p.D, entry = p.n <= 9000 ? 0.02 : 0.03;
+        sweep = std::max(sweep, 0.03 * n);
+        mfma += 3.5e-8 * pairs * p.k;
+        weights += 8.0 * n * p.k * p.D / 4.7e6;
+        bytes += 8e-6 * pairs / (p.n <= 9000 ? 20.0 : 5.0);
+        even = std::max(even, entry * n / std::min(p.k, 8) + 0.056 * p.k);
+        one = std::max(one, entry * n + 0.056 * p.k);
+        blocks += (long long)p.D * ceil_div(p.n, 64);
+    }
+    const double rounds = (double)((blocks + 511) / 512);
+    const double sums = 0.8 * std::max(bytes, rounds * even) + 0.2 * std::max(bytes, rounds * one);
+    return sums <= std::max(sweep, mfma) + weights + 2.0;
+}
+
 static int path_of(const tcol_ctx* c);
 static bool merged(const tcol_ctx* c);
 // 64 x 64 group-concentration tiles from which they are used at any n: four per CU
@@ -560,9 +588,9 @@ static tcol_status rebuild_schedule(tcol_ctx* c) {
         mt_tiling(c->layouts[g], c->params[g].n, c->layouts[g].n_pad > 2048 || t64 >= kMtFill ? 64 : 32);
     // class-row sums: fp32 operands, one colour per vertex, a row in registers (which also keeps a block's 64
     // gradient rows within its LDS), P's row offsets in 32 bits, and finite tables (the adjacency is the sign of an
-    // entry times t, which 0 times infinity loses); beyond that the fp32 contraction
+    // entry times t, which 0 times infinity loses), where they are the faster way; beyond that the fp32 contraction
     c->rows = common_op(c) == kPrecFP32 && !c->any_mcol && c->tables_finite && update_rows_kpl(c->kmax) > 0 &&
-              class_rows_lds(c->kmax) <= (size_t)kMaxBlockLds && c->nmax <= 16384;
+              class_rows_lds(c->kmax) <= (size_t)kMaxBlockLds && c->nmax <= 16384 && rows_preferred(c);
     c->cr_lds = c->rows ? class_rows_lds(c->kmax) : 0;
     if (c->rows) HIPCHK(class_rows_prepare(c->kmax, c->update_var));
     c->total_ps = ps_k > 0 ? 1 : 0;   // merged() asks whether there are any; counted below

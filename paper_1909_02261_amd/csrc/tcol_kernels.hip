@@ -2029,12 +2029,18 @@ __global__ __launch_bounds__(256) void k_update_rows(const GraphDev* __restrict_
 // load, two instructions to count and one to add; the next class is loaded while one is summed.  The block's
 // eight waves share the colours by eighths of the list; the 64 gradient rows meet in LDS and the same block takes the row
 // update (or writes the gradients).
+// With all vertices in one class (n = 1000, k = 85, D = 48) an iteration takes 82 us, 172 before a wave's walks of a long class were
+// pipelined and the block counted a large one together.
 // n = 500, k = 50, D = 64: 16 us per launch against 44 us (contraction) + 8 us (row update) before, n = 125, k = 18,
 // D = 8 7.6 against 16 + 3.7 us; gradients at n = 1000, k = 85, D = 48 41 against 162 + 11 us.  (A first form, with the
 // adjacency from bit masks and lists in LDS, two walks and a check per entry, took 26, 10.6 and 49 us.)
 //
 // mode 0: step (merged iteration); 1: gS / gW of graph gsel and 2 f_color.
 constexpr int kCrThreads = 512;
+// entries of a class's list beyond which its walks are pipelined through the list, and beyond which, when that is half as much
+// again as a wave's share, the block counts it together (a class within the share is counted by its wave, whose sum then finds its
+// rows in the caches: n = 8000, k = 14, D = 4 306 us an iteration against 459); and the entries that walking a class costs by itself
+constexpr int kCrLong = 144, kCrLarge = 256, kCrClass = 16;
 template <int KPL, int VAR>
 __global__ __launch_bounds__(kCrThreads) __attribute__((amdgpu_waves_per_eu(KPL <= 8 ? 4 : 2))) void k_class_rows(const GraphDev* __restrict__ gd, int G, int total_blocks,
                                                            int honor_stop, int mode, int gsel, float* __restrict__ gS_out,
@@ -2068,8 +2074,9 @@ __global__ __launch_bounds__(kCrThreads) __attribute__((amdgpu_waves_per_eu(KPL 
     const bool pen = (d.lambda * tf != 0.0f) || (d.mu * tf != 0.0f);
     const uint32_t sign = prob_partition(d.problem) ? 0x80000000u : 0u;
     // the row update's rows: 16 lanes each, two rows per group of lanes; where they fit in registers
-    // their loads go out now, behind the sums
-    constexpr bool AHEAD = KPL <= 4 && VAR == 0;
+    // their loads go out now, behind the sums (at KPL = 4 they spill: n = 500, k = 50, D = 64 211 us for eight iterations, 204.5
+    // without)
+    constexpr bool AHEAD = KPL <= 2 && VAR == 0;
     const RowCtx x = row_ctx(d, t);
     const int l16 = tid & 15, g16 = tid >> 4;
     constexpr int NG = kCrThreads / 16, NR = 64 / NG;
@@ -2091,17 +2098,21 @@ __global__ __launch_bounds__(kCrThreads) __attribute__((amdgpu_waves_per_eu(KPL 
     const scalar_ptr off = (scalar_ptr)co;
     const scalar_ptr lst = (scalar_ptr)(d.cls_j + (size_t)m * d.js);
     const char* __restrict__ Pc = (const char*)d.Pop + (size_t)strip * 256;
-    // this wave's colours: those whose list starts in its eighth
+    // this wave's colours: those with their middle in its eighth of the work (the entries of the lists, and for each class
+    // what kCrClass entries cost); and whether some class is large
     int l0 = 0, l1 = 0;
+    bool large = false;
+    const int large_from = max(kCrLarge, 3 * (int)off[k] / (2 * NW));
     {
-        const long long T = off[k];
+        const int T = (int)off[k] + kCrClass * k;
         for (int lb = 0; lb < k; lb += 64) {
             const int l = lb + lane;
-            const long long o = l < k ? (long long)NW * (gview(co)[l] & ~3) : (long long)1 << 40;
+            const int o0 = gview(co)[min(l, k)] & ~3, o1 = gview(co)[min(l + 1, k)] & ~3;
+            const int o = l < k ? NW / 2 * (o0 + o1 + kCrClass * (2 * l + 1)) : 1 << 30;
             l0 += __popcll(__ballot(o < wave * T));
             l1 += __popcll(__ballot(o < (wave + 1) * T));
+            large |= __any(o1 - o0 > large_from);
         }
-        if (wave == NW - 1) l1 = k;      // and the empty classes at the end
         l0 = __builtin_amdgcn_readfirstlane(l0);
         l1 = __builtin_amdgcn_readfirstlane(l1);
     }
@@ -2137,16 +2148,94 @@ __global__ __launch_bounds__(kCrThreads) __attribute__((amdgpu_waves_per_eu(KPL 
             }
         return acc;
     };
+    // the same 16 loads in a long class, whose list entries come 64 at a time, a lane each, ahead of their use (lv: those
+    // from the walk's position on; past its end the row of zeros, which stays in the caches).  Without conditions, so that a
+    // wait for one piece leaves the next in flight
+    const uint32_t* __restrict__ cj = d.cls_j + (size_t)m * d.js;
+    const uint32_t zero_row = 4u * (uint32_t)d.n_pad * (uint32_t)d.n_pad;
+    auto entries = [&](int q, int e) {
+        const uint32_t x = gview(cj)[min(q + lane, e - 1)];
+        return q + lane < e ? x : zero_row;
+    };
+    auto load_at = [&](float (&v)[16], uint32_t lv, int at) {
+#pragma unroll
+        for (int u = 0; u < 16; ++u)
+            v[u] = gview((const float*)(Pc + (uint32_t)__builtin_amdgcn_readlane((int)lv, at + u)))[lane];
+    };
+    auto groups = [](int entries) { return max(0, min(4, entries >> 2)); };
+    // edges of the entries [p, e), by this wave
+    auto count_walk = [&](int p, int e) {
+        float v[16], w[16];
+        int c = 0;
+        if (p >= e) return c;
+        uint32_t lv = entries(p, e);
+        load_at(v, lv, 0);
+        for (int q = p; q < e; q += 64) {
+            const uint32_t next = entries(q + 64, e);
+            load_at(w, lv, 16);
+            c = edges(v, groups(e - q), c);
+            load_at(v, lv, 32);
+            c = edges(w, groups(e - q - 16), c);
+            load_at(w, lv, 48);
+            c = edges(v, groups(e - q - 32), c);
+            load_at(v, next, 0);
+            c = edges(w, groups(e - q - 48), c);
+            lv = next;
+        }
+        return c;
+    };
+    if (large) {
+        // the block's waves count a large class together, a piece each, into its place among the gradient rows
+        auto each_large = [&](auto f) {
+            for (int lb = 0; lb < k; lb += 64) {
+                const int l = lb + lane;
+                unsigned long long b = __ballot((gview(co)[min(l + 1, k)] & ~3) - (gview(co)[min(l, k)] & ~3) > large_from);
+                for (; b; b &= b - 1) f(lb + __builtin_ctzll(b));
+            }
+        };
+        if (wave == 0) each_large([&](int l) { ((int*)Gl)[l] = 0; });
+        __syncthreads();
+        each_large([&](int l) {
+            const int p = (int)off[l] & ~3, e = (int)off[l + 1] & ~3;
+            const int piece = ((e - p) / 4 + NW - 1) / NW * 4;
+            const int q = p + wave * piece;
+            atomicAdd((int*)Gl + l, count_walk(min(q, e), min(q + piece, e)));
+        });
+        __syncthreads();
+    }
     // class l in v (its first 16 entries), entries [p, e), of which the last `pads` are padding (counted as edges
     // by their sign, so taken off)
     auto finish = [&](float (&v)[16], int l, int p, int e, int pads) {
+        if (e - p > kCrLong) {
+            const int c = (e - p > large_from ? ((const int*)Gl)[l] : count_walk(p, e)) - pads;
+            if (mode != 0 && own_c == l) own = c;
+            float acc = (float)c;
+            if (pen) {
+                float w[16];
+                uint32_t lv = entries(p, e);
+                for (int q = p; q < e; q += 64) {
+                    const uint32_t next = entries(q + 64, e);
+                    load_at(w, lv, 16);
+                    acc = add(v, groups(e - q), acc);
+                    load_at(v, lv, 32);
+                    acc = add(w, groups(e - q - 16), acc);
+                    load_at(w, lv, 48);
+                    acc = add(v, groups(e - q - 32), acc);
+                    load_at(v, next, 0);
+                    acc = add(w, groups(e - q - 48), acc);
+                    lv = next;
+                }
+            }
+            Gl[l] = acc;
+            return;
+        }
         int c = edges(v, min(4, (e - p) >> 2), -pads);
         if (e - p <= 16) {
             if (mode != 0 && own_c == l) own = c;
             Gl[l] = pen ? add(v, (e - p) >> 2, (float)c) : (float)c;
             return;
         }
-        // a large class: both walks two pieces deep
+        // both walks two pieces deep
         float w[16];
         for (int q = p + 16; q < e; q += 32) {
             load(v, q, min(4, (e - q) >> 2));

@@ -107,3 +107,19 @@ def test_conflicts_of_one_graph_of_a_batch():
     assert f == host(s.loss_grad(3)[0])[1]
     s.close()
     assert a < 1.5 * b, (a, b)
+
+
+@pytest.mark.parametrize("n,k,D,one", [(2000, 40, 8, True), (4000, 2, 20, False), (1000, 1, 8, True), (8000, 3, 8, False),
+                                       (300, 500, 4, False), (500, 50, 64, True)])
+def test_class_rows_of_few_or_large_classes(n, k, D, one):
+    """fp32 iterations where a class holds every vertex, where there are few classes, and where there are more than
+    vertices, against the plain schedule, whose contraction does not depend on the classes (a wave summing a whole class
+    by itself took up to 2.4 times)."""
+    cols = np.full((D, n), k // 2) if one else None
+    us = []
+    for fused in (0, 1):
+        s = solver(n, k, D, FP32, cols=cols)
+        s.set_options(fused=fused, penalty=1)
+        us.append(us_of(lambda: s.step(8)))
+        s.close()
+    assert us[1] < us[0], us
