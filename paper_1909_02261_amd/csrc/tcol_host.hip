@@ -450,6 +450,7 @@ static void pick_merged_shape(tcol_ctx* c) {
         (c->opt.tile_bm && c->opt.tile_ntw))
         return;
     double best = 1e30;
+    GemmShape own = c->shape;       // of the contraction without the row update, where that is the choice
     for (auto& m : kMergedShapes)
         for (bool fuse : {true, false}) {
             if (!fuse && !shape_listed(m.bm, m.ntw)) continue;
@@ -457,16 +458,13 @@ static void pick_merged_shape(tcol_ctx* c) {
             const double cost = merged_cost(c, m, fuse, &kf);
             if (cost >= best || (fuse && (kf == 0 || !gemm_rows_built(m.bm, m.ntw, kf, c->update_var)))) continue;
             best = cost;
-            if (fuse) {
-                c->gr_bm = m.bm;
-                c->gr_ntw = m.ntw;
-                c->gr_k = kf;
-            } else {
-                c->gr_bm = 0;
-                c->shape.bm = m.bm;
-                c->shape.ntw = m.ntw;
-            }
+            c->gr_bm = fuse ? m.bm : 0;
+            c->gr_ntw = fuse ? m.ntw : 0;
+            c->gr_k = fuse ? kf : 0;
+            own.bm = m.bm;
+            own.ntw = m.ntw;
         }
+    if (!c->gr_bm) c->shape = own;
 }
 
 // The batch launch (fused = 3): whether it can run these graphs, and its item segments.  It

@@ -37,3 +37,15 @@ def test_named_tile_stays_named():
     s.set_options(fused=2)
     assert tile(s) == auto
     s.close()
+
+
+@pytest.mark.parametrize("n,k,D", [(1000, 90, 64), (500, 50, 64), (1000, 28, 128)])
+def test_shown_tile_is_the_one_of_the_storing_contractions(n, k, D):
+    """Where the contraction of an iteration takes the row update in a tile of its own, the tile shown, which the gradients and the
+    class conflicts take, is the choice for storing G: the plain schedule's."""
+    case = GraphCase("shown", KCOL, n, k, D, FP4, "gnp", 0.5, graph_seed=13, stop_on_legal=0)
+    s, _ = make_solver([case])
+    shown = tile(s)
+    s.set_options(fused=0)
+    assert tile(s) == shown
+    s.close()
