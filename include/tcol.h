@@ -226,8 +226,9 @@ tcol_status tcol_step(tcol_ctx *ctx, int32_t max_steps, int32_t *steps_done, int
 
 /* Steps 1-2 only, on the current W of graph g (W unchanged, t unchanged):
  *   colors_dev (D*n int16, may be NULL) argmax colours c_d(i);
- *   f_main_dev (D int64, may be NULL) main fitness per member: f_color, computed
- *              from the contraction A.S as 1/2 sum_i (A.S_d)[i, c_d(i)], or for
+ *   f_main_dev (D int64, may be NULL) main fitness per member: f_color, counted from the
+ *              bits of A and of the colour classes (multicolouring contexts: from the
+ *              contraction A.S as 1/2 sum_i (A.S_d)[i, c_d(i)]), or for
  *              partitioning the cut |E| - f_color;
  *   f_sec_dev  (D int64, may be NULL) added fitness per member: f_eq (ECP,
  *              balanced partitioning), the colour cost (minimum sum colouring)
@@ -286,7 +287,8 @@ tcol_status tcol_get_counters(tcol_ctx *ctx, int32_t g, int64_t *counts);
  * candidates are every instantiated tile shape under the plain schedule (when
  * the options ask for it, fused = 0), else under the fast and the epilogue
  * schedules, each with the per-iteration penalty choice and the two fixed
- * penalty routes (tcol_options.penalty 0, 1, 2).  W and t are restored after
+ * penalty routes (tcol_options.penalty 0, 1, 2), the fast schedule with the
+ * automatic tile (penalty 0 and 1), and the batch launch where the graphs can take it.  W and t are restored after
  * every candidate (the trial iterations count in tcol_get_counters).  The
  * result is cached for the process per device and per context signature (n, k,
  * D, precision, problem and momentum of every graph, and whether the plain
@@ -314,7 +316,11 @@ tcol_status tcol_cancel(tcol_ctx *ctx);
 /* Measurement utility.  Runs `steps` iterations of every graph eagerly (no
  * captured graph) with HIP events around each kernel on the context's stream
  * and writes the average milliseconds per iteration of each phase to
- * ms[TCOL_NPHASES]: 0 argmax colours, 1 class sizes, 2 one-hot S expansion,
+ * ms[TCOL_NPHASES].  The phases are those of the plain, fast or epilogue schedule as
+ * separate kernels; where tcol_step runs merged iterations (no graph on the sparse
+ * rows: one launch for all that depends on the colours, and for fp32 graphs the
+ * class-row sums in place of the contraction) their sum is not the time of its
+ * iteration, which a timed tcol_step gives.  Phases: 0 argmax colours, 1 class sizes, 2 one-hot S expansion,
  * 3 penalty (group concentration + dense operand, or the sparse rows, which on
  * the fast path run after the contraction and add their rows to G, or for the
  * graphs whose row update rides on them, update the rows themselves),

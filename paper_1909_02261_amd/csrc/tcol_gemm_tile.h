@@ -312,11 +312,11 @@ __device__ __forceinline__ void gemm_sweep(f32x4 (&acc)[tile_mt(BM)][NTW], const
 // bytes of each S^T row in fp4, whose 0/1 nibbles (1.0 = 0x2) become bf16 in registers
 // when the MFMAs need them.  They become 2.0 rather than 1.0: bf16 2.0 is 0x4000, a
 // single byte, so one shift-and-mask and one byte permute make each pair; the operand
-// P of an fp4 graph is stored halved (exact in bf16), so the products are unchanged.  This avoids a bf16 copy of S and quarters the S bytes
-// staged and read from LDS, so more stage buffers fit than the fp4 A.S sweep has.
+// P of an fp4 graph is stored halved (exact in bf16), so the products are unchanged.  This avoids a bf16 copy of S and
+// quarters the S bytes staged and read from LDS, so more stage buffers fit than the fp4 A.S sweep has.
 // A direct-to-LDS load of the S rows takes 32 rows of 32 bytes per wave, 16 bytes per lane;
-// word w of row r sits at slot w ^ (((r >> 3) & 1) << 2), so a fragment read (16 consecutive rows, one word each) touches 16 different banks
-// pairs.
+// word w of row r sits at slot w ^ (((r >> 3) & 1) << 2), so a fragment read (16 consecutive rows, one word each)
+// touches 16 different banks pairs.
 template <int BM, int NTW>
 struct PenTile {
     using T = Tile<BM, NTW>;

@@ -360,16 +360,16 @@ static bool pick_sparse(int kmax, int dmax, int nmax, int& PM, int& threads) {
     return false;
 }
 
-// Whether the class-row sums are the faster way to the gradients of fp32 graphs, by estimates in us fitted to iterations of
-// n = 125 to 12000, k = 1 to 400, D = 1 to 64.
+// Whether the class-row sums are the faster way to the gradients of fp32 graphs, by estimates in us fitted to
+// iterations of n = 125 to 12000, k = 1 to 400, D = 1 to 64.
 // The contraction: the K-sweeps of one tile, or the matrix instructions at 114 TFLOP/s, then G written and read and a
 // launch more.
 // The sums: P read twice for every member at what its size leaves of the caches' bandwidth, or the rounds of resident
-// blocks, each as long as the wave with the most to walk (its lists twice, and a time per class).  That wave has an eighth of the
-// vertices or one class, or all of them in the iterations after a smoothing that leave every vertex in one class; these count
-// for a fifth (the usual smoothing period is 5).
-// An iteration by sums and by contraction, us: n = 1000, D = 20, k = 100 38 and 105; n = 4000, D = 20, k = 2 234 and 199,
-// k = 14 174 and 323; n = 8000, D = 10, k = 3 486 and 426; n = 300, D = 4, k = 400 57 and 39.
+// blocks, each as long as the wave with the most to walk (its lists twice, and a time per class).  That wave has an
+// eighth of the vertices or one class, or all of them in the iterations after a smoothing that leave every vertex in
+// one class; these count for a fifth (the usual smoothing period is 5).
+// An iteration by sums and by contraction, us: n = 1000, D = 20, k = 100 38 and 105; n = 4000, D = 20, k = 2 234 and
+// 199, k = 14 174 and 323; n = 8000, D = 10, k = 3 486 and 426; n = 300, D = 4, k = 400 57 and 39.
 static bool rows_preferred(const tcol_ctx* c) {
     double sweep = 0.0, mfma = 0.0, weights = 0.0, bytes = 0.0, even = 0.0, one = 0.0;
     long long blocks = 0;
@@ -409,8 +409,8 @@ static bool rows_fit(const tcol_graph_params& p, int bn) { return p.k <= bn && 1
 // Estimated time in us of a merged iteration's contraction and row update with a shape; fuse: graphs
 // whose members fit the tiles are updated by the contraction.  Rounds of resident blocks (a last one that is
 // partly empty costs about a quarter), then either the epilogue's members one after the other at 2 us
-// each or 8 bytes per weight at 4.7 TB/s, whichever is more, or for graphs updated in their own launch 16 bytes per weight
-// and the launch.  Measured at k = 28, D = 128, n = 1000: 45.7 us with (64 x 128 tiles) against 55.6
+// each or 8 bytes per weight at 4.7 TB/s, whichever is more, or for graphs updated in their own launch 16 bytes per
+// weight and the launch.  Measured at k = 28, D = 128, n = 1000: 45.7 us with (64 x 128 tiles) against 55.6
 // without; at k = 20, D = 20, n = 200, where a tile's three members follow one another, 18.3 against 16.5.
 static double merged_cost(const tcol_ctx* c, const MergedShape& m, bool fuse, int* kf) {
     const int bn = gemm_bn(m.ntw);
@@ -807,8 +807,8 @@ static hipError_t enqueue_sparse_add(tcol_ctx* c, bool fitness, hipStream_t s) {
 }
 
 // one iteration on the fast path; c[pS] holds the colours of the current weights.  The
-// expansion reads only the colours, so its blocks ride on the class-size launch.  In a run of iterations the class-size launch
-// also ends the previous one (advance_prev), and only the last iteration launches its own
+// expansion reads only the colours, so its blocks ride on the class-size launch.  In a run of iterations the class-size
+// launch also ends the previous one (advance_prev), and only the last iteration launches its own
 // end (advance_own)
 static hipError_t enqueue_step_fast(tcol_ctx* c, bool advance_prev, bool advance_own, hipStream_t s) {
     HIPRET(launch_prep(c->ddesc, c->G, c->total_mem, c->prep_lds, 1, 0, c->total_ps > 0 ? 1 : 0,
@@ -1146,8 +1146,8 @@ tcol_status tcol_init(tcol_ctx** out, int32_t G, const tcol_graph_params* p, con
         std::vector<double> lka(nlut), lvb(nlut);
         for (int m = 0; m < nlut; ++m) {
             const double x = prob_partition(q.problem) ? (double)(q.D - m) : (double)m;
-            // without its weight a term is 0 whatever its exponent (free then: a negative one would give -0, a power that
-            // overflows NaN)
+            // without its weight a term is 0 whatever its exponent (free then: a negative one would give -0, a power
+            // that overflows NaN)
             lp[m] = q.lambda > 0.0f ? (float)(2.0 * q.alpha * q.lambda * pow0(x, (double)q.alpha - 1.0)) : 0.0f;
             lb[m] = q.mu > 0.0f ? (float)(2.0 * q.beta * q.mu * pow0(x, (double)q.beta - 1.0)) : 0.0f;
             if (!isfinite(lp[m]) || !isfinite(lb[m])) c->tables_finite = false;
@@ -1275,7 +1275,8 @@ tcol_status tcol_loss_grad(tcol_ctx* c, int32_t g, double* loss_dev, float* grad
     const bool grads = gradS_dev || gradW_dev;
     // without gradients the conflicts are all the sums that the loss needs
     const bool count = !grads && !c->any_mcol;
-    HIPCHK(enqueue_phase1(c, 0, 0, (grads ? 2 : 0) | 4, c->total_mt, kFlagLoss | kFlagForcePen, g, !c->rows && !count, c->stream, count));
+    HIPCHK(enqueue_phase1(c, 0, 0, (grads ? 2 : 0) | 4, c->total_mt, kFlagLoss | kFlagForcePen, g, !c->rows && !count,
+                          c->stream, count));
     if (c->rows && grads)
         HIPCHK(launch_class_rows(c->ddesc, c->G, c->total_cr, c->cr_lds, c->kmax, c->update_var, 0, 1, g, gradS_dev,
                                  gradW_dev, c->stream));

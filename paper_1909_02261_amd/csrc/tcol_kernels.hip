@@ -1424,9 +1424,9 @@ __host__ __device__ inline size_t member_lds_bytes(int k, int n) {
 }
 
 // One part's answer to whether member m is illegal: the parts of a member (the blocks of its conflict search and,
-// with an added fitness, its member block) add to one word, and the last of them, which sees that all have answered, clears it and
-// lists a member that none found illegal.  The word is the member's first conflict slot, which is zero between the
-// launches that use it.
+// with an added fitness, its member block) add to one word, and the last of them, which sees that all have answered,
+// clears it and lists a member that none found illegal.  The word is the member's first conflict slot, which is zero
+// between the launches that use it.
 __device__ __forceinline__ void legal_vote(const GraphDev& d, GraphState* st, int m, int parts, bool bad) {
     int* word = d.f2p + (size_t)m * kF2Slots;
     const int add = bad ? 0x10000 : 1;
@@ -1627,8 +1627,8 @@ __host__ __device__ inline size_t scan_lds_bytes(int n, int k) {
     return 4 * kScanHead + 8 * (size_t)k * scan_shape(n, k).stride;
 }
 
-// the class masks of words [s0, s1) of the vertices with colours c, by the block's 256 threads (which have read the last
-// ones before): msk[l * stride + w] holds the vertices of class l in word s0 + w
+// the class masks of words [s0, s1) of the vertices with colours c, by the block's 256 threads (which have read the
+// last ones before): msk[l * stride + w] holds the vertices of class l in word s0 + w
 template <typename C>
 __device__ __forceinline__ void class_masks(C c, int n, int k, ScanShape ss, int s0, int s1, unsigned long long* msk) {
     const int tid = threadIdx.x;
@@ -1648,13 +1648,13 @@ __device__ __forceinline__ void class_masks(C c, int n, int k, ScanShape ss, int
     __syncthreads();
 }
 
-// The stop rule's question for one part of a member: whether some pair of its vertices conflicts (partitioning: is cut).
-// The member's classes are bit masks in LDS, 64 vertices to a word, a piece of the words at a time, and vertex i's adjacency
-// to 64 vertices is one word (A is symmetric, so a wave reads 64 rows' words in one load): i conflicts with those of
-// them that both words hold.  n^2 / 128 words a member whatever its classes are, and a search that finds a pair ends at once,
-// which in all but the last iterations is in the first words.
-// Eight iterations with members one conflict from legal, D = 8 (fp4): n = 2700, k = 2 412 us, 384 without the stop rule; n = 5000,
-// k = 3 647 and 643.  A scan of the pairs of each class, byte by byte, took 9350 and 22040 there.
+// The stop rule's question for one part of a member: whether some pair of its vertices conflicts (partitioning: is
+// cut). The member's classes are bit masks in LDS, 64 vertices to a word, a piece of the words at a time, and vertex
+// i's adjacency to 64 vertices is one word (A is symmetric, so a wave reads 64 rows' words in one load): i conflicts
+// with those of them that both words hold.  n^2 / 128 words a member whatever its classes are, and a search that finds
+// a pair ends at once, which in all but the last iterations is in the first words.
+// Eight iterations with members one conflict from legal, D = 8 (fp4): n = 2700, k = 2 412 us, 384 without the stop
+// rule; n = 5000, k = 3 647 and 643.  A scan of the pairs of each class, byte by byte, took 9350 and 22040 there.
 __device__ __forceinline__ void legal_block(const GraphDev* __restrict__ gd, int G, int b, int honor_stop, int adv, int want,
                                             int* sh) {
     const GraphDev& d = gd[find_graph(gd, G, b, [](const GraphDev& x) { return x.lg_begin; })];
@@ -1703,10 +1703,10 @@ __device__ __forceinline__ void legal_block(const GraphDev* __restrict__ gd, int
 }
 
 // 2 f_color without a contraction (one colour per vertex): each wave of a block takes 64 vertices of one member and
-// counts, as the search above looks, the vertices that a word of A and the class's word of masks both hold.  Words before the vertices'
-// own count twice, for the pair's other end.
-// Launch with the member blocks: n = 2999, k = 211, D = 25 12.2 us, n = 1000, k = 90, D = 64 5.1 us (the compares of every pair of
-// colours, two to a register, 25 and 10.7; the contraction and its expansion 50 and 24).
+// counts, as the search above looks, the vertices that a word of A and the class's word of masks both hold.  Words
+// before the vertices' own count twice, for the pair's other end.
+// Launch with the member blocks: n = 2999, k = 211, D = 25 12.2 us, n = 1000, k = 90, D = 64 5.1 us (the compares of
+// every pair of colours, two to a register, 25 and 10.7; the contraction and its expansion 50 and 24).
 __device__ __forceinline__ void conflict_block(const GraphDev* __restrict__ gd, int G, int b, int gsel, int* sh) {
     const int g = find_graph(gd, G, b, [](const GraphDev& x) { return x.cf_begin; });
     if (gsel >= 0 && g != gsel) return;
@@ -1755,12 +1755,14 @@ __device__ __forceinline__ void conflict_block(const GraphDev* __restrict__ gd, 
 
 // First launch of a merged iteration: everything that depends only on the colours, in blocks of
 // several kinds: the members (class sizes, lists), the search for legal members, the group-concentration tiles with the
-// penalty operand, the expansion of S^T, and (where they are asked for) the conflict counts.  As three launches of 4-5 us each they were most of a
-// small graph's iteration.  t stays as it is here (the launch that updates the weights advances
-// it), so the tiles may read it; a pending non-finite update ends the graph (adv).
+// penalty operand, the expansion of S^T, and (where they are asked for) the conflict counts.  As three launches of 4-5
+// us each they were most of a small graph's iteration.  t stays as it is here (the launch that updates the weights
+// advances it), so the tiles may read it; a pending non-finite update ends the graph (adv).
 // Held to 64 registers (eight waves per SIMD, no spills; 95 without): the blocks of the later kinds start
-// beside the tiles instead of after them (16 graphs, 10 iterations: 4608 -> 4538 us).  With the search for legal members
-// (LEGAL: contexts with a stop rule) the same bound spills in the tiles, so that variant takes seven.
+// beside the tiles instead of after them (16 graphs, 10 iterations: 4608 -> 4538 us).  The search for legal members
+// (LEGAL: contexts with a stop rule) is a variant, since its code costs the tiles registers (eight iterations of
+// n = 5000, k = 3, D = 8 without a stop rule: 601 us, 637 with the search in the same kernel); it takes seven waves
+// (n = 1000, k = 28, D = 128: 398.5 us for eight iterations, 401.7 at eight waves).
 template <int LEGAL>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(LEGAL ? 7 : 8))) void k_phase1(
     const GraphDev* __restrict__ gd, int G, int total_mem, int total_mt, int total_ex, int total_cf, int total_lg,
@@ -2021,30 +2023,31 @@ __global__ __launch_bounds__(256) void k_update_rows(const GraphDev* __restrict_
 //   G[d, i, l] = sum_{j in class (d, l)} (a_ij + P_ij),
 // so a wave takes 64 vertices i of member d (one per lane) and walks the member's vertices j
 // grouped by colour: P is symmetric, so row j gives its 64 entries in one load, whose sign bits are the
-// adjacency (mtilde_tile).  n^2 D additions instead of the contraction's n^2 D k multiply-adds: at
-// the 157 TFLOP/s of the fp32 matrix instructions the additions win from k of about 4 up.  The counts
+// adjacency (mtilde_tile).  n^2 D additions instead of the contraction's n^2 D k multiply-adds at
+// the 157 TFLOP/s of the fp32 matrix instructions (rows_preferred says where the additions win).  The counts
 // come first, exactly, then the P_ij in FP32 one after the other in the order of the member's list, which is
 // the order of the fp32 contraction's accumulation: the same bits.  The list holds row offsets, read into scalar
 // registers, and each class is padded to a multiple of four with a row of zeros, so an entry costs one
 // load, two instructions to count and one to add; the next class is loaded while one is summed.  The block's
-// eight waves share the colours by eighths of the list; the 64 gradient rows meet in LDS and the same block takes the row
-// update (or writes the gradients).
-// With all vertices in one class (n = 1000, k = 85, D = 48) an iteration takes 82 us, 172 before a wave's walks of a long class were
-// pipelined and the block counted a large one together.
+// eight waves share the colours by eighths of the work; the 64 gradient rows meet in LDS and the same block takes the
+// row update (or writes the gradients).
+// With all vertices in one class (n = 1000, k = 85, D = 48) an iteration takes 82 us, 172 before a wave's walks of a
+// long class were pipelined and the block counted a large one together.
 // n = 500, k = 50, D = 64: 16 us per launch against 44 us (contraction) + 8 us (row update) before, n = 125, k = 18,
-// D = 8 7.6 against 16 + 3.7 us; gradients at n = 1000, k = 85, D = 48 41 against 162 + 11 us.  (A first form, with the
+// D = 8 7.6 against 16 + 3.7 us; gradients at n = 1000, k = 85, D = 48 36 against 162 + 11 us.  (A first form, with the
 // adjacency from bit masks and lists in LDS, two walks and a check per entry, took 26, 10.6 and 49 us.)
 //
 // mode 0: step (merged iteration); 1: gS / gW of graph gsel and 2 f_color.
 constexpr int kCrThreads = 512;
-// entries of a class's list beyond which its walks are pipelined through the list, and beyond which, when that is half as much
-// again as a wave's share, the block counts it together (a class within the share is counted by its wave, whose sum then finds its
-// rows in the caches: n = 8000, k = 14, D = 4 306 us an iteration against 459); and the entries that walking a class costs by itself
+// entries of a class's list beyond which its walks are pipelined through the list, and beyond which, when that is half
+// as much again as a wave's share, the block counts it together (a class within the share is counted by its wave, whose
+// sum then finds its rows in the caches: n = 8000, k = 14, D = 4 367 us an iteration against 459); and the entries that
+// walking a class costs by itself
 constexpr int kCrLong = 144, kCrLarge = 256, kCrClass = 16;
 template <int KPL, int VAR>
-__global__ __launch_bounds__(kCrThreads) __attribute__((amdgpu_waves_per_eu(KPL <= 8 ? 4 : 2))) void k_class_rows(const GraphDev* __restrict__ gd, int G, int total_blocks,
-                                                           int honor_stop, int mode, int gsel, float* __restrict__ gS_out,
-                                                           float* __restrict__ gW_out) {
+__global__ __launch_bounds__(kCrThreads) __attribute__((amdgpu_waves_per_eu(KPL <= 8 ? 4 : 2))) void k_class_rows(
+    const GraphDev* __restrict__ gd, int G, int total_blocks, int honor_stop, int mode, int gsel,
+    float* __restrict__ gS_out, float* __restrict__ gW_out) {
     extern __shared__ __attribute__((aligned(16))) uint8_t cr_sh[];
     constexpr int NW = kCrThreads / 64;
     if ((int)blockIdx.x >= total_blocks) return;
@@ -2074,8 +2077,8 @@ __global__ __launch_bounds__(kCrThreads) __attribute__((amdgpu_waves_per_eu(KPL 
     const bool pen = (d.lambda * tf != 0.0f) || (d.mu * tf != 0.0f);
     const uint32_t sign = prob_partition(d.problem) ? 0x80000000u : 0u;
     // the row update's rows: 16 lanes each, two rows per group of lanes; where they fit in registers
-    // their loads go out now, behind the sums (at KPL = 4 they spill: n = 500, k = 50, D = 64 211 us for eight iterations, 204.5
-    // without)
+    // their loads go out now, behind the sums (at KPL = 4 they spill: n = 500, k = 50, D = 64 211 us for eight
+    // iterations, 204.5 without)
     constexpr bool AHEAD = KPL <= 2 && VAR == 0;
     const RowCtx x = row_ctx(d, t);
     const int l16 = tid & 15, g16 = tid >> 4;
@@ -2098,8 +2101,8 @@ __global__ __launch_bounds__(kCrThreads) __attribute__((amdgpu_waves_per_eu(KPL 
     const scalar_ptr off = (scalar_ptr)co;
     const scalar_ptr lst = (scalar_ptr)(d.cls_j + (size_t)m * d.js);
     const char* __restrict__ Pc = (const char*)d.Pop + (size_t)strip * 256;
-    // this wave's colours: those with their middle in its eighth of the work (the entries of the lists, and for each class
-    // what kCrClass entries cost); and whether some class is large
+    // this wave's colours: those with their middle in its eighth of the work (the entries of the lists, and for each
+    // class what kCrClass entries cost); and whether some class is large
     int l0 = 0, l1 = 0;
     bool large = false;
     const int large_from = max(kCrLarge, 3 * (int)off[k] / (2 * NW));
@@ -2148,9 +2151,9 @@ __global__ __launch_bounds__(kCrThreads) __attribute__((amdgpu_waves_per_eu(KPL 
             }
         return acc;
     };
-    // the same 16 loads in a long class, whose list entries come 64 at a time, a lane each, ahead of their use (lv: those
-    // from the walk's position on; past its end the row of zeros, which stays in the caches).  Without conditions, so that a
-    // wait for one piece leaves the next in flight
+    // the same 16 loads in a long class, whose list entries come 64 at a time, a lane each, ahead of their use (lv:
+    // those from the walk's position on; past its end the row of zeros, which stays in the caches).  Without
+    // conditions, so that a wait for one piece leaves the next in flight
     const uint32_t* __restrict__ cj = d.cls_j + (size_t)m * d.js;
     const uint32_t zero_row = 4u * (uint32_t)d.n_pad * (uint32_t)d.n_pad;
     auto entries = [&](int q, int e) {
@@ -2322,8 +2325,8 @@ __global__ void k_advance(const GraphDev* __restrict__ gd, int G) {
     advance_graph(gd[g].st);
 }
 
-// Fitness report of every graph (one block each), then (unless out is null) graph g's FP64 loss: L = sum main fitness + nu t sum added fitness + lambda t kappa
-// - mu t varpi (kappa, varpi from the group-concentration kernel's partials).
+// Fitness report of every graph (one block each), then (unless out is null) graph g's FP64 loss: L = sum main fitness +
+// nu t sum added fitness + lambda t kappa - mu t varpi (kappa, varpi from the group-concentration kernel's partials).
 // fold: kFlagFoldCounts where the conflicts are in the slots, else 0.
 __global__ __launch_bounds__(256) void k_loss(const GraphDev* __restrict__ gd, int G, int g, int ntiles, int fold,
                                               double* __restrict__ out) {

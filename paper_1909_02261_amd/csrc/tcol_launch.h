@@ -48,9 +48,9 @@ int update_rows_kpl(int kmax);
 hipError_t launch_update_rows(const GraphDev* gd, int G, int row0, int total_rows, int kmax, int var, int honor_stop, int mode,
                               int gsel, float* gS_out, float* gW_out, int merged, hipStream_t s);
 // merged iterations: first launch (members, search for legal members, group-concentration tiles, expansion and conflict
-// blocks; want & 1: legality, & 2: class lists for the class-row sums, & 4: conflict counters cleared for the gather that
-// follows; lists: some graph needs its class lists), and the class-row sums with the row update (graphs with `rows`;
-// modes in k_class_rows)
+// blocks; want & 1: legality, & 2: class lists for the class-row sums, & 4: conflict counters cleared for the gather
+// that follows; lists: some graph needs its class lists), and the class-row sums with the row update (graphs with
+// `rows`; modes in k_class_rows)
 constexpr int kMaxBlockLds = 150 * 1024;
 size_t phase1_lds(int kmax, int nmax, int lists);
 hipError_t phase1_prepare();

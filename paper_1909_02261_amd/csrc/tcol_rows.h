@@ -214,8 +214,8 @@ __device__ __forceinline__ int row_step(RowRegs<KPL, VAR>& R, const RowClasses<K
 }
 
 // Multicolouring: the row's demand of colours from its updated weights (-INFINITY past k) in registers, as the colour
-// kernel's selection: one after the other the largest weight not yet taken, the lowest colour on ties (adding zero makes
-// -0 and 0 tie as they compare).  Slots past the demand take -1; slot 0 is also the vertex's colour.
+// kernel's selection: one after the other the largest weight not yet taken, the lowest colour on ties (adding zero
+// makes -0 and 0 tie as they compare).  Slots past the demand take -1; slot 0 is also the vertex's colour.
 template <int KPL>
 __device__ __forceinline__ void row_select(const GraphDev& d, const float (&wv)[KPL], int m, int i, int l16, int16_t* c) {
     const int k = d.k, CM = d.cmax, ci = d.dem[i];
