@@ -1761,7 +1761,7 @@ __device__ __forceinline__ void conflict_block(const GraphDev* __restrict__ gd, 
 // Held to 64 registers (eight waves per SIMD, no spills; 95 without): the blocks of the later kinds start
 // beside the tiles instead of after them (16 graphs, 10 iterations: 4608 -> 4538 us).  The search for legal members
 // (LEGAL: contexts with a stop rule) is a variant, since its code costs the tiles registers (eight iterations of
-// n = 5000, k = 3, D = 8 without a stop rule: 601 us, 637 with the search in the same kernel); it takes seven waves
+// n = 2000, k = 28, D = 20 without a stop rule: 341 us, 349 with the search in the same kernel); it takes seven waves
 // (n = 1000, k = 28, D = 128: 398.5 us for eight iterations, 401.7 at eight waves).
 template <int LEGAL>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(LEGAL ? 7 : 8))) void k_phase1(

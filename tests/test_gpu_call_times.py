@@ -13,18 +13,20 @@ from gpu_util import host, torch_mod
 pytestmark = pytest.mark.gpu
 
 
-def us_of(f, reps=8):
-    """Microseconds a call, the least of five runs of `reps`."""
+def us_of(*calls, reps=10, rounds=9):
+    """Microseconds of each call, in turn over `rounds`, the least of its runs of `reps`."""
     torch = torch_mod()
-    f(), f()
-    best = float("inf")
-    for _ in range(5):
-        torch.cuda.synchronize()
-        t0 = time.perf_counter()
-        for _ in range(reps):
-            f()
-        torch.cuda.synchronize()
-        best = min(best, (time.perf_counter() - t0) / reps * 1e6)
+    best = [float("inf")] * len(calls)
+    for f in calls:
+        f(), f()
+    for _ in range(rounds):
+        for x, f in enumerate(calls):
+            torch.cuda.synchronize()
+            t0 = time.perf_counter()
+            for _ in range(reps):
+                f()
+            torch.cuda.synchronize()
+            best[x] = min(best[x], (time.perf_counter() - t0) / reps * 1e6)
     return best
 
 
@@ -70,16 +72,17 @@ def one_conflict(n, k, part):
 def test_stop_rule_of_nearly_legal_members(problem, n, k, D, prec):
     """Eight iterations with the stop rule on members one conflict away from legal against the same without it."""
     A, base = one_conflict(n, k, problem == KPART)
-    us = []
-    for stop in (0, 1):
-        s = solver(n, k, D, prec, cols=np.tile(base, (D, 1)), A=A, problem=problem, stop_on_legal=stop)
-        if problem == KPART:
+    ss = [solver(n, k, D, prec, cols=np.tile(base, (D, 1)), A=A, problem=problem, stop_on_legal=stop) for stop in (0, 1)]
+    if problem == KPART:
+        for s in ss:
             s.set_options(penalty=1)
-        assert s.conflicts(0)[1].tolist() == [1] * D
-        us.append(us_of(lambda: s.step(8)))
+    assert all(s.conflicts(0)[1].tolist() == [1] * D for s in ss)
+    us = us_of(lambda: ss[0].step(8), lambda: ss[1].step(8))
+    for s in ss:
         assert s.conflicts(0)[1].tolist() == [1] * D
         s.close()
     # (a scan of the pairs of the classes, one byte at a time, took 2.4 to 37 times)
+    print(us)
     assert us[1] < 1.35 * us[0] + 40, us
 
 
@@ -87,13 +90,12 @@ def test_stop_rule_of_nearly_legal_members(problem, n, k, D, prec):
 def test_conflicts_of_few_colours(n, k, D):
     """The conflict counts from the adjacency bits against the contraction's gather (a multicolouring context's) where the
     contraction has few columns (pair by pair they took 3.2 and 2.1 times its time)."""
-    out, us = [], []
-    for problem in (KCOL, MCOL):
-        s = solver(n, k, D, FP4, problem=problem)
-        us.append(us_of(lambda: s.conflicts(0)))
-        out.append(host(s.conflicts(0)[1]))
+    ss = [solver(n, k, D, FP4, problem=problem) for problem in (KCOL, MCOL)]
+    us = us_of(lambda: ss[0].conflicts(0), lambda: ss[1].conflicts(0), reps=40)
+    assert np.array_equal(*(host(s.conflicts(0)[1]) for s in ss))
+    for s in ss:
         s.close()
-    assert np.array_equal(*out)
+    print(us)
     assert us[0] < 1.1 * us[1], us
 
 
@@ -101,11 +103,11 @@ def test_conflicts_of_one_graph_of_a_batch():
     """conflicts() on a context of 128 small graphs: the graphs' fitness side by side.  Against the loss without gradients,
     which has the same launches and a block per graph (one block for all of them took 2.7 us a graph)."""
     s = solver(100, 10, 8, FP4, G=128)
-    a = us_of(lambda: s.conflicts(3))
-    b = us_of(lambda: s.loss_grad(3, want_gs=False, want_gw=False))
+    a, b = us_of(lambda: s.conflicts(3), lambda: s.loss_grad(3, want_gs=False, want_gw=False))
     f = host(s.conflicts(3)[1]).sum()
     assert f == host(s.loss_grad(3)[0])[1]
     s.close()
+    print(a, b)
     assert a < 1.5 * b, (a, b)
 
 
@@ -116,10 +118,11 @@ def test_class_rows_of_few_or_large_classes(n, k, D, one):
     vertices, against the plain schedule, whose contraction does not depend on the classes (a wave summing a whole class
     by itself took up to 2.4 times)."""
     cols = np.full((D, n), k // 2) if one else None
-    us = []
-    for fused in (0, 1):
-        s = solver(n, k, D, FP32, cols=cols)
+    ss = [solver(n, k, D, FP32, cols=cols) for _ in range(2)]
+    for fused, s in enumerate(ss):
         s.set_options(fused=fused, penalty=1)
-        us.append(us_of(lambda: s.step(8)))
+    us = us_of(lambda: ss[0].step(8), lambda: ss[1].step(8))
+    for s in ss:
         s.close()
+    print(us)
     assert us[1] < us[0], us
