@@ -611,7 +611,8 @@ static tcol_status rebuild_schedule(tcol_ctx* c) {
         d.cr_begin = cr;
         cr += p.D * ceil_div(p.n, 64);
         d.cf_begin = cf;
-        cf += conflict_blocks(p.D, p.n);
+        d.cf_words = conflict_words(p.D, p.n, p.k);
+        cf += conflict_blocks(p.D, p.n, d.cf_words);
         d.lg_begin = lg;
         if (p.stop_on_legal) lg += p.D * search_parts(p.n);
         d.ps_begin = pg;
@@ -1748,6 +1749,7 @@ extern "C" tcol_status tcol_conflicts_noalloc(const tcol_graph_params* p, const 
     d.W[0] = const_cast<float*>(W_dev);
     d.Ab = (const unsigned long long*)(base + L.aop);
     d.f2p = (int32_t*)(base + L.sop);
+    d.cf_words = conflict_words(p->D, p->n, p->k);
     d.c[0] = (int16_t*)(base + L.c);
     d.V[0] = (int32_t*)(base + L.V);
     d.cT = (int16_t*)(base + L.cT);
@@ -1767,7 +1769,8 @@ extern "C" tcol_status tcol_conflicts_noalloc(const tcol_graph_params* p, const 
     HIPCHK(launch_pack_graph(A_dev, p->n, L.n_pad, kPrecFP4, nullptr, const_cast<unsigned long long*>(d.Ab), nullptr,
                              (int*)(base + L.ones), ones, s));
     HIPCHK(launch_colors(gd, 1, total_rows, 0, s));
-    HIPCHK(launch_phase1(gd, 1, p->D, 0, 0, conflict_blocks(p->D, p->n), 0, phase1_lds(p->k, p->n, 0), 0, 0, 0, 0, -1, s));
+    HIPCHK(launch_phase1(gd, 1, p->D, 0, 0, conflict_blocks(p->D, p->n, d.cf_words), 0, phase1_lds(p->k, p->n, 0), 0, 0, 0,
+                         0, -1, s));
     HIPCHK(launch_report(gd, 1, 0, kFlagFoldCounts, colors_dev, f_main_dev, f_sec_dev, s));
     return TCOL_OK;
 }

@@ -1617,8 +1617,8 @@ constexpr int kScanHead = 16;   // ints before the masks
 __host__ __device__ inline ScanShape scan_shape(int n, int k) {
     constexpr int room = (kMtLds - 4 * kScanHead) / 8;
     const int all = (n + 63) / 64;
+    if (k * (all | 1) <= room) return {all, all | 1};
     int w = room / k;
-    if (w > all) w = all;
     if (w > 1 && !(w & 1) && k * (w + 1) > room) --w;
     if (w < 1) w = 1;
     return {w, w | 1};
@@ -1627,22 +1627,35 @@ __host__ __device__ inline size_t scan_lds_bytes(int n, int k) {
     return 4 * kScanHead + 8 * (size_t)k * scan_shape(n, k).stride;
 }
 
+// The conflict counts by these masks or by compares.  A piece of masks takes a block about 0.85 us whatever it holds;
+// the compares take about 0.07 us per 10^6 pairs, and more blocks.  tcol_conflicts, masks and compares, fp4:
+// n = 2000, k = 900, D = 16 (32 pieces) 58 and 34 us; k = 500 (7 pieces) 27.7 and 26.2, at D = 64 55 and 67;
+// n = 1000, k = 500, D = 16 (4 pieces) 18.3 and 16.8, at D = 64 33 and 35; n = 4000, k = 200, D = 16 (6 pieces) 30 and
+// 42.  One piece: n = 2000, k = 60, D = 64 26 and 44; n = 71, D = 16 3.9 and 3.4 (the launch).
+inline bool count_by_masks(int n, int D, ScanShape ss) {
+    return 2 * ceil_div(n, 64) <= ss.words * (1 + (long long)n * n * D / 6000000);
+}
+
 // the class masks of words [s0, s1) of the vertices with colours c, by the block's 256 threads (which have read the
 // last ones before): msk[l * stride + w] holds the vertices of class l in word s0 + w
 template <typename C>
 __device__ __forceinline__ void class_masks(C c, int n, int k, ScanShape ss, int s0, int s1, unsigned long long* msk) {
     const int tid = threadIdx.x;
+    const int end = min(n, 64 * s1);
+    int x[4];
+    auto load = [&](int v0) {
+#pragma unroll
+        for (int u = 0; u < 4; ++u) x[u] = c[min(v0 + 256 * u, end - 1)];
+    };
+    load(64 * s0 + tid);    // in flight while the masks are cleared
     for (int e = tid; e < k * ss.stride; e += 256) msk[e] = 0ull;
     __syncthreads();
-    const int end = min(n, 64 * s1);
     for (int v0 = 64 * s0 + tid; v0 < end; v0 += 256 * 4) {
-        int x[4];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) x[u] = v0 + 256 * u < end ? (int)c[v0 + 256 * u] : -1;
+        if (v0 >= 64 * s0 + 256 * 4) load(v0);
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
             const int v = v0 + 256 * u;
-            if (x[u] >= 0) atomicOr((uint32_t*)(msk + x[u] * ss.stride + (v >> 6) - s0) + ((v >> 5) & 1), 1u << (v & 31));
+            if (v < end) atomicOr((uint32_t*)(msk + x[u] * ss.stride + (v >> 6) - s0) + ((v >> 5) & 1), 1u << (v & 31));
         }
     }
     __syncthreads();
@@ -1706,18 +1719,11 @@ __device__ __forceinline__ void legal_block(const GraphDev* __restrict__ gd, int
 // counts, as the search above looks, the vertices that a word of A and the class's word of masks both hold.  Words
 // before the vertices' own count twice, for the pair's other end.
 // Launch with the member blocks: n = 2999, k = 211, D = 25 12.2 us, n = 1000, k = 90, D = 64 5.1 us (the compares of
-// every pair of colours, two to a register, 25 and 10.7; the contraction and its expansion 50 and 24).
-__device__ __forceinline__ void conflict_block(const GraphDev* __restrict__ gd, int G, int b, int gsel, int* sh) {
-    const int g = find_graph(gd, G, b, [](const GraphDev& x) { return x.cf_begin; });
-    if (gsel >= 0 && g != gsel) return;
-    const GraphDev& d = gd[g];
-    const int n = d.n, k = d.k;
-    const int strips = (n + 63) / 64, parts = count_parts(n);
-    const int loc = b - d.cf_begin;
-    const int m = loc / parts, part = loc - m * parts;
+// every pair of colours, below, 25 and 10.7; the contraction and its expansion 50 and 24).
+__device__ __forceinline__ int count_masks(const GraphDev& d, int m, int part, ScanShape ss, int* sh) {
+    const int n = d.n, k = d.k, strips = (n + 63) / 64, parts = count_parts(n);
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    const ScanShape ss = scan_shape(n, k);
     unsigned long long* msk = (unsigned long long*)(sh + kScanHead);
     const auto* __restrict__ c = gview((const int16_t*)d.c[d.st->pS]) + (size_t)m * d.cs;
     const size_t n_pad = d.n_pad;
@@ -1730,21 +1736,86 @@ __device__ __forceinline__ void conflict_block(const GraphDev* __restrict__ gd, 
     for (int s0 = 0; s0 <= last; s0 += ss.words) {
         const int s1 = min(strips, s0 + ss.words);
         if (s0) __syncthreads();
+        // the first words are in flight while the masks are made (past the strip's own they are not counted)
+        unsigned long long w[8];
+        auto load = [&](int s) {
+#pragma unroll
+            for (int u = 0; u < 8; ++u) w[u] = a[(size_t)min(s + u, strips - 1) * n_pad];
+        };
+        load(s0);
         class_masks(c, n, k, ss, s0, s1, msk);
         if (strip > last) continue;
         const unsigned long long* row = msk + ci * ss.stride - s0;
         const int e = min(s1, strip);
         for (int s = s0; s < e; s += 8) {
-            unsigned long long w[8];
-#pragma unroll
-            for (int u = 0; u < 8; ++u) w[u] = s + u < e ? a[(size_t)(s + u) * n_pad] : 0ull;
+            if (s > s0) load(s);
 #pragma unroll
             for (int u = 0; u < 8; ++u)
                 if (s + u < e) below += __popcll(w[u] & row[s + u]);
         }
         if (strip >= s0 && strip < s1) own = __popcll(a[(size_t)strip * n_pad] & row[strip]);
     }
-    int f = 2 * below + own;
+    return 2 * below + own;
+}
+
+// even bits of x to the low half, odd bits to the high half
+__device__ __forceinline__ uint32_t unshuffle(uint32_t x) {
+    uint32_t t = (x ^ (x >> 1)) & 0x22222222u;
+    x ^= t ^ (t << 1);
+    t = (x ^ (x >> 2)) & 0x0C0C0C0Cu;
+    x ^= t ^ (t << 2);
+    t = (x ^ (x >> 4)) & 0x00F000F0u;
+    x ^= t ^ (t << 4);
+    t = (x ^ (x >> 8)) & 0x0000FF00u;
+    return x ^ t ^ (t << 8);
+}
+
+// The same by compares, as fast for any number of classes: a block takes one strip of 64 vertices i, one per lane, and
+// each of its waves a quarter of the vertices j.  Lane i's adjacency to 64 vertices is one word, their colours come two
+// to a scalar word; a pair of colours takes four instructions: (c_i ^ c_j) + 0x7fff7fff sets bits 15 and 31 where they
+// differ, the complemented adjacency bits of the two vertices are shifted onto the same bits, and a masked population
+// count adds the pairs that are no conflict.
+__device__ __forceinline__ int count_compares(const GraphDev& d, int m, int strip) {
+    const int n = d.n, strips = (n + 63) / 64;
+    const int quarter = (strips + 3) / 4;
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int s0 = min(strips, wave * quarter), s1 = min(strips, s0 + quarter);
+    const int i = strip * 64 + (threadIdx.x & 63);
+    const int16_t* __restrict__ c = d.c[d.st->pS] + (size_t)m * d.cs;
+    const uint32_t ci = (uint16_t)gview(c)[i];      // rows are padded to 64 entries
+    const uint32_t ci2 = ci | (ci << 16);
+    const unsigned long long* __restrict__ Ab = d.Ab + i;
+    const size_t n_pad = d.n_pad;
+    typedef const __attribute__((address_space(4))) uint32_t* scalar_ptr;
+    int none = 0;
+    unsigned long long a = s0 < s1 ? gview(Ab)[(size_t)s0 * n_pad] : 0ull;
+    for (int s = s0; s < s1; ++s) {
+        const unsigned long long an = s + 1 < s1 ? gview(Ab)[(size_t)(s + 1) * n_pad] : 0ull;
+        const uint32_t lo = ~unshuffle((uint32_t)a), hi = ~unshuffle((uint32_t)(a >> 32));
+        const scalar_ptr cw = (scalar_ptr)(c + 64 * s);
+#pragma unroll
+        for (int w = 0; w < 16; ++w) {
+            const uint32_t y = ((ci2 ^ cw[w]) + 0x7fff7fffu) | (lo << (15 - w));
+            const uint32_t z = ((ci2 ^ cw[16 + w]) + 0x7fff7fffu) | (hi << (15 - w));
+            none += __builtin_popcount(y & 0x80008000u);
+            none += __builtin_popcount(z & 0x80008000u);
+        }
+        a = an;
+    }
+    return i < n ? 64 * (s1 - s0) - none : 0;
+}
+
+__device__ __forceinline__ void conflict_block(const GraphDev* __restrict__ gd, int G, int b, int gsel, int* sh) {
+    const int g = find_graph(gd, G, b, [](const GraphDev& x) { return x.cf_begin; });
+    if (gsel >= 0 && g != gsel) return;
+    const GraphDev& d = gd[g];
+    const int words = d.cf_words;
+    const bool masks = words != 0;
+    const int parts = masks ? count_parts(d.n) : (d.n + 63) / 64;
+    const int loc = b - d.cf_begin;
+    const int m = loc / parts, part = loc - m * parts;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    int f = masks ? count_masks(d, m, part, {words, words | 1}, sh) : count_compares(d, m, part);
     for (int o = 32; o >= 1; o >>= 1) f += __shfl_xor(f, o);
     // one add per block, spread over the member's slots (the fitness folds them): adds of every wave to the
     // members' counters, a few cache lines, took longer than the counting
@@ -1760,11 +1831,12 @@ __device__ __forceinline__ void conflict_block(const GraphDev* __restrict__ gd, 
 // advances it), so the tiles may read it; a pending non-finite update ends the graph (adv).
 // Held to 64 registers (eight waves per SIMD, no spills; 95 without): the blocks of the later kinds start
 // beside the tiles instead of after them (16 graphs, 10 iterations: 4608 -> 4538 us).  The search for legal members
-// (LEGAL: contexts with a stop rule) is a variant, since its code costs the tiles registers (eight iterations of
-// n = 2000, k = 28, D = 20 without a stop rule: 341 us, 349 with the search in the same kernel); it takes seven waves
-// (n = 1000, k = 28, D = 128: 398.5 us for eight iterations, 401.7 at eight waves).
-template <int LEGAL>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(LEGAL ? 7 : 8))) void k_phase1(
+// (contexts with a stop rule) and the counts (calls that report) are variants, since their code costs the tiles
+// registers (eight iterations of n = 2000, k = 28, D = 20 without a stop rule: 341 us, 349 with the search in the same
+// kernel); the search takes seven waves (n = 1000, k = 28, D = 128: 398.5 us for eight iterations, 401.7 at eight).
+constexpr int kPhase1Plain = 0, kPhase1Legal = 1, kPhase1Count = 2;
+template <int KIND>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(KIND == kPhase1Legal ? 7 : 8))) void k_phase1(
     const GraphDev* __restrict__ gd, int G, int total_mem, int total_mt, int total_ex, int total_cf, int total_lg,
     int honor_stop, int adv, int want, int mt_flags, int gsel) {
     extern __shared__ __attribute__((aligned(16))) int p1_sh[];
@@ -1774,7 +1846,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(LEGAL ? 7 :
         return;
     }
     b -= total_mem;
-    if constexpr (LEGAL != 0) {
+    if constexpr (KIND == kPhase1Legal) {
         if (b < total_lg) {
             legal_block(gd, G, b, honor_stop, adv, want, p1_sh);
             return;
@@ -1790,8 +1862,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(LEGAL ? 7 :
         expand_block(gd, G, b, honor_stop, 0, 1, adv);
         return;
     }
-    b -= total_ex;
-    if (b < total_cf) conflict_block(gd, G, b, gsel, p1_sh);
+    if constexpr (KIND == kPhase1Count) {
+        b -= total_ex;
+        if (b < total_cf) conflict_block(gd, G, b, gsel, p1_sh);
+    }
 }
 
 // ------------------------------------------------------- step 2, stop rule -----
@@ -2733,22 +2807,31 @@ size_t phase1_lds(int kmax, int nmax, int lists) {
 }
 
 hipError_t phase1_prepare() {
-    const hipError_t e =
-        hipFuncSetAttribute((const void*)k_phase1<0>, hipFuncAttributeMaxDynamicSharedMemorySize, kMaxBlockLds);
-    if (e != hipSuccess) return e;
-    return hipFuncSetAttribute((const void*)k_phase1<1>, hipFuncAttributeMaxDynamicSharedMemorySize, kMaxBlockLds);
+    for (const void* f : {(const void*)k_phase1<kPhase1Plain>, (const void*)k_phase1<kPhase1Legal>,
+                          (const void*)k_phase1<kPhase1Count>}) {
+        const hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, kMaxBlockLds);
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+}
+
+int conflict_words(int D, int n, int k) {
+    const ScanShape ss = scan_shape(n, k);
+    return count_by_masks(n, D, ss) ? ss.words : 0;
 }
 
 hipError_t launch_phase1(const GraphDev* gd, int G, int total_mem, int total_mt, int total_ex, int total_cf, int total_lg,
                          size_t lds, int honor_stop, int adv, int want, int mt_flags, int gsel, hipStream_t s) {
-    if (lds > (size_t)kMaxBlockLds) return hipErrorInvalidValue;
+    // no sequence both searches and counts
+    if (lds > (size_t)kMaxBlockLds || (total_lg > 0 && total_cf > 0)) return hipErrorInvalidValue;
     const dim3 grid(total_mem + total_lg + total_mt + total_ex + total_cf), blk(256);
-    if (total_lg > 0)
-        hipLaunchKernelGGL(k_phase1<1>, grid, blk, lds, s, gd, G, total_mem, total_mt, total_ex, total_cf, total_lg,
-                           honor_stop, adv, want, mt_flags, gsel);
-    else
-        hipLaunchKernelGGL(k_phase1<0>, grid, blk, lds, s, gd, G, total_mem, total_mt, total_ex, total_cf, 0, honor_stop,
-                           adv, want, mt_flags, gsel);
+#define TCOL_P1(KIND) \
+    hipLaunchKernelGGL(k_phase1<KIND>, grid, blk, lds, s, gd, G, total_mem, total_mt, total_ex, total_cf, total_lg, \
+                       honor_stop, adv, want, mt_flags, gsel)
+    if (total_lg > 0) TCOL_P1(kPhase1Legal);
+    else if (total_cf > 0) TCOL_P1(kPhase1Count);
+    else TCOL_P1(kPhase1Plain);
+#undef TCOL_P1
     TCOL_LAUNCH_CHECK();
     return hipSuccess;
 }
