@@ -614,7 +614,8 @@ static tcol_status rebuild_schedule(tcol_ctx* c) {
         d.cf_words = conflict_words(p.D, p.n, p.k);
         cf += conflict_blocks(p.D, p.n, d.cf_words);
         d.lg_begin = lg;
-        if (p.stop_on_legal) lg += p.D * search_parts(p.n);
+        d.lg_parts = search_parts(p.n, p.k);
+        if (p.stop_on_legal) lg += p.D * d.lg_parts;
         d.ps_begin = pg;
         if (d.psparse) pg += p.n;
         d.mt_begin = mt;

@@ -152,6 +152,7 @@ struct GraphDev {
     int cf_begin;             // blocks of the conflict counts
     int cf_words;             // words of a piece of their class masks (0: by compares)
     int lg_begin;             // blocks of the search for legal members
+    int lg_parts;             // blocks per member of that search
     int mt_begin;             // tiles of the group-concentration kernel
     int mt_T;                 // tiles per side
     int mt_ts;                // tile side of the group-concentration kernel (32 or 64)
@@ -267,10 +268,7 @@ __device__ inline int xcd_remap(int b, int nb) {
     return x * q + min(x, r) + i;
 }
 
-// blocks per member of the search for legal members (1024 vertices each: at n = 1000 one block's search to the end
-// takes about 6 us, less than the tiles of the same launch)
-__host__ __device__ inline int search_parts(int n) { return ceil_div(n, 1024); }
-// and of the conflict counts by masks (256 vertices each, 64 a wave)
+// blocks per member of the conflict counts by masks (256 vertices each, 64 a wave)
 __host__ __device__ inline int count_parts(int n) { return ceil_div(n, 256); }
 
 // find the graph that owns flattened work item `w` given a begin offset per graph

@@ -1525,7 +1525,7 @@ __device__ __forceinline__ void member_block(const GraphDev* __restrict__ gd, in
             const long long f = fsum[0] + fsum[1] + fsum[2] + fsum[3];
             d.feq[m] = f;
             // with an added fitness the member is legal only if that is 0 too
-            if (asks_legal(d, want)) legal_vote(d, st, m, search_parts(n) + 1, f != 0);
+            if (asks_legal(d, want)) legal_vote(d, st, m, d.lg_parts + 1, f != 0);
         }
     }
     if (lists) {
@@ -1674,7 +1674,7 @@ __device__ __forceinline__ void legal_block(const GraphDev* __restrict__ gd, int
     GraphState* st = d.st;
     if (honor_stop && (st->stopped || (adv && st->next_bad))) return;
     if (!asks_legal(d, want)) return;
-    const int n = d.n, k = d.k, parts = search_parts(n);
+    const int n = d.n, k = d.k, parts = d.lg_parts;
     const int loc = b - d.lg_begin;
     const int m = loc / parts, part = loc - m * parts;
     const int tid = threadIdx.x, lane = tid & 63;
@@ -2814,6 +2814,12 @@ hipError_t phase1_prepare() {
     }
     return hipSuccess;
 }
+
+// Blocks per member of the search for legal members: 1024 vertices each (n = 1000: one block's search to the end takes
+// about 6 us, less than the tiles of the same launch), 256, a strip a wave, where the masks take several pieces, each of
+// which waits for its loads (eight iterations with members one conflict from legal, D = 8, fp4: n = 1000, k = 300
+// 366 -> 322 us, 314 without the stop rule; n = 2000, k = 300 653 -> 590, 576).
+int search_parts(int n, int k) { return ceil_div(n, scan_shape(n, k).words < ceil_div(n, 64) ? 256 : 1024); }
 
 int conflict_words(int D, int n, int k) {
     const ScanShape ss = scan_shape(n, k);

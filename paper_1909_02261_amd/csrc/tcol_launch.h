@@ -71,6 +71,7 @@ hipError_t launch_advance(const GraphDev* gd, int G, hipStream_t s);
 hipError_t launch_loss(const GraphDev* gd, int G, int g, int ntiles, int fold, double* out, hipStream_t s);
 // fitness of every graph (report only) and graph g's results and colours out
 hipError_t launch_report(const GraphDev* gd, int G, int g, int fold, int16_t* colors, int64_t* fcol, int64_t* feq, hipStream_t s);
+int search_parts(int n, int k);
 // conflict counts of a graph: words of a piece of the class masks (0: by compares), and blocks
 int conflict_words(int D, int n, int k);
 inline int conflict_blocks(int D, int n, int words) { return D * (words ? count_parts(n) : ceil_div(n, 64)); }
